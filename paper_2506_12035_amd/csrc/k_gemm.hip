@@ -17,7 +17,8 @@
 // load operands straight from global memory into XOR-swizzled LDS stages and
 // write back through LDS in row-major order.
 //
-// fp32 path: plain FMA, 64x64 tiles, 4x4 outputs per thread.
+// fp32 path: fp32 matrix instructions, a 64x64 tile or, for few rows, a
+// workgroup per 16 columns whose wavefronts split K.
 #include "device_common.h"
 
 namespace marche {
@@ -1471,61 +1472,186 @@ static hipError_t run_bf16(const void *a, const void *w, int m, int n, int k, co
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ fp32 FMA
+// ------------------------------------------------------------------ fp32 (v_mfma_f32)
+//
+// fp32 products run on the fp32 matrix instructions (exact fp32 multiplies and
+// accumulation, twice the rate of the vector FMA).  Lanes load four
+// consecutive k of a row as one 16-byte read and spend them in four MFMAs:
+// both operands then carry the same permutation of k, which a dot product
+// does not see.
+//
+// Two kernels:
+//  - f32_tile: a 64x64x32 tile of four 32x32 wavefronts, operands straight
+//    from global memory into the 128-byte swizzled LDS rows of the bf16 tiles
+//    (32 floats per row), four stages;
+//  - f32_skinny: for products whose 64x64 tiles would not give every compute
+//    unit one.  These are bound by the latency of one workgroup's walk over K
+//    (a 64x64 FMA tile with two barriers per 16 of K took 182 us for 32 rows x
+//    768 x 3072 on 12 compute units), so a workgroup takes 16 columns and up
+//    to 64 rows, its 16 wavefronts split K, load both operands directly into
+//    the MFMA registers (64-byte row segments, every load of a wavefront
+//    independent of the others) and sum their partial tiles through LDS in
+//    wavefront order.
+// The split depends on K alone, so a row's result does not depend on how many
+// rows share the call within either kernel.
+namespace f32 {
 
-template <class Epi>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A,
-                                                       const float *__restrict__ W, int M, int N,
-                                                       int K, Epi epi) {
-  constexpr int T = 64, BK = 16;
-  __shared__ float As[BK][T + 4];
-  __shared__ float Ws[BK][T + 4];
-  const int tiles_n = N / T;
-  const int m0 = (blockIdx.x / tiles_n) * T, n0 = (blockIdx.x % tiles_n) * T;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int lr = tid >> 2, lc = (tid & 3) * 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    const float4 av =
-        *reinterpret_cast<const float4 *>(A + (size_t)min(m0 + lr, M - 1) * K + k0 + lc);
-    const float4 wv = *reinterpret_cast<const float4 *>(W + (size_t)(n0 + lr) * K + k0 + lc);
-    As[lc + 0][lr] = av.x; As[lc + 1][lr] = av.y; As[lc + 2][lr] = av.z; As[lc + 3][lr] = av.w;
-    Ws[lc + 0][lr] = wv.x; Ws[lc + 1][lr] = wv.y; Ws[lc + 2][lr] = wv.z; Ws[lc + 3][lr] = wv.w;
-    __syncthreads();
+constexpr int kWaves = 16;  // K slices of the skinny kernel
+
+__device__ __forceinline__ f32x4 mfma4(const f32x4 &w, const f32x4 &x, f32x4 acc) {
 #pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], x[e], acc, 0, 0, 0);
+  return acc;
+}
+
+}  // namespace f32
+
+// C^T blocks of 16 columns x MB * 16 rows: lane l holds column group l / 16
+// (four consecutive columns) of row l % 16 of each block.
+template <class Epi, int MB>
+__global__ __launch_bounds__(1024) void gemm_f32_skinny_kernel(const float *__restrict__ A,
+                                                               const float *__restrict__ W, int M,
+                                                               int N, int K, Epi epi) {
+  using namespace f32;
+  __shared__ f32x4 part[kWaves][MB][64];
+  const int tiles_n = N / 16;
+  const int n0 = (blockIdx.x % tiles_n) * 16, m0 = (blockIdx.x / tiles_n) * (MB * 16);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // steps of 16 k; wavefront w takes steps [w S / 16, (w + 1) S / 16)
+  const int steps = K / 16;
+  const int s0 = wave * steps / kWaves, s1 = (wave + 1) * steps / kWaves;
+  const int kl = (lane >> 4) * 4;
+  const float *wp = W + (size_t)(n0 + (lane & 15)) * K + kl;
+  const float *xp[MB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+  for (int i = 0; i < MB; ++i)
+    xp[i] = A + (size_t)min(m0 + i * 16 + (lane & 15), M - 1) * K + kl;
+  f32x4 acc[MB];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Ws[kk][tx * 4 + j];
+  for (int i = 0; i < MB; ++i) acc[i] = f32x4{};
+  constexpr int U = MB >= 4 ? 3 : 4;  // steps whose loads are in flight together
+  int s = s0;
+  for (; s + U <= s1; s += U) {
+    f32x4 w[U], x[U][MB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int u = 0; u < U; ++u) {
+      w[u] = *reinterpret_cast<const f32x4 *>(wp + (s + u) * 16);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+      for (int i = 0; i < MB; ++i)
+        x[u][i] = *reinterpret_cast<const f32x4 *>(xp[i] + (s + u) * 16);
     }
-    __syncthreads();
-  }
-  const f32x4 b = epi.bias4(n0 + tx * 4);
-  const typename Epi::Col c = epi.col(n0 + tx * 4);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= M) continue;
-    const typename Epi::Row r = epi.row(row);
-    const f32x4 v = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-    epi.store(r, row, c, v + b + (Epi::kPrior ? epi.prior(r, c) : f32x4{}));
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < MB; ++i) acc[i] = mfma4(w[u], x[u][i], acc[i]);
   }
+  for (; s < s1; ++s) {
+    const f32x4 w = *reinterpret_cast<const f32x4 *>(wp + s * 16);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+      acc[i] = mfma4(w, *reinterpret_cast<const f32x4 *>(xp[i] + s * 16), acc[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i) part[wave][i][lane] = acc[i];
+  __syncthreads();
+  if (wave >= MB) return;
+  f32x4 v = part[0][wave][lane];
+#pragma unroll
+  for (int g = 1; g < kWaves; ++g) v += part[g][wave][lane];
+  const int row = m0 + wave * 16 + (lane & 15), c0 = n0 + kl;
+  // the column's destination is uniform over the wavefront: computed by all
+  // lanes, before the row guard
+  const typename Epi::Col c = epi.col(c0);
+  if (row >= M) return;
+  const typename Epi::Row r = epi.row(row);
+  if constexpr (Epi::kPrior) v = v + epi.bias4(c0) + epi.prior(r, c);
+  else v = v + epi.bias4(c0);
+  epi.store(r, row, c, v);
+}
+
+// A 64x64x32 tile; `Frag`s are 16-byte chunks of 32 rows, as in the bf16 tiles.
+template <class Epi>
+__global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const float *A, const float *W, int M,
+                                                            int N, int K, Epi epi) {
+  using Row = typename Epi::Row;
+  constexpr int T = 64, NS = 4;
+  constexpr int kWOff = T * 128, kStage = 2 * T * 128;  // 8 KB per operand
+  constexpr int kStr = 36;                              // staged write-back row (floats)
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * kStage];
+  __shared__ __attribute__((aligned(16))) Row rows_lds[T];
+  static_assert(4 * 32 * kStr * 4 <= NS * kStage, "staged write-back fits the stages");
+  const int tiles_m = (M + T - 1) / T, tiles_n = N / T;
+  int tm, tn;
+  tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * T, n0 = tn * T;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
+  const int nk = K / 32;
+  // a k-tile of 32 floats is 64 16-bit elements to the loader
+  const bf16 *A2 = reinterpret_cast<const bf16 *>(A), *W2 = reinterpret_cast<const bf16 *>(W);
+  auto load_tile = [&](int t) {
+    const unsigned sb = lds0 + (unsigned)(t % NS) * kStage;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      big::load_lds(sb, wave * 2 + p, A2, M, 2 * K, m0, t * 64, lane);
+      big::load_lds(sb + kWOff, wave * 2 + p, W2, N, 2 * K, n0, t * 64, lane);
+    }
+  };
+  Row rec{};
+  if (tid < T) rec = epi.row(min(m0 + tid, M - 1));
+  const f32x4 bias = epi.bias4(n0 + wn * 32 + (lane & 7) * 4);
+  f32x16 acc[1][1] = {{f32x16{}}};
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < nk) load_tile(t);
+  for (int t = 0; t < nk; ++t) {
+    // k-tile t landed (issued so far: up to t + NS - 2, four loads each) and
+    // every wavefront done with k-tile t - 1, whose stage takes t + NS - 1
+    const int ahead = min(NS - 2, nk - 1 - t);
+    if (ahead >= 2) pair::barrier_vm<8>();
+    else if (ahead == 1) pair::barrier_vm<4>();
+    else pair::barrier_vm<0>();
+    if (t + NS - 1 < nk) load_tile(t + NS - 1);
+    const unsigned char *sc = smem + (t % NS) * kStage;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int kc = s * 2 + (lane >> 5);
+      const int rx = wm * 32 + (lane & 31), rw = wn * 32 + (lane & 31);
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(sc + rx * 128 + big::swz(rx, kc) * 16);
+      const f32x4 w = *reinterpret_cast<const f32x4 *>(sc + kWOff + rw * 128 + big::swz(rw, kc) * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], x[e], acc[0][0], 0, 0, 0);
+    }
+  }
+  if (tid < T) rows_lds[tid] = rec;
+  pair::barrier_vm<0>();
+  write_back_staged<1, 1, 4>(acc, epi, m0 + wm * 32, n0 + wn * 32, M, lane,
+                             reinterpret_cast<float *>(smem) + wave * 32 * kStr, rows_lds + wm * 32,
+                             bias);
 }
 
 template <class Epi>
 static hipError_t run_f32(const void *a, const void *w, int m, int n, int k, const Epi &epi,
                           hipStream_t s) {
   if (m == 0) return hipSuccess;
-  if (n % 64 != 0 || k % 16 != 0) return hipErrorInvalidValue;
-  const int grid = ((m + 63) / 64) * (n / 64);
-  launch_kernel(gemm_f32_kernel<Epi>, grid, 256, 0, s, static_cast<const float *>(a),
-                                            static_cast<const float *>(w), m, n, k, epi);
+  if (n % 64 != 0 || k % 32 != 0) return hipErrorInvalidValue;
+  const float *A = static_cast<const float *>(a), *W = static_cast<const float *>(w);
+  const long tiles = (long)((m + 63) / 64) * (n / 64);
+  // 64x64 tiles once every compute unit has one; below that the skinny kernel,
+  // with as few rows per workgroup as cover a small M
+  if (tiles >= device_cu_count())
+    launch_kernel(gemm_f32_tile_kernel<Epi>, (unsigned)tiles, 256, 0, s, A, W, m, n, k, epi);
+  else if (m <= 16)
+    launch_kernel(gemm_f32_skinny_kernel<Epi, 1>, n / 16, 1024, 0, s, A, W, m, n, k, epi);
+  else if (m <= 32)
+    launch_kernel(gemm_f32_skinny_kernel<Epi, 2>, n / 16, 1024, 0, s, A, W, m, n, k, epi);
+  else
+    launch_kernel(gemm_f32_skinny_kernel<Epi, 4>, (n / 16) * ((m + 63) / 64), 1024, 0, s, A, W, m,
+                  n, k, epi);
   return hipGetLastError();
 }
 
