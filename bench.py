@@ -123,10 +123,9 @@ def counter_class(name: str):
         for qb, q in (("8", "q256"), ("4", "q128"), ("2", "q64"), ("1", "q32")):
             if f"attn_reg_kernelILi{qb}E" in name or f"attn_reg_kernel<{qb}," in name:
                 return f"attention_{q}"
-    if "attn_mfma_kernel" in name:
-        for nw, q in (("4", "q128"), ("2", "q64"), ("1", "q32")):
-            if f"ELi{nw}ELb" in name or f"ELi{nw}EEEv" in name or f", {nw}, " in name:
-                return f"attention_{q}"
+    if "attn_gen_kernel" in name:
+        m = re.search(r"attn_gen_kernel(?:<\d+, |ILi\d+ELi)(\d)", name)
+        return {"1": "attention_q32", "2": "attention_q64", "4": "attention_q128"}[m.group(1)]
     for key, cls in (("gather_ln_kernel", "gather_ln"), ("attn_scores_kernel", "attn_scores"),
                      ("select_topk_kernel", "select_topk"), ("decoder_input_kernel", "decoder_input"),
                      ("row_map_kernel", "row_map"), ("fill_zero_kernel", "fill_zero")):

@@ -8,22 +8,22 @@
 // key tiles, with a running maximum and a rescaled running sum, and no K/V is
 // ever concatenated or copied.
 //
-// bf16 kernel (gfx950 MFMA, v_mfma_f32_32x32x16_bf16), one workgroup per
-// (image, head, chunk of NW*32 active queries), one wavefront per 32 queries:
-//   - K and V tiles of 64 keys stream global -> registers -> LDS, double
-//     buffered (the next tile's loads are in flight during this tile's math);
+// bf16 kernels (gfx950 MFMA, v_mfma_f32_32x32x16_bf16): one workgroup per
+// (image, head, chunk of active queries), one wavefront per 32 queries:
 //   - S^T = K Q^T is formed so that lane l owns query (l & 31): the row
 //     maximum and sum need one cross-half exchange, and the accumulator
 //     rescale is a per-lane scalar;
-//   - O^T = V^T P^T: P stays in registers (converted to bf16), V is stored
-//     transposed in LDS with the keys of every 16-key group permuted to match
-//     the accumulator layout of S^T, so each MFMA operand is one 16-byte read.
-// Softmax runs in the log2 domain with fp32 statistics.
-//
-// The same kernel also takes the two segments as separate buffers (SEG2):
-// key tiles of the first segment, then of the second, in one online-softmax
-// pass -- Appendix A's merge without concatenation, as the stand-alone
-// two-segment attention of Appendix B's comparison.
+//   - O^T = V^T P^T: P stays in registers (converted to bf16); the operand V^T
+//     comes from a transposing LDS read, or (resident kernel) from tiles stored
+//     transposed with the keys of every 16-key group permuted to match the
+//     accumulator layout of S^T.
+// Softmax runs in the log2 domain with fp32 statistics.  Three kernels:
+// attn_resident_kernel (full layers, every key of a head in LDS),
+// attn_reg_kernel (head width 64, whole key tiles) and attn_gen_kernel (any
+// other shape, among them the two segments of Appendix B's comparison as
+// separate buffers in one online-softmax pass: Appendix A's merge without
+// concatenation).
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -126,166 +126,6 @@ __device__ __forceinline__ void attn_tile(const bf16 *ks, const bf16 *vt, const 
         acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb, acc[d], 0, 0, 0);
       }
     }
-}
-
-// ALIGNED: every segment's length is a multiple of TK, so no key tile runs
-// past its segment and only the unmasked tile step is compiled.
-template <int DH, int NW, bool SEG2, bool ALIGNED>
-__global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(AttnArgs a, int chunks) {
-  constexpr int NT = NW * 64;
-  constexpr int KS = DH + 8;        // K tile row stride (elements)
-  constexpr int ODB = (DH + 31) / 32;
-  constexpr int DHV = ODB * 32;     // rows of the transposed V tile
-  constexpr int VS = TK + 8;        // V^T tile row stride (elements)
-  constexpr int CPR = DH / 8;       // 16-byte chunks per K/V row
-  constexpr int TCH = TK * CPR;     // chunks per tile per matrix
-  constexpr int LPT = (TCH + NT - 1) / NT;
-  constexpr int QS = DH / 16;       // k-steps of the QK^T contraction
-  __shared__ __attribute__((aligned(16))) bf16 Ks[2][TK * KS];
-  __shared__ __attribute__((aligned(16))) bf16 Vt[2][DHV * VS];
-
-  const int id = xcd_remap(blockIdx.x, gridDim.x);
-  const int bh = id / chunks, chunk = id - bh * chunks;
-  const int b = bh / a.n_heads, h = bh - b * a.n_heads;
-  const int r0 = a.a_off ? a.a_off[b] : b * a.a_max;
-  const int na = a.a_off ? a.a_off[b + 1] - r0 : a.a_max;
-  const int q0 = chunk * NW * 32;
-  if (q0 >= na) return;  // uniform over the workgroup
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int N = a.n_tokens, D = a.d_model;
-  const int N2 = SEG2 ? a.n2 : 0;
-  const bf16 *kg = static_cast<const bf16 *>(a.k_cache) + (size_t)(b * a.n_heads + h) * N * DH;
-  const bf16 *vg = static_cast<const bf16 *>(a.v_cache) + (size_t)(b * a.n_heads + h) * N * DH;
-  const bf16 *kg2 = SEG2 ? static_cast<const bf16 *>(a.k2) + (size_t)(b * a.n_heads + h) * N2 * DH : kg;
-  const bf16 *vg2 = SEG2 ? static_cast<const bf16 *>(a.v2) + (size_t)(b * a.n_heads + h) * N2 * DH : vg;
-  const int nt1 = (N + TK - 1) / TK;
-  // key tile t: first segment for t < nt1, else the second; its first key
-  // within the segment and the segment's length
-  auto seg_of = [&](int t, const bf16 *&kb, const bf16 *&vb, int &t0, int &ns) {
-    if (!SEG2 || t < nt1) {
-      kb = kg; vb = vg; t0 = t * TK; ns = N;
-    } else {
-      kb = kg2; vb = vg2; t0 = (t - nt1) * TK; ns = N2;
-    }
-  };
-
-  // V^T rows beyond DH (padding up to a multiple of 32) hold zeros.
-  if constexpr (DHV > DH) {
-    for (int i = tid; i < 2 * (DHV - DH) * VS; i += NT) {
-      const int buf = i / ((DHV - DH) * VS), rem = i % ((DHV - DH) * VS);
-      Vt[buf][DH * VS + rem] = (bf16)0.0f;
-    }
-  }
-
-  // This wavefront's queries as the B operand of S^T = K Q^T.
-  const int wq0 = q0 + wave * 32;
-  const int qi = wq0 + (lane & 31);
-  const bf16 *qrow = static_cast<const bf16 *>(a.q) + (size_t)(r0 + min(qi, na - 1)) * D + h * DH;
-  bf16x8 qf[QS];
-#pragma unroll
-  for (int s = 0; s < QS; ++s)
-    qf[s] = *reinterpret_cast<const bf16x8 *>(qrow + s * 16 + (lane >> 5) * 8);
-
-  // K tiles are staged as 16-byte chunks; V tiles as pairs of keys so that
-  // the transposed write to LDS packs two keys into one 32-bit word (keys 2p
-  // and 2p+1 are adjacent in the permuted layout).
-  constexpr int VPCH = TCH / 2;
-  constexpr int LPV = (VPCH + NT - 1) / NT;
-  u32x4 rk[LPT], rv0[LPV], rv1[LPV];
-  auto gload = [&](int t) {
-    const bf16 *kb, *vb;
-    int t0, ns;
-    seg_of(t, kb, vb, t0, ns);
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-      const int c = i * NT + tid;
-      if (c < TCH) {
-        const int key = min(t0 + c / CPR, ns - 1), d = (c % CPR) * 8;
-        rk[i] = *reinterpret_cast<const u32x4 *>(kb + (size_t)key * DH + d);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < LPV; ++i) {
-      const int c = i * NT + tid;
-      if (c < VPCH) {
-        const int kp = c / CPR, d = (c % CPR) * 8;
-        const int k0 = min(t0 + 2 * kp, ns - 1), k1 = min(t0 + 2 * kp + 1, ns - 1);
-        rv0[i] = *reinterpret_cast<const u32x4 *>(vb + (size_t)k0 * DH + d);
-        rv1[i] = *reinterpret_cast<const u32x4 *>(vb + (size_t)k1 * DH + d);
-      }
-    }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-      const int c = i * NT + tid;
-      if (c < TCH) {
-        const int key = c / CPR, d = (c % CPR) * 8;
-        *reinterpret_cast<u32x4 *>(&Ks[buf][key * KS + d]) = rk[i];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < LPV; ++i) {
-      const int c = i * NT + tid;
-      if (c < VPCH) {
-        const int kp = c / CPR, d = (c % CPR) * 8;
-        const int pos = ((2 * kp) & ~15) | vperm16((2 * kp) & 15);
-        unsigned *vt = reinterpret_cast<unsigned *>(&Vt[buf][d * VS + pos]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const unsigned w0 = rv0[i][e >> 1], w1 = rv1[i][e >> 1];
-          const unsigned lo = (e & 1) ? (w0 >> 16) : (w0 & 0xFFFFu);
-          const unsigned hi = (e & 1) ? (w1 & 0xFFFF0000u) : (w1 << 16);
-          vt[e * (VS / 2)] = lo | hi;
-        }
-      }
-    }
-  };
-
-  const float sl2 = 1.4426950408889634f / sqrtf((float)DH);  // log2(e) / sqrt(d_h)
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x16 acc[ODB];
-#pragma unroll
-  for (int d = 0; d < ODB; ++d) acc[d] = f32x16{};
-
-  const int ntiles = nt1 + (SEG2 ? (N2 + TK - 1) / TK : 0);
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    const int cur = t & 1;
-    int t0 = t * TK, ns = N;
-    if constexpr (SEG2) {
-      const bf16 *kb, *vb;
-      seg_of(t, kb, vb, t0, ns);
-    }
-    const bool more = t + 1 < ntiles;
-    if (more) gload(t + 1);
-    if (ALIGNED || t0 + TK <= ns)
-      attn_tile<DH>(Ks[cur], Vt[cur], qf, acc, m_run, l_run, t0, ns, sl2, lane);
-    else
-      attn_tile<DH, false, true>(Ks[cur], Vt[cur], qf, acc, m_run, l_run, t0, ns, sl2, lane);
-    if (more) sstore(cur ^ 1);
-    __syncthreads();
-  }
-
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const float inv = 1.0f / l_tot;
-  if (qi < na) {
-    bf16 *orow = static_cast<bf16 *>(a.o) + (size_t)(r0 + qi) * D + h * DH;
-#pragma unroll
-    for (int d = 0; d < ODB; ++d)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int dh0 = d * 32 + g * 8 + (lane >> 5) * 4;
-        if (dh0 < DH) {
-          bf16x4 pk = {(bf16)(acc[d][4 * g + 0] * inv), (bf16)(acc[d][4 * g + 1] * inv),
-                       (bf16)(acc[d][4 * g + 2] * inv), (bf16)(acc[d][4 * g + 3] * inv)};
-          *reinterpret_cast<bf16x4 *>(orow + dh0) = pk;
-        }
-      }
-  }
 }
 
 // ------------------------------------------------------------ cache-aware kernel, head width 64
@@ -590,6 +430,287 @@ __global__ __launch_bounds__(QB * 64) void attn_reg_kernel(AttnArgs a, int chunk
   }
 }
 
+// ------------------------------------------------------------ general streaming kernel
+//
+// Every other shape: head width 80, key counts that are no multiple of a tile,
+// two key segments, and calls with too few (image, head) pairs to fill the
+// chip.  The tile step and LDS layout follow attn_reg_kernel (row-major K and
+// V, V^T from the transposing LDS read); in addition
+//  - key tiles of the first segment are followed by those of the second, and a
+//    segment's last tile may be partial (ALIGNED: none is, and no masked tile
+//    step is compiled);
+//  - KS groups of QB wavefronts share a workgroup: group g takes the key tiles
+//    t = g mod KS with LDS slots of its own, and the groups' (maximum, sum,
+//    output) are merged in group order at the end.  With few workgroups a
+//    compute unit then walks KS tiles at a time instead of one;
+//  - stats (optional) receives each row's final maximum (log2 domain) and
+//    1 / sum, which the stand-alone score pass reads.
+// Head width 80: K rows of 176 and V rows of 192 bytes, so that the 16 rows of
+// a K fragment read and the 4 rows of a V^T read start on distinct bank
+// groups without a permutation; the V^T rows past 80 are whatever the padding
+// holds and only reach output rows that are never stored.
+namespace gen {
+
+template <int DH>
+struct Lay {
+  static constexpr bool SWZ = DH == 64;
+  static constexpr int CPR = DH / 8;                 // 16-byte chunks per row
+  static constexpr int KSTR = SWZ ? 128 : 176;       // bytes per K row
+  static constexpr int VSTR = SWZ ? 128 : 192;       // bytes per V row
+  static constexpr int VOFF = TK * KSTR;
+  static constexpr int SLOT = TK * (KSTR + VSTR);
+  static constexpr int ODB = (DH + 31) / 32;
+  __device__ __forceinline__ static int k_at(int row, int c) {
+    return row * KSTR + ((SWZ ? c ^ strm::swz(row) : c) << 4);
+  }
+  __device__ __forceinline__ static int v_at(int row, int c) {
+    return VOFF + row * VSTR + ((SWZ ? c ^ strm::swz(row) : c) << 4);
+  }
+};
+
+// One tile of the online softmax (as strm::tile) of which the first `left`
+// keys exist (uniform).
+template <int DH, bool ALIGNED>
+__device__ __forceinline__ void tile(const unsigned char *slot, const bf16x8 (&qf)[DH / 16],
+                                     f32x16 (&acc)[Lay<DH>::ODB], float &m_run, float &l_run,
+                                     float sl2, int left, int lane) {
+  using L = Lay<DH>;
+  f32x16 s[2];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    s[kb] = f32x16{};
+    const int row = kb * 32 + (lane & 31);
+#pragma unroll
+    for (int st = 0; st < DH / 16; ++st) {
+      const bf16x8 ka =
+          *reinterpret_cast<const bf16x8 *>(slot + L::k_at(row, st * 2 + (lane >> 5)));
+      s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[st], s[kb], 0, 0, 0);
+    }
+  }
+  if constexpr (!ALIGNED) {
+    if (left < TK) {
+      asm volatile("");  // keeps the branch: if-converted, every tile would pay for the mask
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3) >= left) s[kb][r] = -INFINITY;
+    }
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  const float m_new = fmaxf(m_run, mx * sl2);
+  const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+  float psum = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], sl2, -m_new));
+      s[kb][r] = p;
+      psum += p;
+    }
+  l_run = l_run * alpha + psum;
+  m_run = m_new;
+#pragma unroll
+  for (int d = 0; d < L::ODB; ++d) acc[d] *= alpha;
+  const int g = lane >> 4, e = (lane & 15) >> 2, q = lane & 3, hf = lane >> 5;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      bf16x8 pb;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) pb[j] = (bf16)s[kb][8 * u + j];
+#pragma unroll
+      for (int db = 0; db < L::ODB; ++db) {
+        const int c = db * 4 + (g & 1) * 2 + (q >> 1);
+        const int row = kb * 32 + u * 16 + 4 * hf + e;
+        const strm::s16x4 v8[2] = {strm::read_tr(slot + L::v_at(row, c) + (q & 1) * 8),
+                                   strm::read_tr(slot + L::v_at(row + 8, c) + (q & 1) * 8)};
+        const bf16x8 va = *reinterpret_cast<const bf16x8 *>(v8);
+        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb, acc[db], 0, 0, 0);
+      }
+    }
+}
+
+}  // namespace gen
+
+template <int DH, int QB, int KS, bool SEG2, bool ALIGNED>
+__global__ __launch_bounds__(QB *KS * 64) void attn_gen_kernel(AttnArgs a, int chunks) {
+  using L = gen::Lay<DH>;
+  constexpr int GT = QB * 64;                        // threads of a key group
+  constexpr int MPL = 512 / GT;                      // chunks 0..7 of 64 rows: per lane
+  constexpr int TAIL = DH == 80 ? 256 : 0;           // chunks 8 and 9 of K's and V's rows
+  constexpr int TPL = TAIL / GT;
+  static_assert(512 % GT == 0 && TAIL % GT == 0, "whole chunks per lane");
+  constexpr int kMerge = KS > 1 ? (KS - 1) * QB * (L::ODB * 16 + 2) * 256 : 0;
+  // A group of one wavefront needs no second slot (nor barriers): its LDS
+  // operations are in order, so it overwrites a tile once it has read it, and
+  // twice as many workgroups fit.
+  constexpr int SLOTS = QB == 1 ? 1 : 2;
+  constexpr int kTiles = SLOTS * KS * L::SLOT;
+  constexpr int kSmem = kTiles > kMerge ? kTiles : kMerge;
+  auto group_sync = [] {
+    if constexpr (QB == 1) __builtin_amdgcn_wave_barrier();
+    else __syncthreads();
+  };
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmem];
+
+  const int id = xcd_remap(blockIdx.x, gridDim.x);
+  const int bh = id / chunks, chunk = id - bh * chunks;
+  const int b = bh / a.n_heads, h = bh - b * a.n_heads;
+  const int r0 = a.a_off ? a.a_off[b] : b * a.a_max;
+  const int na = a.a_off ? a.a_off[b + 1] - r0 : a.a_max;
+  const int q0 = chunk * QB * 32;
+  if (q0 >= na) return;  // uniform over the workgroup
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave / QB, qb = wave - grp * QB;
+  const int gt = qb * 64 + lane;
+  const int N1 = a.n_tokens, N2 = SEG2 ? a.n2 : 0, D = a.d_model;
+  const bf16 *kg = static_cast<const bf16 *>(a.k_cache) + (size_t)bh * N1 * DH;
+  const bf16 *vg = static_cast<const bf16 *>(a.v_cache) + (size_t)bh * N1 * DH;
+  const bf16 *kg2 = SEG2 ? static_cast<const bf16 *>(a.k2) + (size_t)bh * N2 * DH : kg;
+  const bf16 *vg2 = SEG2 ? static_cast<const bf16 *>(a.v2) + (size_t)bh * N2 * DH : vg;
+  const int nt1 = (N1 + TK - 1) / TK, nt = nt1 + (N2 + TK - 1) / TK;
+  // rows of tile t that exist (>= 1), and its first row in K and V
+  auto tile_of = [&](int t, const bf16 *&kb, const bf16 *&vb) {
+    const bool s1 = !SEG2 || t < nt1;
+    const int t0 = (s1 ? t : t - nt1) * TK;
+    kb = (s1 ? kg : kg2) + (size_t)t0 * DH;
+    vb = (s1 ? vg : vg2) + (size_t)t0 * DH;
+    return (s1 ? N1 : N2) - t0;
+  };
+
+  const int qi = q0 + qb * 32 + (lane & 31);
+  const bf16 *qrow = static_cast<const bf16 *>(a.q) + (size_t)(r0 + min(qi, na - 1)) * D + h * DH;
+  bf16x8 qf[DH / 16];
+#pragma unroll
+  for (int s = 0; s < DH / 16; ++s)
+    qf[s] = *reinterpret_cast<const bf16x8 *>(qrow + s * 16 + (lane >> 5) * 8);
+
+  // Lane gt moves chunk gt % 8 of rows gt / 8 + (GT / 8) i of K and V and, at
+  // head width 80, tail chunks 8 + gt % 2 (rows of K, then of V).  Loads are
+  // unconditional: rows past a segment's end repeat its last one.
+  u32x4 rk[MPL], rv[MPL], rtl[TPL ? TPL : 1];
+  auto gload = [&](int t) {
+    const bf16 *kb, *vb;
+    const int last = tile_of(min(t, nt - 1), kb, vb) - 1;
+#pragma unroll
+    for (int i = 0; i < MPL; ++i) {
+      const int row = (gt >> 3) + i * (GT / 8);
+      const uint32_t off = (uint32_t)((ALIGNED ? row : min(row, last)) * DH + (gt & 7) * 8);
+      rk[i] = *reinterpret_cast<const u32x4 *>(kb + off);
+      rv[i] = *reinterpret_cast<const u32x4 *>(vb + off);
+    }
+#pragma unroll
+    for (int i = 0; i < TPL; ++i) {
+      const int j = i * GT + gt, row = (j & 127) >> 1;
+      const uint32_t off = (uint32_t)((ALIGNED ? row : min(row, last)) * DH + 64 + (j & 1) * 8);
+      rtl[i] = *reinterpret_cast<const u32x4 *>((j < 128 ? kb : vb) + off);
+    }
+  };
+  auto sstore = [&](unsigned char *slot) {
+#pragma unroll
+    for (int i = 0; i < MPL; ++i) {
+      const int row = (gt >> 3) + i * (GT / 8);
+      *reinterpret_cast<u32x4 *>(slot + L::k_at(row, gt & 7)) = rk[i];
+      *reinterpret_cast<u32x4 *>(slot + L::v_at(row, gt & 7)) = rv[i];
+    }
+#pragma unroll
+    for (int i = 0; i < TPL; ++i) {
+      const int j = i * GT + gt, row = (j & 127) >> 1, c = 8 + (j & 1);
+      *reinterpret_cast<u32x4 *>(slot + (j < 128 ? L::k_at(row, c) : L::v_at(row, c))) = rtl[i];
+    }
+  };
+
+  const float sl2 = 1.4426950408889634f / sqrtf((float)DH);  // log2(e) / sqrt(d_h)
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 acc[L::ODB];
+#pragma unroll
+  for (int d = 0; d < L::ODB; ++d) acc[d] = f32x16{};
+  // a wavefront whose queries all lie past the active set only moves tiles
+  const bool live = q0 + qb * 32 < na;
+  unsigned char *slots = smem + grp * SLOTS * L::SLOT;
+  gload(grp);
+  sstore(slots);
+  group_sync();
+  const int rounds = (nt + KS - 1) / KS;
+#pragma unroll 1
+  for (int it = 0; it < rounds; ++it) {
+    const int t = it * KS + grp;
+    gload(t + KS);
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned char *sp = slots + (it & (SLOTS - 1)) * L::SLOT;
+    if (live && t < nt) {
+      const bf16 *kb, *vb;
+      const int left = ALIGNED ? TK : tile_of(t, kb, vb);
+      gen::tile<DH, ALIGNED>(sp, qf, acc, m_run, l_run, sl2, left, lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    sstore(slots + ((it + 1) & (SLOTS - 1)) * L::SLOT);
+    group_sync();
+  }
+
+  l_run += __shfl_xor(l_run, 32, 64);
+  if constexpr (KS > 1) {
+    if constexpr (QB == 1) __syncthreads();  // every group is done with its slot
+    constexpr int REC = (L::ODB * 16 + 2) * 64;  // floats per wavefront
+    float *rec = reinterpret_cast<float *>(smem) + ((grp - 1) * QB + qb) * REC + lane;
+    if (grp > 0) {
+      rec[0] = m_run;
+      rec[64] = l_run;
+#pragma unroll
+      for (int d = 0; d < L::ODB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) rec[(2 + d * 16 + r) * 64] = acc[d][r];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int g2 = 0; g2 < KS - 1; ++g2) {
+      const float *o2 = reinterpret_cast<const float *>(smem) + (g2 * QB + qb) * REC + lane;
+      // group 0 always holds a key, so m_new is finite wherever the logits are
+      const float m2 = o2[0], m_new = fmaxf(m_run, m2);
+      const float a1 = __builtin_amdgcn_exp2f(m_run - m_new);
+      const float a2 = __builtin_amdgcn_exp2f(m2 - m_new);
+      l_run = l_run * a1 + o2[64] * a2;
+      m_run = m_new;
+#pragma unroll
+      for (int d = 0; d < L::ODB; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          acc[d][r] = acc[d][r] * a1 + o2[(2 + d * 16 + r) * 64] * a2;
+    }
+  }
+  const float inv = 1.0f / l_run;
+  if (qi < na) {
+    bf16 *orow = static_cast<bf16 *>(a.o) + (size_t)(r0 + qi) * D + h * DH;
+#pragma unroll
+    for (int d = 0; d < L::ODB; ++d)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int dh0 = d * 32 + g * 8 + (lane >> 5) * 4;
+        if (dh0 < DH) {
+          bf16x4 pk = {(bf16)(acc[d][4 * g + 0] * inv), (bf16)(acc[d][4 * g + 1] * inv),
+                       (bf16)(acc[d][4 * g + 2] * inv), (bf16)(acc[d][4 * g + 3] * inv)};
+          *reinterpret_cast<bf16x4 *>(orow + dh0) = pk;
+        }
+      }
+    if (a.stats && lane < 32) {
+      float *st = a.stats + ((size_t)(r0 + qi) * a.n_heads + h) * 2;
+      st[0] = m_run;
+      st[1] = inv;
+    }
+  }
+}
+
 // Every query of an image in one workgroup and every key resident in LDS
 // (layers where all N <= NTL * 64 tokens are active): one workgroup per
 // (image, head); wavefront w owns the NQB 32-query blocks w, w + NW, ...  All
@@ -821,17 +942,21 @@ __global__ __launch_bounds__(NW * 64) void attn_resident_kernel(AttnArgs a) {
 
 constexpr int RES_NTL = 5;    // keys resident: 320
 constexpr int RES_QMAX = 320; // queries per workgroup
+constexpr int RES_QMIN = 128; // queries below which the streaming kernels are used
 
-// Host choice of the resident kernel: more than 64 active queries per image
-// (where the streaming kernel needs several workgroups per (image, head)), all
-// of them and all keys within one workgroup's reach, one key segment.
+// Host choice of the resident kernel: more than 128 active queries in some
+// image (below that one streaming workgroup of four wavefronts covers an
+// (image, head), reads each K/V element once as well and skips wavefronts
+// without queries: 64 images x 16 heads with 9..71 queries of width 64
+// measured 25.5 against 30.7 us), all of them and all keys within one
+// workgroup's reach, one key segment.
 // Query blocks per workgroup of the streaming kernel for a_max rows.
 static int reg_qb(int32_t a_max) {
   return a_max <= 32 ? 1 : a_max <= 64 ? 2 : a_max <= 128 ? 4 : 8;
 }
 
 bool attn_resident(int32_t a_max, int32_t n_tokens, bool two_segments) {
-  return !two_segments && a_max > 64 && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
+  return !two_segments && a_max > RES_QMIN && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
 }
 
 bool attn_fuses_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_t gen_max) {
@@ -841,15 +966,14 @@ bool attn_fuses_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_
   return attn_streams(head_dim, n_tokens, false) && 2 * ((gen_max + 31) / 32) <= reg_qb(a_max);
 }
 
-template <int DH, int NW, bool SEG2>
-static hipError_t run_attn_mfma(const AttnArgs &a, hipStream_t s) {
-  const int chunks = (a.a_max + NW * 32 - 1) / (NW * 32);
+template <int DH, int QB, int KS, bool SEG2>
+static hipError_t run_attn_gen(const AttnArgs &a, hipStream_t s) {
+  const int chunks = (a.a_max + QB * 32 - 1) / (QB * 32);
   const int grid = a.batch * a.n_heads * chunks;
-  const bool aligned = a.n_tokens % TK == 0 && (!SEG2 || a.n2 % TK == 0);
-  if (aligned)
-    launch_kernel(attn_mfma_kernel<DH, NW, SEG2, true>, grid, NW * 64, 0, s, a, chunks);
+  if (a.n_tokens % TK == 0 && (!SEG2 || a.n2 % TK == 0))
+    launch_kernel(attn_gen_kernel<DH, QB, KS, SEG2, true>, grid, QB * KS * 64, 0, s, a, chunks);
   else
-    launch_kernel(attn_mfma_kernel<DH, NW, SEG2, false>, grid, NW * 64, 0, s, a, chunks);
+    launch_kernel(attn_gen_kernel<DH, QB, KS, SEG2, false>, grid, QB * KS * 64, 0, s, a, chunks);
   return hipGetLastError();
 }
 
@@ -871,17 +995,54 @@ static hipError_t run_attn_reg(const AttnArgs &a, hipStream_t s) {
 }
 
 
+// Query blocks per workgroup, key groups, and whether attn_reg_kernel runs.
+struct AttnShape {
+  int qb, ks;
+  bool reg;
+};
+
+// Launch shape of the streaming kernels.  QB wavefronts of 32 queries per
+// workgroup: as many as the largest active set needs, up to four (eight in
+// attn_reg_kernel).  Two key groups where QB <= 2 and the grid is no more than
+// one workgroup per compute unit: a workgroup's time is then its serial walk
+// over the key tiles (16 images x 16 heads of width 80, 45 queries x 1548
+// keys: 33.4 us with one group, 26.4 with two; with 512 workgroups or more
+// two groups only shrink the number resident: 19.1 against 22.2 us at 1024).
+// Longer query lists on a nearly empty chip take two wavefronts per workgroup
+// for the same reason (16 (image, head) pairs, 150 queries x 1088 keys: 21.6
+// against 14.4 us).  The layer step asks for half the workgroups before it
+// splits, so that an image range and the batch it is part of run the same
+// kernel (and sum in the same order) down to about 8 images.
+static AttnShape attn_shape(const AttnArgs &a) {
+  const int64_t bh = (int64_t)a.batch * a.n_heads;
+  const int q = a.a_max <= 32 ? 1 : 2;
+  const int64_t few = a.a_off ? device_cu_count() / 2 : device_cu_count();
+  const bool split = bh * ((a.a_max + 32 * q - 1) / (32 * q)) <= few;
+  if (attn_streams(a.head_dim, a.n_tokens, a.k2 != nullptr) && !a.stats && (a.scores || !split))
+    return {reg_qb(a.a_max), 1, true};  // eight: one pass over K/V per 256 queries
+  return {split ? q : std::min(reg_qb(a.a_max), 4), split ? 2 : 1, false};
+}
+
+int attn_query_blocks(const AttnArgs &a) { return attn_shape(a).qb; }
+
 template <int DH, bool SEG2>
 static hipError_t attn_bf16_nw(const AttnArgs &a, hipStream_t s) {
-  if (attn_streams(DH, a.n_tokens, SEG2)) {
-    if (a.a_max <= 32) return run_attn_reg<1>(a, s);
-    if (a.a_max <= 64) return run_attn_reg<2>(a, s);
-    if (a.a_max <= 128) return run_attn_reg<4>(a, s);
-    return run_attn_reg<8>(a, s);  // one pass over K/V per 256 queries
+  const AttnShape f = attn_shape(a);
+  if constexpr (DH == 64 && !SEG2) {
+    if (f.reg) {
+      switch (f.qb) {
+        case 1: return run_attn_reg<1>(a, s);
+        case 2: return run_attn_reg<2>(a, s);
+        case 4: return run_attn_reg<4>(a, s);
+        default: return run_attn_reg<8>(a, s);
+      }
+    }
   }
-  if (a.a_max <= 32) return run_attn_mfma<DH, 1, SEG2>(a, s);
-  if (a.a_max <= 64) return run_attn_mfma<DH, 2, SEG2>(a, s);
-  return run_attn_mfma<DH, 4, SEG2>(a, s);
+  if (f.qb == 1)
+    return f.ks == 2 ? run_attn_gen<DH, 1, 2, SEG2>(a, s) : run_attn_gen<DH, 1, 1, SEG2>(a, s);
+  if (f.qb == 2)
+    return f.ks == 2 ? run_attn_gen<DH, 2, 2, SEG2>(a, s) : run_attn_gen<DH, 2, 1, SEG2>(a, s);
+  return run_attn_gen<DH, 4, 1, SEG2>(a, s);
 }
 
 template <int DH>
@@ -962,58 +1123,155 @@ hipError_t launch_concat_kv(DType dt, void *k_dst, void *v_dst, const void *k_a,
   return hipGetLastError();
 }
 
-// fp32 attention: one wavefront per (active row, head).  Logits are formed
-// lane-per-key, then the output lane-per-dimension; exact expf.
-template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
+// fp32 attention: one workgroup per (image, head, R active rows).  Four lanes
+// share a key (each holds DH / 4 dims in 16-byte pieces, so a load instruction
+// covers 64 bytes of 16 keys and two shuffles finish a dot product), the
+// logits of every key stay in LDS, the softmax runs over them with exact expf,
+// and the output is formed with DH / 4 lanes per key, the lane groups' partial
+// sums added in group order.  Its time at a few dozen rows is load latency:
+// one wavefront per (row, head) walking its keys one by one took 20 us at 32
+// rows x 12 heads x 320 keys.  R = 4 where there are enough rows to fill the
+// chip (each K/V element read then serves four rows).
+// stats (optional): the row's maximum logit and 1 / sum, [row][head][2].
+template <int DH, int R>
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int chunks) {
+  constexpr int C4 = DH / 16;       // 16-byte pieces per lane of a key
+  constexpr int LPD = DH / 4;       // lanes per key when forming the output
+  constexpr int G = 256 / LPD;      // keys in flight there: 16 or 12
   extern __shared__ float smem[];
-  float *qs = smem;          // [DH]
-  float *ps = smem + DH;     // [N]
-  const int gw = blockIdx.x;
-  const int row = gw / a.n_heads, h = gw - row * a.n_heads;
-  const int lane = threadIdx.x;
+  float *ps = smem;                 // [R][N]
+  float *red = ps + R * a.n_tokens; // [4][R], then the output partials [G][R][DH]
+  const int bh = blockIdx.x / chunks, chunk = blockIdx.x - bh * chunks;
+  const int b = bh / a.n_heads, h = bh - b * a.n_heads;
+  const int r0 = a.a_off[b], na = a.a_off[b + 1] - r0;
+  const int q0 = chunk * R;
+  if (q0 >= na) return;  // uniform over the workgroup
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int N = a.n_tokens, D = a.d_model;
-  const RowMap m = a.map[row];
-  const size_t head_base = (size_t)(m.b * a.n_heads + h) * N * DH;
-  const float *kg = static_cast<const float *>(a.k_cache) + head_base;
-  const float *vg = static_cast<const float *>(a.v_cache) + head_base;
-  const float *qg = static_cast<const float *>(a.q) + (size_t)row * D + h * DH;
-  for (int d = lane; d < DH; d += 64) qs[d] = qg[d];
-  __syncthreads();
+  const float *kg = static_cast<const float *>(a.k_cache) + (size_t)bh * N * DH;
+  const float *vg = static_cast<const float *>(a.v_cache) + (size_t)bh * N * DH;
   const float scale = 1.0f / sqrtf((float)DH);
-  float mx = -INFINITY;
-  for (int j = lane; j < N; j += 64) {
-    const float *kr = kg + (size_t)j * DH;
-    float acc = 0.f;
-#pragma unroll 8
-    for (int d = 0; d < DH; ++d) acc = fmaf(qs[d], kr[d], acc);
-    acc *= scale;
-    ps[j] = acc;
-    mx = fmaxf(mx, acc);
+  const int li = lane & 3;
+  f32x4 q[R][C4];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const float *qg =
+        static_cast<const float *>(a.q) + (size_t)(r0 + min(q0 + r, na - 1)) * D + h * DH;
+#pragma unroll
+    for (int c = 0; c < C4; ++c) q[r][c] = *reinterpret_cast<const f32x4 *>(qg + c * 16 + li * 4);
   }
-  mx = wave_max(mx);
-  float sum = 0.f;
-  for (int j = lane; j < N; j += 64) {
-    const float e = expf(ps[j] - mx);
-    ps[j] = e;
-    sum += e;
+  float mx[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) mx[r] = -INFINITY;
+#pragma unroll 2
+  for (int j0 = 0; j0 < N; j0 += 64) {
+    const int j = j0 + (tid >> 2);
+    const float *kr = kg + (size_t)min(j, N - 1) * DH + li * 4;
+    f32x4 k[C4];
+#pragma unroll
+    for (int c = 0; c < C4; ++c) k[c] = *reinterpret_cast<const f32x4 *>(kr + c * 16);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float d = 0.f;
+#pragma unroll
+      for (int c = 0; c < C4; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d = fmaf(q[r][c][e], k[c][e], d);
+      d += __shfl_xor(d, 1, 64);
+      d += __shfl_xor(d, 2, 64);
+      d *= scale;
+      if (j < N) {
+        if (li == 0) ps[r * N + j] = d;
+        mx[r] = fmaxf(mx[r], d);
+      }
+    }
   }
-  sum = wave_sum(sum);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    mx[r] = wave_max(mx[r]);
+    if (lane == 0) red[wave * R + r] = mx[r];
+  }
   __syncthreads();
-  const float inv = 1.0f / sum;
-  float *og = static_cast<float *>(a.o) + (size_t)row * D + h * DH;
-  for (int d = lane; d < DH; d += 64) {
-    float acc = 0.f;
-    for (int j = 0; j < N; ++j) acc = fmaf(ps[j], vg[(size_t)j * DH + d], acc);
-    og[d] = acc * inv;
+  float sum[R], inv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    mx[r] = fmaxf(fmaxf(red[r], red[R + r]), fmaxf(red[2 * R + r], red[3 * R + r]));
+    sum[r] = 0.f;
+    for (int j = tid; j < N; j += 256) {
+      const float e = expf(ps[r * N + j] - mx[r]);
+      ps[r * N + j] = e;
+      sum[r] += e;
+    }
+    sum[r] = wave_sum(sum[r]);
   }
+  __syncthreads();  // the maxima have been read
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane == 0) red[wave * R + r] = sum[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    inv[r] = 1.0f / ((red[r] + red[R + r]) + (red[2 * R + r] + red[3 * R + r]));
+  if (a.stats && tid < R && q0 + tid < na) {
+    float m_r = 0.f, i_r = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (tid == r) { m_r = mx[r]; i_r = inv[r]; }
+    float *st = a.stats + ((size_t)(r0 + q0 + tid) * a.n_heads + h) * 2;
+    st[0] = m_r;
+    st[1] = i_r;
+  }
+  __syncthreads();  // the sums have been read: red becomes the output partials
+  const int g = tid / LPD, dl = (tid - g * LPD) * 4;
+  if (g < G) {
+    f32x4 acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = f32x4{};
+#pragma unroll 4
+    for (int j = g; j < N; j += G) {
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(vg + (size_t)j * DH + dl);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float p = ps[r * N + j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[r][e] = fmaf(p, v[e], acc[r][e]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[(g * R + r) * DH + dl + e] = acc[r][e];
+  }
+  __syncthreads();
+  for (int i = tid; i < R * DH; i += 256) {
+    const int r = i / DH, d = i - r * DH;
+    if (q0 + r >= na) continue;
+    float o = 0.f;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) o += red[(gg * R + r) * DH + d];
+    float iv = inv[0];
+#pragma unroll
+    for (int rr = 1; rr < R; ++rr) iv = r == rr ? inv[rr] : iv;
+    static_cast<float *>(a.o)[(size_t)(r0 + q0 + r) * D + h * DH + d] = o * iv;
+  }
+}
+
+template <int DH, int R>
+static hipError_t attn_f32_run(const AttnArgs &a, hipStream_t s) {
+  const int chunks = (a.a_max + R - 1) / R;
+  constexpr int G = 256 / (DH / 4);
+  const size_t lds = ((size_t)R * a.n_tokens + G * R * DH) * sizeof(float);
+  launch_kernel(attn_f32_kernel<DH, R>, a.batch * a.n_heads * chunks, 256, lds, s, a, chunks);
+  return hipGetLastError();
 }
 
 template <int DH>
 static hipError_t attn_f32_dispatch(const AttnArgs &a, hipStream_t s) {
-  const size_t lds = (size_t)(DH + a.n_tokens) * sizeof(float);
-  launch_kernel(attn_f32_kernel<DH>, a.a_total * a.n_heads, 64, lds, s, a);
-  return hipGetLastError();
+  // four rows per workgroup once that still leaves two workgroups per compute
+  // unit (and their logits fit 32 KB), else one
+  if (a.n_tokens <= 2048 && (int64_t)a.a_total * a.n_heads >= 8LL * device_cu_count())
+    return attn_f32_run<DH, 4>(a, s);
+  return attn_f32_run<DH, 1>(a, s);
 }
 
 hipError_t launch_attention(DType dt, const AttnArgs &a, hipStream_t s) {
@@ -1033,128 +1291,75 @@ hipError_t launch_attention(DType dt, const AttnArgs &a, hipStream_t s) {
 //
 // scores[b][h][j] = sum over the generating rows i (the first n_gen[b] active
 // rows of image b) of softmax_j(q_i . k_j / sqrt(d_h)) -- the post-softmax
-// attention mass each key receives, one head at a time, with each row's
-// maximum and normaliser taken over all N keys.  One workgroup per
-// (image, head); thread t owns keys t, t+256, ...; generating rows are taken
-// GQ at a time and their logits staged in LDS.  All sums run in a fixed
-// order, so the result is deterministic.
-
-constexpr int SC_THREADS = 256;
-constexpr int SC_MAX_KPT = 16;  // keys per thread: n_tokens <= 4096
-
-__device__ __forceinline__ float block_reduce(float v, bool is_max, float *red) {
-  v = is_max ? wave_max(v) : wave_sum(v);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[w] = v;
-  __syncthreads();
-  float r = red[0];
-#pragma unroll
-  for (int i = 1; i < SC_THREADS / 64; ++i) r = is_max ? fmaxf(r, red[i]) : r + red[i];
-  return r;
-}
-
-// Eight consecutive elements as float (16- or 32-byte aligned source).
-__device__ __forceinline__ void load8(const bf16 *p, float (&out)[8]) {
-  const bf16x8 v = *reinterpret_cast<const bf16x8 *>(p);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) out[e] = (float)v[e];
-}
-__device__ __forceinline__ void load8(const float *p, float (&out)[8]) {
-  const f32x4 a = *reinterpret_cast<const f32x4 *>(p);
-  const f32x4 b = *reinterpret_cast<const f32x4 *>(p + 4);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    out[e] = a[e];
-    out[e + 4] = b[e];
-  }
-}
+// attention mass each key receives, one head at a time, from the row
+// statistics (maximum and 1 / sum over all N keys) that the attention kernel
+// left in a.stats.  One workgroup per (image, head, 64 keys), four lanes per
+// key; the generating rows are added in order, so the result is
+// deterministic.  (With one workgroup per (image, head) finding the
+// statistics itself, the pass took 101 us for 12 heads x 320 keys x 16 rows.)
+constexpr int SC_ROWS = 16;  // generating rows staged in LDS at a time
 
 template <typename T, int DH>
-__global__ __launch_bounds__(SC_THREADS) void attn_scores_kernel(AttnArgs a,
-                                                                 const int32_t *__restrict__ n_gen,
-                                                                 float *__restrict__ scores,
-                                                                 int gq) {
-  extern __shared__ float smem[];
+__global__ __launch_bounds__(256) void attn_scores_kernel(AttnArgs a,
+                                                          const int32_t *__restrict__ n_gen,
+                                                          float *__restrict__ scores, int key_wgs) {
+  constexpr int C4 = DH / 16;
+  __shared__ __attribute__((aligned(16))) float qs[SC_ROWS][DH];
+  __shared__ float st[SC_ROWS][2];
   const int N = a.n_tokens, D = a.d_model;
-  float *qs = smem;                 // [gq][DH]
-  float *ss = smem + gq * DH;       // [gq][N]
-  float *red = ss + gq * N;         // [4]
-  const int b = blockIdx.x / a.n_heads, h = blockIdx.x - b * a.n_heads;
-  const int tid = threadIdx.x;
+  const int bh = blockIdx.x / key_wgs, kw = blockIdx.x - bh * key_wgs;
+  const int b = bh / a.n_heads, h = bh - b * a.n_heads;
+  const int tid = threadIdx.x, li = tid & 3, j = kw * 64 + (tid >> 2);
   const int g = n_gen[b], r0 = a.a_off[b];
-  const size_t head_base = (size_t)(b * a.n_heads + h) * N * DH;
-  const T *kg = static_cast<const T *>(a.k_cache) + head_base;
+  const T *kr = static_cast<const T *>(a.k_cache) + ((size_t)bh * N + min(j, N - 1)) * DH + li * 4;
   const T *qg = static_cast<const T *>(a.q);
-  const float scale = 1.0f / sqrtf((float)DH);
-
-  float acc[SC_MAX_KPT];
+  f32x4 k[C4];
 #pragma unroll
-  for (int i = 0; i < SC_MAX_KPT; ++i) acc[i] = 0.f;
-
-  for (int g0 = 0; g0 < g; g0 += gq) {
-    const int nq = min(gq, g - g0);
-    for (int i = tid; i < nq * DH; i += SC_THREADS) {
-      const int qq = i / DH, d = i - qq * DH;
-      qs[i] = to_f32(qg[(size_t)(r0 + g0 + qq) * D + h * DH + d]);
+  for (int c = 0; c < C4; ++c) {
+    if constexpr (sizeof(T) == 4) {
+      k[c] = *reinterpret_cast<const f32x4 *>(kr + c * 16);
+    } else {
+      const bf16x4 v = *reinterpret_cast<const bf16x4 *>(kr + c * 16);
+      k[c] = f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < SC_MAX_KPT; ++i) {
-      const int j = tid + SC_THREADS * i;
-      if (j >= N) break;
-      float dot[8];
-#pragma unroll
-      for (int qq = 0; qq < 8; ++qq) dot[qq] = 0.f;
-      const T *kr = kg + (size_t)j * DH;
-#pragma unroll 2
-      for (int d0 = 0; d0 < DH; d0 += 8) {
-        float kv[8];
-        load8(kr + d0, kv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int qq = 0; qq < 8; ++qq)
-            if (qq < nq) dot[qq] = fmaf(qs[qq * DH + d0 + e], kv[e], dot[qq]);
-      }
-#pragma unroll
-      for (int qq = 0; qq < 8; ++qq)
-        if (qq < nq) ss[qq * N + j] = dot[qq] * scale;
-    }
-    __syncthreads();
-    for (int qq = 0; qq < nq; ++qq) {
-      float mx = -INFINITY;
-      for (int j = tid; j < N; j += SC_THREADS) mx = fmaxf(mx, ss[qq * N + j]);
-      mx = block_reduce(mx, true, red);
-      float sm = 0.f;
-      for (int j = tid; j < N; j += SC_THREADS) sm += expf(ss[qq * N + j] - mx);
-      sm = block_reduce(sm, false, red);
-      const float inv = 1.0f / sm;
-#pragma unroll
-      for (int i = 0; i < SC_MAX_KPT; ++i) {
-        const int j = tid + SC_THREADS * i;
-        if (j >= N) break;
-        acc[i] += expf(ss[qq * N + j] - mx) * inv;
-      }
-    }
-    __syncthreads();
   }
+  // the statistics' domain: natural for fp32 (expf), log2 for bf16
+  const float scale = (sizeof(T) == 4 ? 1.0f : 1.4426950408889634f) / sqrtf((float)DH);
+  float tot = 0.f;
+  for (int g0 = 0; g0 < g; g0 += SC_ROWS) {
+    const int nr = min(SC_ROWS, g - g0);
+    __syncthreads();
+    for (int i = tid; i < nr * DH; i += 256) {
+      const int r = i / DH, d = i - r * DH;
+      qs[r][d] = to_f32(qg[(size_t)(r0 + g0 + r) * D + h * DH + d]);
+    }
+    if (tid < 2 * nr)
+      st[tid >> 1][tid & 1] = a.stats[((size_t)(r0 + g0 + (tid >> 1)) * a.n_heads + h) * 2 + (tid & 1)];
+    __syncthreads();
+    for (int r = 0; r < nr; ++r) {
+      float d = 0.f;
 #pragma unroll
-  for (int i = 0; i < SC_MAX_KPT; ++i) {
-    const int j = tid + SC_THREADS * i;
-    if (j >= N) break;
-    scores[(size_t)(b * a.n_heads + h) * N + j] = acc[i];
+      for (int c = 0; c < C4; ++c) {
+        const f32x4 q = *reinterpret_cast<const f32x4 *>(&qs[r][c * 16 + li * 4]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d = fmaf(q[e], k[c][e], d);
+      }
+      d += __shfl_xor(d, 1, 64);
+      d += __shfl_xor(d, 2, 64);
+      const float p = sizeof(T) == 4 ? expf(d * scale - st[r][0])
+                                     : __builtin_amdgcn_exp2f(fmaf(d, scale, -st[r][0]));
+      tot += p * st[r][1];
+    }
   }
+  if (li == 0 && j < N) scores[(size_t)bh * N + j] = tot;
 }
 
 template <typename T, int DH>
 static hipError_t scores_dispatch(const AttnArgs &a, const int32_t *n_gen, float *scores,
                                   hipStream_t s) {
-  int gq = 12288 / a.n_tokens;
-  gq = gq < 1 ? 1 : (gq > 8 ? 8 : gq);
-  const size_t lds = (size_t)(gq * DH + gq * a.n_tokens + 4) * sizeof(float);
-  launch_kernel(attn_scores_kernel<T, DH>, a.batch * a.n_heads, SC_THREADS, lds, s,
-                a, n_gen, scores, gq);
+  const int key_wgs = (a.n_tokens + 63) / 64;
+  launch_kernel(attn_scores_kernel<T, DH>, a.batch * a.n_heads * key_wgs, 256, 0, s, a, n_gen,
+                scores, key_wgs);
   return hipGetLastError();
 }
 
@@ -1162,7 +1367,7 @@ hipError_t launch_attn_scores(DType dt, const AttnArgs &a, const int32_t *n_gen,
                               float *scores, hipStream_t s) {
   (void)gen_max;
   if (a.batch == 0) return hipSuccess;
-  if (a.n_tokens > SC_THREADS * SC_MAX_KPT) return hipErrorInvalidValue;
+  if (!a.stats) return hipErrorInvalidValue;
   if (dt == DType::BF16) {
     if (a.head_dim == 64) return scores_dispatch<bf16, 64>(a, n_gen, scores, s);
     if (a.head_dim == 80) return scores_dispatch<bf16, 80>(a, n_gen, scores, s);

@@ -104,7 +104,8 @@ marche_status_t check_model(const marche_model_t *m) {
 
 // One class per kernel symbol.  The attention kernel is instantiated per
 // query-chunk width (1, 2, 4 or 8 wavefronts of 32 queries), chosen from the
-// largest active set of the call; each bf16 GEMM has a 128x256, a 256x256
+// largest active set and the number of (image, head) pairs of the call (fp32
+// attention is timed under the first); each bf16 GEMM has a 128x256, a 256x256
 // (class + 1), a 64x128 (_S), a 128x128 (_M) and a 320x256 (_I) tile
 // instantiation, chosen from its shape (fp32 GEMMs are timed under the
 // first).
@@ -195,10 +196,16 @@ int gemm_class(int base, DType dt, int32_t m, int32_t n, int32_t k) {
   }
 }
 
-int attn_class(DType dt, int a_max, int n_tokens, int head_dim) {
-  if (dt == DType::BF16 && attn_resident(a_max, n_tokens, false)) return K_ATTN_RES;
-  if (a_max > 128 && dt == DType::BF16 && attn_streams(head_dim, n_tokens, false)) return K_ATTN_W8;
-  return a_max <= 32 ? K_ATTN_W1 : (a_max <= 64 ? K_ATTN_W2 : K_ATTN_W4);
+int attn_class(DType dt, const AttnArgs &a) {
+  const bool seg2 = a.k2 != nullptr;
+  if (dt != DType::BF16) return K_ATTN_W1;
+  if (attn_resident(a.a_max, a.n_tokens, seg2)) return K_ATTN_RES;
+  switch (attn_query_blocks(a)) {
+    case 1: return seg2 ? K_ATTN2_W1 : K_ATTN_W1;
+    case 2: return seg2 ? K_ATTN2_W2 : K_ATTN_W2;
+    case 4: return seg2 ? K_ATTN2_W4 : K_ATTN_W4;
+    default: return K_ATTN_W8;
+  }
 }
 
 struct Pending {
@@ -474,10 +481,12 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
     if (fused) {
       aa.n_gen = n_gen;
       aa.scores = scores;
+    } else if (sel) {
+      aa.stats = static_cast<float *>(hid);  // free until fc1; 8 H bytes per row of its >= 512
     }
     // Algorithmic traffic: every cached K/V element of the batch read once,
     // plus the queries read and the outputs written (and the scores).
-    const int acls = attn_class(dt, a_max, N, dh);
+    const int acls = attn_class(dt, aa);
     LAUNCH((fused ? (acls == K_ATTN_RES ? K_ATTN_RES_SC : K_ATTN_SC) : acls) + ko,
            4.0 * M * N * D + (fused ? 2.0 * batch * gen_max * N * D : 0.0),
            es * (2.0 * batch * N * D + 2.0 * M * D) + (fused ? 4.0 * batch * H * N : 0.0),
@@ -605,7 +614,6 @@ marche_status_t marche_attention_segments(const void *q, void *o, int32_t n_quer
     if (reinterpret_cast<uintptr_t>(p) & 15)
       return fail(MARCHE_ERR_INVALID_ARG, "q, o and the segment buffers must be 16-byte aligned");
   hipStream_t stream = static_cast<hipStream_t>(stream_);
-  const int cls_w = n_query <= 32 ? 0 : (n_query <= 64 ? 1 : 2);
   const int32_t nt = n_a + n_c;
   const double flops = 4.0 * batch * n_query * (double)nt * d_model;
   // Algorithmic traffic of attention: q, every K/V row of both segments and o once.
@@ -623,9 +631,7 @@ marche_status_t marche_attention_segments(const void *q, void *o, int32_t n_quer
       aa.v2 = v_c;
       aa.n2 = n_c;
     }
-    const int cls = (n_a > 0 && n_c > 0) ? K_ATTN2_W1 + cls_w
-                                         : attn_class(DType::BF16, n_query, aa.n_tokens, head_dim);
-    LAUNCH(cls, flops, attn_bytes, launch_attention(DType::BF16, aa, stream));
+    LAUNCH(attn_class(DType::BF16, aa), flops, attn_bytes, launch_attention(DType::BF16, aa, stream));
     return MARCHE_OK;
   }
   const size_t need =
@@ -644,7 +650,7 @@ marche_status_t marche_attention_segments(const void *q, void *o, int32_t n_quer
   aa.k_cache = kcat;
   aa.v_cache = vcat;
   aa.n_tokens = nt;
-  LAUNCH(attn_class(DType::BF16, n_query, nt, head_dim), flops, attn_bytes,
+  LAUNCH(attn_class(DType::BF16, aa), flops, attn_bytes,
          launch_attention(DType::BF16, aa, stream));
   return MARCHE_OK;
 }

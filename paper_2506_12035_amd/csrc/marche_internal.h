@@ -158,6 +158,10 @@ struct AttnArgs {
   // attn_fuses_scores() holds (one key segment).
   const int32_t *n_gen = nullptr;
   float *scores = nullptr;
+  // Optional row statistics [a_total][n_heads][2] (maximum logit, 1 / sum) for
+  // launch_attn_scores, written by the kernels that run where
+  // attn_fuses_scores() does not hold (and by every fp32 one).
+  float *stats = nullptr;
 };
 hipError_t launch_attention(DType dt, const AttnArgs &a, hipStream_t s);
 // Whether bf16 attention with these sizes runs the resident-K/V kernel (one
@@ -166,6 +170,9 @@ bool attn_resident(int32_t a_max, int32_t n_tokens, bool two_segments);
 // Whether bf16 attention with these sizes runs the register-staged streaming
 // kernel (head width 64, one key segment of whole tiles).
 bool attn_streams(int32_t head_dim, int32_t n_tokens, bool two_segments);
+// Wavefronts of 32 queries per workgroup of the streaming kernel that these
+// bf16 arguments run (where the resident one does not).
+int attn_query_blocks(const AttnArgs &a);
 // Whether bf16 attention with these sizes can write the score pass itself:
 // the resident kernel (every key of a head in LDS), or the streaming kernel
 // when the generating rows fit its first query chunk.
