@@ -108,6 +108,7 @@ def counter_class(name: str):
     tile = ("t256" if ("gemm_bf16_big_kernel" in name or "gemm_bf16_big8_kernel" in name) else
             "t320" if "gemm_bf16_t320_kernel" in name else
             "t64x128" if "gemm_bf16_small_kernel" in name else
+            "rows" if "gemm_bf16_rows_kernel" in name else
             "t128" if "gemm_bf16_mid_kernel" in name else "t128x256")
     if "gemm_bf16" in name:
         for key, cls in (("EpiResidILi1E", "fc2"), ("EpiResid<1>", "fc2"), ("EpiResidILi0E", "o"),

@@ -1003,24 +1003,24 @@ struct AttnShape {
 
 // Launch shape of the streaming kernels.  QB wavefronts of 32 queries per
 // workgroup: as many as the largest active set needs, up to four (eight in
-// attn_reg_kernel).  Two key groups where QB <= 2 and the grid is no more than
-// one workgroup per compute unit: a workgroup's time is then its serial walk
-// over the key tiles (16 images x 16 heads of width 80, 45 queries x 1548
-// keys: 33.4 us with one group, 26.4 with two; with 512 workgroups or more
-// two groups only shrink the number resident: 19.1 against 22.2 us at 1024).
-// Longer query lists on a nearly empty chip take two wavefronts per workgroup
-// for the same reason (16 (image, head) pairs, 150 queries x 1088 keys: 21.6
-// against 14.4 us).  The layer step asks for half the workgroups before it
-// splits, so that an image range and the batch it is part of run the same
-// kernel (and sum in the same order) down to about 8 images.
+// attn_reg_kernel: one pass over K/V per 256 queries).  The stand-alone
+// segment attention takes two key groups of at most two query blocks where
+// its grid is then no more than one workgroup per compute unit: a workgroup's
+// time is its serial walk over the key tiles (16 images x 16 heads of width
+// 80, 45 queries x 1548 keys: 33.4 us with one group, 26.4 with two; at 512
+// workgroups or more two groups only shrink the number resident: 19.1 against
+// 22.2 us at 1024).  A layer step never does: its images' results must not
+// depend on how many images share the call, and two groups sum in another
+// order.
 static AttnShape attn_shape(const AttnArgs &a) {
-  const int64_t bh = (int64_t)a.batch * a.n_heads;
   const int q = a.a_max <= 32 ? 1 : 2;
-  const int64_t few = a.a_off ? device_cu_count() / 2 : device_cu_count();
-  const bool split = bh * ((a.a_max + 32 * q - 1) / (32 * q)) <= few;
-  if (attn_streams(a.head_dim, a.n_tokens, a.k2 != nullptr) && !a.stats && (a.scores || !split))
-    return {reg_qb(a.a_max), 1, true};  // eight: one pass over K/V per 256 queries
-  return {split ? q : std::min(reg_qb(a.a_max), 4), split ? 2 : 1, false};
+  const bool split = !a.a_off && (int64_t)a.batch * a.n_heads *
+                                         ((a.a_max + 32 * q - 1) / (32 * q)) <=
+                                     device_cu_count();
+  if (split) return {q, 2, false};
+  if (attn_streams(a.head_dim, a.n_tokens, a.k2 != nullptr) && !a.stats)
+    return {reg_qb(a.a_max), 1, true};
+  return {std::min(reg_qb(a.a_max), 4), 1, false};
 }
 
 int attn_query_blocks(const AttnArgs &a) { return attn_shape(a).qb; }

@@ -19,6 +19,8 @@
 //
 // fp32 path: fp32 matrix instructions, a 64x64 tile or, for few rows, a
 // workgroup per 16 columns whose wavefronts split K.
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace marche {
@@ -52,12 +54,24 @@ __device__ __forceinline__ f32x4 load_bias4(const float *bias, int col0) {
 // Epilogue interface: row(r) per-row addressing data (may load the row map);
 // col(c0) per-column addressing data for the four columns c0..c0+3, computed
 // once per lane where the columns of a lane are fixed; bias4(c0); prior(row,
-// col) the value the result is added to (residual epilogues); store(row, r,
-// col, v) with v = acc + bias + prior.
+// col) what the result is combined with (residual epilogues: the value it is
+// added to); combine(acc + bias, prior) the value stored; store(row, r, col,
+// v).  Epilogues without a prior (kPrior = false) store acc + bias.
+
+// Epilogues that combine with nothing, or by adding.
+struct PlainPrior {
+  static constexpr bool kPrior = false;
+  using Prior = f32x4;
+  __device__ __forceinline__ f32x4 combine(f32x4 v, const Prior &) const { return v; }
+};
+struct AddPrior {
+  static constexpr bool kPrior = true;
+  using Prior = f32x4;
+  __device__ __forceinline__ f32x4 combine(f32x4 v, const Prior &p) const { return v + p; }
+};
 
 template <typename T>
-struct EpiQkv {
-  static constexpr bool kPrior = false;
+struct EpiQkv : PlainPrior {
   T *q;
   T *kc;
   T *vc;
@@ -93,7 +107,6 @@ struct EpiQkv {
     return Col{which == 1 ? kc : vc, (uint32_t)(h * n_tokens * head_dim + d), false};
   }
   __device__ __forceinline__ f32x4 bias4(int c0) const { return load_bias4(bias, c0); }
-  __device__ __forceinline__ f32x4 prior(const Row &, const Col &) const { return f32x4{}; }
   __device__ __forceinline__ void store(const Row &m, int, const Col &c, f32x4 v) const {
     store4(c.base + (c.is_q ? m.q_off : m.kv_off) + c.off, v);
   }
@@ -102,8 +115,7 @@ struct EpiQkv {
 // TAG only distinguishes the output projection (0) from fc2 (1) as kernel
 // symbols, so per-kernel profiles can tell them apart.
 template <int TAG>
-struct EpiResid {
-  static constexpr bool kPrior = true;
+struct EpiResid : AddPrior {
   float *x;
   const float *bias;
   const RowMap *map;
@@ -122,8 +134,7 @@ struct EpiResid {
 };
 
 template <typename T>
-struct EpiGelu {
-  static constexpr bool kPrior = false;
+struct EpiGelu : PlainPrior {
   T *h;
   const float *bias;
   int n;
@@ -132,7 +143,6 @@ struct EpiGelu {
   __device__ __forceinline__ Row row(int r) const { return r; }
   __device__ __forceinline__ Col col(int c0) const { return c0; }
   __device__ __forceinline__ f32x4 bias4(int c0) const { return load_bias4(bias, c0); }
-  __device__ __forceinline__ f32x4 prior(const Row &, const Col &) const { return f32x4{}; }
   __device__ __forceinline__ void store(const Row &, int r, const Col &c, f32x4 v) const {
     f32x4 g = {gelu_erf(v[0]), gelu_erf(v[1]), gelu_erf(v[2]), gelu_erf(v[3])};
     store4(h + (uint32_t)(r * n + c), g);
@@ -142,8 +152,7 @@ struct EpiGelu {
 // Plain epilogue of the sampler's GEMMs: out[r][c] = act(C + bias) stored
 // row-major as T (ld = n), act the identity or SiLU.
 template <typename T, bool SILU>
-struct EpiPlain {
-  static constexpr bool kPrior = false;
+struct EpiPlain : PlainPrior {
   T *out;
   const float *bias;
   int n;
@@ -152,10 +161,44 @@ struct EpiPlain {
   __device__ __forceinline__ Row row(int r) const { return r * n; }
   __device__ __forceinline__ Col col(int c0) const { return c0; }
   __device__ __forceinline__ f32x4 bias4(int c0) const { return load_bias4(bias, c0); }
-  __device__ __forceinline__ f32x4 prior(const Row &, const Col &) const { return f32x4{}; }
   __device__ __forceinline__ void store(const Row &ro, int, const Col &c, f32x4 v) const {
     if constexpr (SILU) v = f32x4{silu(v[0]), silu(v[1]), silu(v[2]), silu(v[3])};
     store4(out + (uint32_t)(ro + c), v);
+  }
+};
+
+// Second product of a sampler block: the gated residual h[r][c] += gate[r][c]
+// (C + bias), h float32 (ld = n), the gate a slice of the modulation buffer
+// (ld = mod_ld).
+template <typename T>
+struct EpiGate {
+  static constexpr bool kPrior = true;
+  struct Prior {
+    f32x4 h;
+    T g __attribute__((ext_vector_type(4)));
+  };
+  float *h;
+  const float *bias;
+  const T *gate;
+  int n, mod_ld;
+  using Row = int2;  // element offsets of the row in h and in the modulations (< 2^31)
+  using Col = int32_t;
+  __device__ __forceinline__ Row row(int r) const { return Row{r * n, r * mod_ld}; }
+  __device__ __forceinline__ Col col(int c0) const { return c0; }
+  __device__ __forceinline__ f32x4 bias4(int c0) const { return load_bias4(bias, c0); }
+  __device__ __forceinline__ Prior prior(const Row &ro, const Col &c) const {
+    Prior p;
+    p.h = *reinterpret_cast<const f32x4 *>(h + (uint32_t)(ro.x + c));
+    p.g = *reinterpret_cast<const decltype(p.g) *>(gate + (uint32_t)(ro.y + c));
+    return p;
+  }
+  __device__ __forceinline__ f32x4 combine(f32x4 v, const Prior &p) const {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = fmaf((float)p.g[e], v[e], p.h[e]);
+    return v;
+  }
+  __device__ __forceinline__ void store(const Row &ro, int, const Col &c, f32x4 v) const {
+    *reinterpret_cast<f32x4 *>(h + (uint32_t)(ro.x + c)) = v;
   }
 };
 
@@ -164,8 +207,7 @@ struct EpiPlain {
 // image token known[b][i - n_buf]; its result goes to that token's sequence
 // position j in the float32 decoder input x [batch][n_tokens][n], plus the
 // decoder's positional embedding pe[j].
-struct EpiEmbed {
-  static constexpr bool kPrior = true;
+struct EpiEmbed : AddPrior {
   float *x;
   const float *bias;
   const float *pe;
@@ -194,9 +236,9 @@ struct EpiEmbed {
 // Empty uses that pin loaded values to this point: without them the compiler
 // sinks the loads into the row-guarded store blocks, one wait per block.
 __device__ __forceinline__ void keep(const f32x4 &v) { asm volatile("" ::"v"(v)); }
-__device__ __forceinline__ void keep(int32_t v) { asm volatile("" ::"v"(v)); }
-__device__ __forceinline__ void keep(const RowMap &m) {
-  asm volatile("" ::"v"(m.x_row), "v"(m.b), "v"(m.tok));
+template <class P>
+__device__ __forceinline__ auto keep(const P &p) -> decltype((void)p.h, (void)p.g) {
+  asm volatile("" ::"v"(p.h), "v"(p.g));
 }
 
 // ------------------------------------------------------------------ bf16 MFMA
@@ -332,15 +374,13 @@ __device__ __forceinline__ void write_back_staged(const f32x16 (&acc)[TN][TM], c
   constexpr int NB = KP / PB;      // batches per 32-row block
   const int c4 = (lane % LPR) * 4, rsub = lane / LPR, half = lane >> 5;
   const typename Epi::Col col = epi.col(col0 + c4);
-  f32x4 pr[2][PB];  // residual priors; zero for epilogues without one
-#pragma unroll
-  for (int k = 0; k < PB; ++k) pr[0][k] = pr[1][k] = f32x4{};
+  typename Epi::Prior pr[2][PB];  // unused by epilogues without a prior
   // batch u: block u / NB, rows rsub + RPP k for k in [(u % NB) PB, + PB)
-  auto load_priors = [&](int u, f32x4 (&dst)[PB]) {
+  auto load_priors = [&](int u, typename Epi::Prior (&dst)[PB]) {
     const int i = u / NB, k0 = (u % NB) * PB;
 #pragma unroll
     for (int k = 0; k < PB; ++k)
-      dst[k] = Epi::kPrior ? epi.prior(rows[i * 32 + rsub + RPP * (k0 + k)], col) : f32x4{};
+      if constexpr (Epi::kPrior) dst[k] = epi.prior(rows[i * 32 + rsub + RPP * (k0 + k)], col);
   };
   if constexpr (Epi::kPrior) load_priors(0, pr[0]);
 #pragma unroll
@@ -368,10 +408,7 @@ __device__ __forceinline__ void write_back_staged(const f32x16 (&acc)[TN][TM], c
 #pragma unroll
         for (int k = 0; k < PB; ++k) keep(pr[u & 1][k]);
       }
-      auto value = [&](int k) -> f32x4 {
-        if constexpr (Epi::kPrior) return v[k] + b + pr[u & 1][k];
-        else return v[k] + b;
-      };
+      auto value = [&](int k) -> f32x4 { return epi.combine(v[k] + b, pr[u & 1][k]); };
       if (full) {
 #pragma unroll
         for (int k = 0; k < PB; ++k) {
@@ -1306,20 +1343,20 @@ __device__ __forceinline__ void mfma(f32x16 (&acc)[2][1], const Frag &f) {
 
 }  // namespace small
 
+// One tile of an M x N x K product; `smem` holds three stages, `rows` kBM row records.
 template <class Epi>
-__global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16 *A, const bf16 *W, int M,
-                                                              int N, int K, Epi epi) {
+__device__ __forceinline__ void small_tile(const bf16 *A, const bf16 *W, int M, int N, int K,
+                                           const Epi &epi, int id, unsigned char *smem,
+                                           typename Epi::Row *rows_lds) {
   using namespace small;
   using pair::barrier_vm;
   using big::pin;
   using Row = typename Epi::Row;
   constexpr int kStr = 2 * 32 + 4;  // staged write-back row (floats)
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * kStage];
-  __shared__ __attribute__((aligned(16))) Row rows_lds[kBM];
   static_assert(4 * 32 * kStr * 4 <= 3 * kStage, "staged write-back fits the stages");
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = N / kBN;
   int tm, tn;
-  tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
+  tile_coords(id, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * kBM, n0 = tn * kBN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1381,6 +1418,131 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16 *A, con
                              rows_lds + wm * 32, bias);
 }
 
+// With side products (see HeadSides) the tiles of the main product come first.
+template <class Epi, bool SIDES>
+__global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16 *A, const bf16 *W, int M,
+                                                              int N, int K, Epi epi,
+                                                              HeadSides sides) {
+  using namespace small;
+  using Plain = EpiPlain<bf16, false>;
+  constexpr size_t kRec = sizeof(typename Epi::Row) > sizeof(Plain::Row) ? sizeof(typename Epi::Row)
+                                                                          : sizeof(Plain::Row);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * kStage];
+  __shared__ __attribute__((aligned(16))) unsigned char rows[kBM * kRec];
+  int id = xcd_remap(blockIdx.x, gridDim.x);
+  if constexpr (SIDES) {
+    const int tiles_m = (M + kBM - 1) / kBM;
+    const int main_tiles = tiles_m * (N / kBN);
+    if (id >= main_tiles) {
+      id -= main_tiles;
+      const int first = tiles_m * (sides.s[0].n / kBN);
+      const HeadSide j = id < first ? sides.s[0] : sides.s[1];
+      const Plain pe{{}, static_cast<bf16 *>(j.out), j.bias, sides.ld};
+      small_tile(static_cast<const bf16 *>(j.a), static_cast<const bf16 *>(j.w), M, j.n, K, pe,
+                 id < first ? id : id - first, smem, reinterpret_cast<Plain::Row *>(rows));
+      return;
+    }
+  }
+  small_tile(A, W, M, N, K, epi, id, smem, reinterpret_cast<typename Epi::Row *>(rows));
+}
+
+// ------------------------------------------------------------------ few rows
+//
+// The sampler's products on up to 64 rows (a few images' generating tokens):
+// such a product is its weights streamed once, and its time the
+// latency of one workgroup's walk over K (the 64x128 tile gave 5 rows x 1280
+// x 1280 ten workgroups and 9.4 us).  A workgroup takes 16 columns; its eight
+// wavefronts split K, load both operands straight into the MFMA registers
+// (64-byte row segments, all of a wavefront's loads independent) and add
+// their partial tiles through LDS in wavefront order.
+namespace rows16 {
+
+constexpr int kWaves = 8;
+constexpr int kBN = 16;
+
+// The 16 columns from n0 of the whole M <= MB * 16 rows.
+template <class Epi, int MB>
+__device__ __forceinline__ void tile(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M,
+                                     int K, const Epi epi, int n0, f32x4 (*part)[MB][64]) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int steps = K / 32;  // of 32 k; wavefront w takes [w S / 8, (w + 1) S / 8)
+  const int s0 = wave * steps / kWaves, s1 = (wave + 1) * steps / kWaves;
+  const int kl = (lane >> 4) * 8;
+  const bf16 *wp = W + (size_t)(n0 + (lane & 15)) * K + kl;
+  const bf16 *xp[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) xp[i] = A + (size_t)min(i * 16 + (lane & 15), M - 1) * K + kl;
+  f32x4 acc[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) acc[i] = f32x4{};
+  constexpr int U = 5;  // steps whose loads are in flight together
+  int s = s0;
+  for (; s + U <= s1; s += U) {
+    bf16x8 w[U], x[U][MB];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      w[u] = *reinterpret_cast<const bf16x8 *>(wp + (s + u) * 32);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        x[u][i] = *reinterpret_cast<const bf16x8 *>(xp[i] + (s + u) * 32);
+    }
+    big::pin();  // every load before the first MFMA's wait
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u], x[u][i], acc[i], 0, 0, 0);
+  }
+  for (; s < s1; ++s) {
+    const bf16x8 w = *reinterpret_cast<const bf16x8 *>(wp + s * 32);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          w, *reinterpret_cast<const bf16x8 *>(xp[i] + s * 32), acc[i], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i) part[wave][i][lane] = acc[i];
+  __syncthreads();
+  if (wave >= MB) return;
+  const int row = wave * 16 + (lane & 15), c0 = n0 + (lane >> 4) * 4;
+  const typename Epi::Col c = epi.col(c0);  // uniform parts: before the row guard
+  if (row >= M) return;
+  const typename Epi::Row r = epi.row(row);
+  f32x4 v = epi.bias4(c0);
+  typename Epi::Prior pr;
+  if constexpr (Epi::kPrior) pr = epi.prior(r, c);
+  f32x4 t = part[0][wave][lane];
+#pragma unroll
+  for (int g = 1; g < kWaves; ++g) t += part[g][wave][lane];
+  epi.store(r, row, c, epi.combine(t + v, pr));
+}
+
+}  // namespace rows16
+
+template <class Epi, int MB, bool SIDES>
+__global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, const bf16 *W, int M,
+                                                             int N, int K, Epi epi,
+                                                             HeadSides sides) {
+  using namespace rows16;
+  __shared__ f32x4 part[kWaves][MB][64];
+  int id = blockIdx.x;
+  if constexpr (SIDES) {
+    const int main_tiles = N / kBN;
+    if (id >= main_tiles) {
+      id -= main_tiles;
+      const int first = sides.s[0].n / kBN;
+      const HeadSide j = id < first ? sides.s[0] : sides.s[1];
+      const EpiPlain<bf16, false> pe{{}, static_cast<bf16 *>(j.out), j.bias, sides.ld};
+      tile<EpiPlain<bf16, false>, MB>(static_cast<const bf16 *>(j.a),
+                                      static_cast<const bf16 *>(j.w), M, K, pe,
+                                      (id < first ? id : id - first) * kBN, part);
+      return;
+    }
+  }
+  tile<Epi, MB>(A, W, M, K, epi, id * kBN, part);
+}
+
 // Tile choice.  A large tile (one workgroup per CU) when 256x256 tiles fill
 // at least 45% of their last wave over the compute units: a partly filled
 // last wave runs at a higher clock under the chip's power limit, and beside
@@ -1427,6 +1589,21 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
   return GEMM_TILE_128x256;
 }
 
+bool gemm_few_rows(DType dt, int32_t m) { return dt == DType::BF16 && m <= 64; }
+
+// The few-row kernel with the side products' tiles after the main ones.
+template <class Epi, bool SIDES>
+static void run_rows(const bf16 *A, const bf16 *W, int m, int n, int k, const Epi &epi,
+                     const HeadSides &sides, hipStream_t s) {
+  const int grid = (n + (SIDES ? sides.s[0].n + sides.s[1].n : 0)) / rows16::kBN;
+  if (m <= 16)
+    launch_kernel(gemm_bf16_rows_kernel<Epi, 1, SIDES>, grid, 512, 0, s, A, W, m, n, k, epi, sides);
+  else if (m <= 32)
+    launch_kernel(gemm_bf16_rows_kernel<Epi, 2, SIDES>, grid, 512, 0, s, A, W, m, n, k, epi, sides);
+  else
+    launch_kernel(gemm_bf16_rows_kernel<Epi, 4, SIDES>, grid, 512, 0, s, A, W, m, n, k, epi, sides);
+}
+
 // N a multiple of 256 and K of 64 (the host limits d_model and d_mlp to
 // multiples of 256).
 template <class Epi>
@@ -1452,9 +1629,9 @@ static hipError_t run_bf16(const void *a, const void *w, int m, int n, int k, co
                     0, s, A, W, m, n, k, epi);
       break;
     case GEMM_TILE_64x128:
-      launch_kernel(gemm_bf16_small_kernel<Epi>,
+      launch_kernel(gemm_bf16_small_kernel<Epi, false>,
                     ((m + small::kBM - 1) / small::kBM) * (n / small::kBN), 256, 0, s, A, W, m, n,
-                    k, epi);
+                    k, epi, HeadSides{});
       break;
     case GEMM_TILE_128:
       launch_kernel(gemm_bf16_mid_kernel<Epi, 4>,
@@ -1541,6 +1718,7 @@ __global__ __launch_bounds__(1024) void gemm_f32_skinny_kernel(const float *__re
       for (int i = 0; i < MB; ++i)
         x[u][i] = *reinterpret_cast<const f32x4 *>(xp[i] + (s + u) * 16);
     }
+    big::pin();  // every load before the first MFMA's wait
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -1565,8 +1743,8 @@ __global__ __launch_bounds__(1024) void gemm_f32_skinny_kernel(const float *__re
   const typename Epi::Col c = epi.col(c0);
   if (row >= M) return;
   const typename Epi::Row r = epi.row(row);
-  if constexpr (Epi::kPrior) v = v + epi.bias4(c0) + epi.prior(r, c);
-  else v = v + epi.bias4(c0);
+  v += epi.bias4(c0);
+  if constexpr (Epi::kPrior) v = epi.combine(v, epi.prior(r, c));
   epi.store(r, row, c, v);
 }
 
@@ -1660,12 +1838,12 @@ static hipError_t run_f32(const void *a, const void *w, int m, int n, int k, con
 hipError_t launch_gemm_qkv(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                            int32_t n, int32_t k, const RowMap *map, QkvOut o, hipStream_t s) {
   if (dt == DType::F32) {
-    EpiQkv<float> e{static_cast<float *>(o.q), static_cast<float *>(o.k_cache),
+    EpiQkv<float> e{{}, static_cast<float *>(o.q), static_cast<float *>(o.k_cache),
                     static_cast<float *>(o.v_cache), bias, map, o.d_model, o.head_dim,
                     o.n_heads, o.n_tokens};
     return run_f32(a, w, m, n, k, e, s);
   }
-  EpiQkv<bf16> e{static_cast<bf16 *>(o.q), static_cast<bf16 *>(o.k_cache),
+  EpiQkv<bf16> e{{}, static_cast<bf16 *>(o.q), static_cast<bf16 *>(o.k_cache),
                  static_cast<bf16 *>(o.v_cache), bias, map, o.d_model, o.head_dim, o.n_heads,
                  o.n_tokens};
   return run_bf16(a, w, m, n, k, e, s);
@@ -1675,20 +1853,20 @@ hipError_t launch_gemm_resid(DType dt, const void *a, const void *w, const float
                              int32_t n, int32_t k, const RowMap *map, float *x, int32_t tag,
                              hipStream_t s) {
   if (tag == 0) {
-    EpiResid<0> e{x, bias, map, n};
+    EpiResid<0> e{{}, x, bias, map, n};
     return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s);
   }
-  EpiResid<1> e{x, bias, map, n};
+  EpiResid<1> e{{}, x, bias, map, n};
   return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s);
 }
 
 hipError_t launch_gemm_gelu(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                             int32_t n, int32_t k, void *h, hipStream_t s) {
   if (dt == DType::F32) {
-    EpiGelu<float> e{static_cast<float *>(h), bias, n};
+    EpiGelu<float> e{{}, static_cast<float *>(h), bias, n};
     return run_f32(a, w, m, n, k, e, s);
   }
-  EpiGelu<bf16> e{static_cast<bf16 *>(h), bias, n};
+  EpiGelu<bf16> e{{}, static_cast<bf16 *>(h), bias, n};
   return run_bf16(a, w, m, n, k, e, s);
 }
 
@@ -1696,27 +1874,84 @@ hipError_t launch_gemm_gelu(DType dt, const void *a, const void *w, const float 
 
 namespace marche {
 
+// A bf16 sampler product without side products.
+template <class Epi>
+static hipError_t run_plain(const void *a, const void *w, int m, int n, int k, const Epi &epi,
+                            hipStream_t s) {
+  if (m == 0 || !gemm_few_rows(DType::BF16, m)) return run_bf16(a, w, m, n, k, epi, s);
+  if (n % 256 != 0 || k % 64 != 0) return hipErrorInvalidValue;
+  run_rows<Epi, false>(static_cast<const bf16 *>(a), static_cast<const bf16 *>(w), m, n, k, epi,
+                       HeadSides{}, s);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_plain(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                              int32_t n, int32_t k, void *out, DType out_dt, bool silu_act,
-                             hipStream_t s) {
+                             int32_t ld, hipStream_t s) {
   if (dt == DType::F32) {
     if (out_dt != DType::F32) return hipErrorInvalidValue;
-    if (silu_act) return run_f32(a, w, m, n, k, EpiPlain<float, true>{static_cast<float *>(out), bias, n}, s);
-    return run_f32(a, w, m, n, k, EpiPlain<float, false>{static_cast<float *>(out), bias, n}, s);
+    if (silu_act) return run_f32(a, w, m, n, k, EpiPlain<float, true>{{}, static_cast<float *>(out), bias, ld}, s);
+    return run_f32(a, w, m, n, k, EpiPlain<float, false>{{}, static_cast<float *>(out), bias, ld}, s);
   }
   if (out_dt == DType::F32) {
     if (silu_act) return hipErrorInvalidValue;
-    return run_bf16(a, w, m, n, k, EpiPlain<float, false>{static_cast<float *>(out), bias, n}, s);
+    return run_plain(a, w, m, n, k, EpiPlain<float, false>{{}, static_cast<float *>(out), bias, ld}, s);
   }
-  if (silu_act) return run_bf16(a, w, m, n, k, EpiPlain<bf16, true>{static_cast<bf16 *>(out), bias, n}, s);
-  return run_bf16(a, w, m, n, k, EpiPlain<bf16, false>{static_cast<bf16 *>(out), bias, n}, s);
+  if (silu_act) return run_plain(a, w, m, n, k, EpiPlain<bf16, true>{{}, static_cast<bf16 *>(out), bias, ld}, s);
+  return run_plain(a, w, m, n, k, EpiPlain<bf16, false>{{}, static_cast<bf16 *>(out), bias, ld}, s);
+}
+
+int head_side_tiles(DType dt, int32_t m, int32_t width) {
+  if (dt != DType::BF16 || m <= 0) return 0;
+  // few rows: the launches stream weights, so a side product of any size only
+  // adds its own bytes
+  if (gemm_few_rows(dt, m)) return 1 << 20;
+  const int tiles_m = (m + small::kBM - 1) / small::kBM;
+  return std::max(0, device_cu_count() / tiles_m - width / small::kBN);
+}
+
+template <class Epi>
+static hipError_t run_head(const void *a, const void *w, int m, int width, const Epi &epi,
+                           const HeadSides &sides, hipStream_t s) {
+  const bf16 *A = static_cast<const bf16 *>(a), *W = static_cast<const bf16 *>(w);
+  const int n_side = sides.s[0].n + sides.s[1].n;
+  if (n_side == 0) return run_plain(a, w, m, width, width, epi, s);
+  if (width % 256 != 0 || sides.s[0].n % small::kBN != 0 || sides.s[1].n % small::kBN != 0)
+    return hipErrorInvalidValue;
+  if (gemm_few_rows(DType::BF16, m))
+    run_rows<Epi, true>(A, W, m, width, width, epi, sides, s);
+  else
+    launch_kernel(gemm_bf16_small_kernel<Epi, true>,
+                  ((m + small::kBM - 1) / small::kBM) * ((width + n_side) / small::kBN), 256, 0, s,
+                  A, W, m, width, width, epi, sides);
+  return hipGetLastError();
+}
+
+hipError_t launch_head_gemm_silu(DType dt, const void *a, const void *w, const float *bias,
+                                 int32_t m, int32_t width, void *y, const HeadSides &sides,
+                                 hipStream_t s) {
+  if (dt == DType::F32)
+    return run_f32(a, w, m, width, width,
+                   EpiPlain<float, true>{{}, static_cast<float *>(y), bias, width}, s);
+  return run_head(a, w, m, width, EpiPlain<bf16, true>{{}, static_cast<bf16 *>(y), bias, width},
+                  sides, s);
+}
+
+hipError_t launch_head_gemm_gate(DType dt, const void *a, const void *w, const float *bias,
+                                 int32_t m, int32_t width, float *h, const void *gate,
+                                 int32_t mod_ld, const HeadSides &sides, hipStream_t s) {
+  if (dt == DType::F32)
+    return run_f32(a, w, m, width, width,
+                   EpiGate<float>{h, bias, static_cast<const float *>(gate), width, mod_ld}, s);
+  return run_head(a, w, m, width,
+                  EpiGate<bf16>{h, bias, static_cast<const bf16 *>(gate), width, mod_ld}, sides, s);
 }
 
 hipError_t launch_gemm_embed(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                              int32_t n, int32_t k, float *x, const float *pe, const int32_t *known,
                              int32_t n_enc, int32_t n_buf, int32_t n_known, int32_t n_tokens,
                              hipStream_t s) {
-  EpiEmbed e{x, bias, pe, known, n, n_enc, n_buf, n_known, n_tokens};
+  EpiEmbed e{{}, x, bias, pe, known, n, n_enc, n_buf, n_known, n_tokens};
   return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s);
 }
 

@@ -1,9 +1,11 @@
 // The rest of a MAR step around the decoder: the encoder's input rows (Eq. 1),
 // the decoder input's masked rows (Eq. 2), LayerNorm of gathered rows, and the
 // kernels of the sampler of Eq. 3 between its GEMMs (time embedding table,
-// condition SiLU, modulated LayerNorms, output projection + DDPM step).
+// condition SiLU, modulated LayerNorms, output projection + DDPM step + input
+// projection).
 //
-// Row kernels run one wavefront per row, four rows per 256-thread workgroup;
+// Except for the last of these, row kernels run one wavefront per row, four
+// rows per 256-thread workgroup;
 // a row of width NV * 256 is NV float4 chunks per lane.  LayerNorm statistics
 // are float32: the mean, then the population variance of the centred values,
 // eps inside the square root.
@@ -214,82 +216,24 @@ __global__ __launch_bounds__(256) void transpose_f32_kernel(float *__restrict__ 
   w_t[(size_t)c * rows + d] = w[idx];
 }
 
-// Input projection of the noisy token and the first block's modulated norm:
-// h[r] = w_in x[r] + b_in;  a[r] = LN(h[r]) * (1 + scale) + shift with
-// (shift, scale) = mod[r][0 .. 2W) (block 0).  The projection is given
-// transposed, w_in_t [C][W].
-template <typename T, int NV, int CM>
-__global__ __launch_bounds__(256) void head_in_mod_kernel(T *__restrict__ a_out,
-                                                          float *__restrict__ h,
-                                                          const float *__restrict__ x,
-                                                          const float *__restrict__ w_in_t,
-                                                          const float *__restrict__ b_in,
-                                                          const T *__restrict__ mod, int mod_ld,
-                                                          int rows, int C, float eps) {
-  constexpr int W = NV * 256;
-  __shared__ float tv[4][CM];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int r = blockIdx.x * 4 + w;
-  if (r >= rows) return;
-  if (lane < CM) tv[w][lane] = lane < C ? x[(size_t)r * C + lane] : 0.f;
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): own LDS writes done
-  __builtin_amdgcn_wave_barrier();
-  float4 v[NV];
-  const float4 *bi = reinterpret_cast<const float4 *>(b_in);
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int c4 = lane + 64 * k;
-    float4 acc = bi[c4];
-#pragma unroll 16
-    for (int c = 0; c < CM; ++c) {  // channels past C have tv = 0 and repeat row C - 1
-      const float4 wv = reinterpret_cast<const float4 *>(w_in_t + (size_t)min(c, C - 1) * W)[c4];
-      const float xc = tv[w][c];
-      acc.x = fmaf(wv.x, xc, acc.x);
-      acc.y = fmaf(wv.y, xc, acc.y);
-      acc.z = fmaf(wv.z, xc, acc.z);
-      acc.w = fmaf(wv.w, xc, acc.w);
-    }
-    v[k] = acc;
-    reinterpret_cast<float4 *>(h + (size_t)r * W)[lane + 64 * k] = v[k];
-  }
-  const float rstd = centre_rstd<NV>(v, eps);
-  const T *mr = mod + (size_t)r * mod_ld;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int c = 4 * (lane + 64 * k);
-    const float4 sh = load_row4(mr + c), sc = load_row4(mr + W + c);
-    store_row4(a_out + (size_t)r * W + c, v[k].x * rstd * (1.f + sc.x) + sh.x,
-               v[k].y * rstd * (1.f + sc.y) + sh.y, v[k].z * rstd * (1.f + sc.z) + sh.z,
-               v[k].w * rstd * (1.f + sc.w) + sh.w);
-  }
-}
-
-// Gated residual of block k and the next modulated norm:
-// h[r] += gate * t[r];  a[r] = LN(h[r]) * (1 + scale) + shift, where gate,
-// shift and scale are W-wide slices of mod[r] at the given offsets.
+// a[r] = LN(h[r]) * (1 + scale) + shift, shift and scale W-wide slices of
+// mod[r] at the given offsets: the modulated norm between two blocks (the
+// gated residual is the epilogue of the block's second product).
 template <typename T, int NV>
-__global__ __launch_bounds__(256) void head_gate_mod_kernel(T *__restrict__ a_out,
-                                                            float *__restrict__ h,
-                                                            const float *__restrict__ t,
-                                                            const T *__restrict__ mod, int mod_ld,
-                                                            int gate_off, int shift_off,
-                                                            int scale_off, int rows, float eps) {
+__global__ __launch_bounds__(256) void head_mod_kernel(T *__restrict__ a_out,
+                                                       const float *__restrict__ h,
+                                                       const T *__restrict__ mod, int mod_ld,
+                                                       int shift_off, int scale_off, int rows,
+                                                       float eps) {
   constexpr int W = NV * 256;
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
   const T *mr = mod + (size_t)r * mod_ld;
-  float4 *hr = reinterpret_cast<float4 *>(h + (size_t)r * W);
-  const float4 *tr = reinterpret_cast<const float4 *>(t + (size_t)r * W);
+  const float4 *hr = reinterpret_cast<const float4 *>(h + (size_t)r * W);
   float4 v[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int c4 = lane + 64 * k;
-    const float4 hv = hr[c4], tv = tr[c4], g = load_row4(mr + gate_off + 4 * c4);
-    v[k] = make_float4(fmaf(g.x, tv.x, hv.x), fmaf(g.y, tv.y, hv.y), fmaf(g.z, tv.z, hv.z),
-                       fmaf(g.w, tv.w, hv.w));
-    hr[c4] = v[k];
-  }
+  for (int k = 0; k < NV; ++k) v[k] = hr[lane + 64 * k];
   const float rstd = centre_rstd<NV>(v, eps);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -301,50 +245,142 @@ __global__ __launch_bounds__(256) void head_gate_mod_kernel(T *__restrict__ a_ou
   }
 }
 
-// Output projection eps[r] = w_out a[r] + b_out (C values) and one DDPM step:
-// x0 = sra x - srm1 eps;  x_next = c1 x0 + c2 x + sigma * noise, with x the
-// current token value (x_cur) and sigma = tau * sqrt(posterior variance)
-// (0 at the last step).  x_next may alias x_cur (each lane reads its own
-// element before writing it).  On the last step the result also goes to
-// tok_out[out_rows[r]].
-template <typename T, int CM>
-__global__ __launch_bounds__(256) void head_out_step_kernel(
-    float *x_next, float *__restrict__ tok_out, const T *__restrict__ a,
-    const float *__restrict__ w_out, const float *__restrict__ b_out, const float *x_cur,
-    const float *__restrict__ noise, const int32_t *__restrict__ out_rows, int rows, int W, int C,
-    float sra, float srm1, float c1, float c2, float sigma) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  float acc[CM];
-#pragma unroll
-  for (int c = 0; c < CM; ++c) acc[c] = 0.f;
-  const T *ar = a + (size_t)r * W;
-  for (int k0 = 4 * lane; k0 < W; k0 += 256) {
-    const float4 av = load_row4(ar + k0);
-    float4 wv[CM];  // all loads of this chunk first (rows past C repeat the last one)
-#pragma unroll
-    for (int c = 0; c < CM; ++c)
-      wv[c] = *reinterpret_cast<const float4 *>(w_out + (size_t)min(c, C - 1) * W + k0);
-#pragma unroll
-    for (int c = 0; c < CM; ++c)
-      acc[c] = fmaf(av.x, wv[c].x, fmaf(av.y, wv[c].y, fmaf(av.z, wv[c].z, fmaf(av.w, wv[c].w, acc[c]))));
+// Sum over the wavefront, every lane (lane exchanges inside 16 lanes as DPP
+// modifiers: a shuffle through the LDS crossbar costs several times as long,
+// and the row kernel below is a chain of such sums).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+  v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  v = dpp_add<0x140>(v);  // row_mirror: every lane of 16 holds their sum
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+
+// Sum over a workgroup of 256 threads; `red` holds four floats.
+__device__ __forceinline__ float block_sum(float v, float *red) {
+  v = wave_sum_dpp(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Everything between two sampling steps' blocks, one workgroup per row (the
+// row's columns are spread over 256 threads, NV each):
+//   out: a = LN(h) (1 + scale_f) + shift_f;  eps = w_out a + b_out;
+//        x0 = sra x - srm1 eps;  x' = c1 x0 + c2 x + sigma noise  (sigma =
+//        tau * sqrt(posterior variance), 0 at the last step, where the
+//        result also goes to tok_out[out_rows[r]]);
+//   in:  h = w_in x' + b_in;  a = LN(h) (1 + scale_0) + shift_0;
+//   sc:  SiLU(cond + temb) of a later step's modulations.
+// Its time is its chain of dependent loads and sums; as four kernels of one
+// wavefront per row (norm, output + update, input + norm, SiLU) the same work
+// took 29 us per sampling step at 512 rows of width 1280.
+template <typename T, int NV, int CM>
+__global__ __launch_bounds__(256) void head_step_kernel(HeadRows p) {
+  constexpr int W = NV * 256;
+  constexpr float inv_w = 1.0f / W;
+  __shared__ float red[4][4];
+  __shared__ float part[4][CM];
+  __shared__ float xv[CM];
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int C = p.c_tok;
+  float *hr = p.h + (size_t)r * W;
+  const T *mr = static_cast<const T *>(p.mod) + (size_t)r * p.mod_ld;
+  if (tid < CM) {
+    const float x = tid < C ? p.x_cur[(size_t)r * C + tid] : 0.f;
+    if (!p.out || tid >= C) xv[tid] = x;
   }
-  float e = 0.f;
+  if (p.out) {
+    float v[NV];
+    float s = 0.f;
 #pragma unroll
-  for (int c = 0; c < CM; ++c) {
-    const float s = wave_sum(acc[c]);
-    if (lane == c) e = s;
+    for (int k = 0; k < NV; ++k) {
+      v[k] = hr[tid + 256 * k];
+      s += v[k];
+    }
+    const float mean = block_sum(s, red[0]) * inv_w;
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      v[k] -= mean;
+      ss += v[k] * v[k];
+    }
+    const float rstd = 1.0f / sqrtf(block_sum(ss, red[1]) * inv_w + p.eps);
+    float acc[CM];
+#pragma unroll
+    for (int c = 0; c < CM; ++c) acc[c] = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int col = tid + 256 * k;
+      const float a =
+          v[k] * rstd * (1.f + to_f32(mr[p.scale_off + col])) + to_f32(mr[p.shift_off + col]);
+#pragma unroll
+      for (int c = 0; c < CM; ++c)  // rows past C repeat the last one
+        acc[c] = fmaf(a, p.w_out[(size_t)min(c, C - 1) * W + col], acc[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CM; ++c) {
+      const float t = wave_sum_dpp(acc[c]);
+      if (lane == 0) part[wave][c] = t;
+    }
+    __syncthreads();
+    if (tid < C) {
+      const size_t idx = (size_t)r * C + tid;
+      const float xc = p.x_cur[idx];
+      const float eps_v =
+          (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]) + p.b_out[tid];
+      const float x0 = p.st.sra * xc - p.st.srm1 * eps_v;
+      float xn = p.st.c1 * x0 + p.st.c2 * xc;
+      if (p.st.sigma != 0.f) xn = fmaf(p.st.sigma, p.noise[idx], xn);
+      p.x_next[idx] = xn;
+      if (p.tok_out) p.tok_out[(size_t)p.out_rows[r] * C + tid] = xn;
+      xv[tid] = xn;
+    }
   }
-  if (lane < C) {
-    const size_t idx = (size_t)r * C + lane;
-    const float xv = x_cur[idx];
-    const float eps_v = e + b_out[lane];
-    const float x0 = sra * xv - srm1 * eps_v;
-    float xn = c1 * x0 + c2 * xv;
-    if (sigma != 0.f) xn = fmaf(sigma, noise[idx], xn);
-    x_next[idx] = xn;
-    if (tok_out) tok_out[(size_t)out_rows[r] * C + lane] = xn;
+  if (p.in) {
+    __syncthreads();
+    float v[NV];
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int col = tid + 256 * k;
+      float h = p.b_in[col];
+#pragma unroll
+      for (int c = 0; c < CM; ++c)  // channels past C hold 0
+        h = fmaf(p.w_in_t[(size_t)min(c, C - 1) * W + col], xv[c], h);
+      hr[col] = h;
+      v[k] = h;
+      s += h;
+    }
+    const float mean = block_sum(s, red[2]) * inv_w;
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      v[k] -= mean;
+      ss += v[k] * v[k];
+    }
+    const float rstd = 1.0f / sqrtf(block_sum(ss, red[3]) * inv_w + p.eps);
+    T *ar = static_cast<T *>(p.a) + (size_t)r * W;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int col = tid + 256 * k;
+      ar[col] = from_f32<T>(v[k] * rstd * (1.f + to_f32(mr[W + col])) + to_f32(mr[col]));
+    }
+  }
+  if (p.sc) {
+    T *sr = static_cast<T *>(p.sc) + (size_t)r * W;
+    const float *cr = p.cond + (size_t)r * W;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int col = tid + 256 * k;
+      sr[col] = from_f32<T>(silu(cr[col] + p.temb[col]));
+    }
   }
 }
 
@@ -468,20 +504,6 @@ hipError_t launch_silu_cond(DType dt, void *sc, const float *cond, const float *
   return hipGetLastError();
 }
 
-template <typename T, int NV>
-static void head_in_mod_dispatch(int grid, hipStream_t s, T *a, float *h, const float *x,
-                                 const float *w_in_t, const float *b_in, const T *mod, int mod_ld,
-                                 int rows, int c, float eps) {
-#define E_(CM) launch_kernel(head_in_mod_kernel<T, NV, CM>, grid, 256, 0, s, a, h, x, w_in_t, b_in, mod, mod_ld, \
-                                                                 rows, c, eps)
-  if (c <= 4) E_(4);
-  else if (c <= 8) E_(8);
-  else if (c <= 16) E_(16);
-  else if (c <= 32) E_(32);
-  else E_(64);
-#undef E_
-}
-
 hipError_t launch_transpose_f32(float *w_t, const float *w, int32_t rows, int32_t cols,
                                 hipStream_t s) {
   const int n = rows * cols;
@@ -490,83 +512,51 @@ hipError_t launch_transpose_f32(float *w_t, const float *w, int32_t rows, int32_
   return hipGetLastError();
 }
 
-hipError_t launch_head_in_mod(DType dt, void *a, float *h, const float *x, const float *w_in_t,
-                              const float *b_in, const void *mod, int32_t mod_ld, int32_t rows,
-                              int32_t width, int32_t c_tok, float eps, hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  if (width % 256 != 0 || c_tok < 1 || c_tok > 64) return hipErrorInvalidValue;
-  const int grid = (rows + 3) / 4;
-  if (dt == DType::F32) {
-#define L_(NV)                                                                                \
-  head_in_mod_dispatch<float, NV>(grid, s, static_cast<float *>(a), h, x, w_in_t, b_in,          \
-                                  static_cast<const float *>(mod), mod_ld, rows, c_tok, eps)
-    MARCHE_NV_SWITCH(width / 256, L_)
-#undef L_
-  } else {
-#define L_(NV)                                                                              \
-  head_in_mod_dispatch<bf16, NV>(grid, s, static_cast<bf16 *>(a), h, x, w_in_t, b_in,          \
-                                 static_cast<const bf16 *>(mod), mod_ld, rows, c_tok, eps)
-    MARCHE_NV_SWITCH(width / 256, L_)
-#undef L_
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_head_gate_mod(DType dt, void *a, float *h, const float *t, const void *mod,
-                                int32_t mod_ld, int32_t gate_off, int32_t shift_off,
-                                int32_t scale_off, int32_t rows, int32_t width, float eps,
-                                hipStream_t s) {
+hipError_t launch_head_mod(DType dt, void *a, const float *h, const void *mod, int32_t mod_ld,
+                           int32_t shift_off, int32_t scale_off, int32_t rows, int32_t width,
+                           float eps, hipStream_t s) {
   if (rows == 0) return hipSuccess;
   if (width % 256 != 0) return hipErrorInvalidValue;
   const int grid = (rows + 3) / 4;
   if (dt == DType::F32) {
-#define L_(NV)                                                                              \
-  launch_kernel(head_gate_mod_kernel<float, NV>, grid, 256, 0, s, static_cast<float *>(a), h, t,          \
-                                                       static_cast<const float *>(mod), mod_ld, \
-                                                       gate_off, shift_off, scale_off, rows, eps)
+#define L_(NV)                                                                               \
+  launch_kernel(head_mod_kernel<float, NV>, grid, 256, 0, s, static_cast<float *>(a), h,     \
+                static_cast<const float *>(mod), mod_ld, shift_off, scale_off, rows, eps)
     MARCHE_NV_SWITCH(width / 256, L_)
 #undef L_
   } else {
-#define L_(NV)                                                                            \
-  launch_kernel(head_gate_mod_kernel<bf16, NV>, grid, 256, 0, s, static_cast<bf16 *>(a), h, t,          \
-                                                      static_cast<const bf16 *>(mod), mod_ld, \
-                                                      gate_off, shift_off, scale_off, rows, eps)
+#define L_(NV)                                                                               \
+  launch_kernel(head_mod_kernel<bf16, NV>, grid, 256, 0, s, static_cast<bf16 *>(a), h,       \
+                static_cast<const bf16 *>(mod), mod_ld, shift_off, scale_off, rows, eps)
     MARCHE_NV_SWITCH(width / 256, L_)
 #undef L_
   }
   return hipGetLastError();
 }
 
-template <typename T>
-static void head_out_step_dispatch(int grid, hipStream_t s, float *x_next, float *tok_out,
-                                   const T *a, const float *w_out, const float *b_out,
-                                   const float *x_cur, const float *noise, const int32_t *out_rows,
-                                   int rows, int W, int c, const HeadStep &st) {
-#define E_(CM)                                                                                 \
-  launch_kernel(head_out_step_kernel<T, CM>, grid, 256, 0, s, x_next, tok_out, a, w_out, b_out, x_cur, noise, \
-                                                   out_rows, rows, W, c, st.sra, st.srm1, st.c1,   \
-                                                   st.c2, st.sigma)
-  if (c <= 4) E_(4);
-  else if (c <= 8) E_(8);
-  else if (c <= 16) E_(16);
-  else if (c <= 32) E_(32);
+template <typename T, int NV>
+static void head_step_dispatch(const HeadRows &p, hipStream_t s) {
+#define E_(CM) launch_kernel(head_step_kernel<T, NV, CM>, p.rows, 256, 0, s, p)
+  if (p.c_tok <= 4) E_(4);
+  else if (p.c_tok <= 8) E_(8);
+  else if (p.c_tok <= 16) E_(16);
+  else if (p.c_tok <= 32) E_(32);
   else E_(64);
 #undef E_
 }
 
-hipError_t launch_head_out_step(DType dt, float *x_next, float *tok_out, const void *a,
-                                const float *w_out, const float *b_out, const float *x_cur,
-                                const float *noise, const int32_t *out_rows, int32_t rows,
-                                int32_t width, int32_t c_tok, const HeadStep &st, hipStream_t s) {
-  if (rows == 0) return hipSuccess;
-  if (width % 256 != 0 || c_tok < 1 || c_tok > 64) return hipErrorInvalidValue;
-  const int grid = (rows + 3) / 4;
-  if (dt == DType::F32)
-    head_out_step_dispatch(grid, s, x_next, tok_out, static_cast<const float *>(a), w_out, b_out,
-                           x_cur, noise, out_rows, rows, width, c_tok, st);
-  else
-    head_out_step_dispatch(grid, s, x_next, tok_out, static_cast<const bf16 *>(a), w_out, b_out,
-                           x_cur, noise, out_rows, rows, width, c_tok, st);
+hipError_t launch_head_step(DType dt, const HeadRows &p, int32_t width, hipStream_t s) {
+  if (p.rows == 0) return hipSuccess;
+  if (width % 256 != 0 || p.c_tok < 1 || p.c_tok > 64) return hipErrorInvalidValue;
+  if (dt == DType::F32) {
+#define L_(NV) head_step_dispatch<float, NV>(p, s)
+    MARCHE_NV_SWITCH(width / 256, L_)
+#undef L_
+  } else {
+#define L_(NV) head_step_dispatch<bf16, NV>(p, s)
+    MARCHE_NV_SWITCH(width / 256, L_)
+#undef L_
+  }
   return hipGetLastError();
 }
 

@@ -106,20 +106,20 @@ marche_status_t check_model(const marche_model_t *m) {
 // query-chunk width (1, 2, 4 or 8 wavefronts of 32 queries), chosen from the
 // largest active set and the number of (image, head) pairs of the call (fp32
 // attention is timed under the first); each bf16 GEMM has a 128x256, a 256x256
-// (class + 1), a 64x128 (_S), a 128x128 (_M) and a 320x256 (_I) tile
-// instantiation, chosen from its shape (fp32 GEMMs are timed under the
+// (class + 1), a 64x128 (_S), a 128x128 (_M), a 320x256 (_I) and, for the
+// sampler, a few-row (_R) instantiation, chosen from its shape (fp32 GEMMs are timed under the
 // first).
 enum KClass {
   K_ROW_MAP, K_GATHER_LN, K_GEMM_QKV, K_GEMM_QKV_L, K_ATTN_W1, K_ATTN_W2, K_ATTN_W4,
   K_ATTN_SCORES, K_GEMM_O, K_GEMM_O_L, K_GEMM_FC1, K_GEMM_FC1_L, K_GEMM_FC2, K_GEMM_FC2_L,
   K_SELECT, K_DECODER_INPUT, K_FILL, K_ATTN2_W1, K_ATTN2_W2, K_ATTN2_W4, K_CONCAT, K_ATTN_RES,
   K_ENC_INPUT, K_MASK_FILL, K_LN_ROWS, K_GEMM_EMBED, K_GEMM_EMBED_L, K_TIME_SINUS, K_GEMM_HEAD,
-  K_GEMM_HEAD_L, K_GEMM_HEAD_SILU, K_GEMM_HEAD_SILU_L, K_HEAD_SILU_COND, K_HEAD_IN_MOD,
-  K_HEAD_GATE_MOD, K_HEAD_OUT_STEP, K_GEMM_QKV_S, K_GEMM_O_S, K_GEMM_FC1_S, K_GEMM_FC2_S,
+  K_GEMM_HEAD_L, K_GEMM_HEAD_SILU, K_GEMM_HEAD_SILU_L, K_HEAD_SILU_COND, K_HEAD_MOD, K_HEAD_STEP,
+  K_GEMM_QKV_S, K_GEMM_O_S, K_GEMM_FC1_S, K_GEMM_FC2_S,
   K_GEMM_EMBED_S, K_GEMM_HEAD_S, K_GEMM_HEAD_SILU_S, K_TRANSPOSE, K_GEMM_QKV_M, K_GEMM_O_M,
   K_GEMM_FC1_M, K_GEMM_FC2_M, K_GEMM_EMBED_M, K_GEMM_HEAD_M, K_GEMM_HEAD_SILU_M,
   K_ATTN_RES_SC, K_ATTN_W8, K_ATTN_SC, K_GEMM_QKV_I, K_GEMM_O_I, K_GEMM_FC1_I, K_GEMM_FC2_I,
-  K_GEMM_EMBED_I, K_GEMM_HEAD_I, K_GEMM_HEAD_SILU_I,
+  K_GEMM_EMBED_I, K_GEMM_HEAD_I, K_GEMM_HEAD_SILU_I, K_GEMM_HEAD_R, K_GEMM_HEAD_SILU_R,
   K_NCLASS
 };
 const char *const kClassNames[K_NCLASS] = {
@@ -131,13 +131,14 @@ const char *const kClassNames[K_NCLASS] = {
     "concat_kv",         "attention_res",  "encoder_input",     "mask_fill",
     "ln_rows",           "gemm_embed_t128x256", "gemm_embed_t256", "time_sinus",
     "gemm_head_t128x256", "gemm_head_t256", "gemm_head_silu_t128x256", "gemm_head_silu_t256",
-    "head_silu_cond",    "head_in_mod",    "head_gate_mod",     "head_out_step",
+    "head_silu_cond",    "head_mod",       "head_step",
     "gemm_qkv_t64x128",  "gemm_o_t64x128", "gemm_fc1_t64x128",  "gemm_fc2_t64x128",
     "gemm_embed_t64x128", "gemm_head_t64x128", "gemm_head_silu_t64x128", "transpose",
     "gemm_qkv_t128",     "gemm_o_t128",    "gemm_fc1_t128",     "gemm_fc2_t128",
     "gemm_embed_t128",   "gemm_head_t128", "gemm_head_silu_t128", "attention_res_scores", "attention_q256",
     "attention_scores",  "gemm_qkv_t320",  "gemm_o_t320",      "gemm_fc1_t320",
-    "gemm_fc2_t320",     "gemm_embed_t320", "gemm_head_t320",  "gemm_head_silu_t320"};
+    "gemm_fc2_t320",     "gemm_embed_t320", "gemm_head_t320",  "gemm_head_silu_t320",
+    "gemm_head_rows",    "gemm_head_silu_rows"};
 static_assert(sizeof(kClassNames) / sizeof(kClassNames[0]) == K_NCLASS, "one name per class");
 
 // Launches inside marche_step in layers where not every token of every image
@@ -160,6 +161,10 @@ const char *class_name(int i) {
 // Timing class of a GEMM launch: base is the projection's 128x256 class, the
 // 256x256 class follows it; the 64x128 classes are listed separately.
 int gemm_class(int base, DType dt, int32_t m, int32_t n, int32_t k) {
+  if (gemm_few_rows(dt, m)) {
+    if (base == K_GEMM_HEAD) return K_GEMM_HEAD_R;
+    if (base == K_GEMM_HEAD_SILU) return K_GEMM_HEAD_SILU_R;
+  }
   const int kind = gemm_tile_kind(dt, m, n, k);
   if (kind == GEMM_TILE_256) return base + 1;
   if (kind == GEMM_TILE_320) {
@@ -889,14 +894,15 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
                         dec_ln_eps, stream));
   LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, W, D), 2.0 * M * (double)W * D,
          es * ((double)M * D + (double)W * D) + 4.0 * M * W,
-         launch_gemm_plain(dt, z, w->w_c, fp(w->b_c), M, W, D, cond, DType::F32, false, stream));
+         launch_gemm_plain(dt, z, w->w_c, fp(w->b_c), M, W, D, cond, DType::F32, false, W, stream));
   LAUNCH(K_TIME_SINUS, 0, es * (double)T * F, launch_time_sinus(dt, sinus, T, F, stream));
   LAUNCH(gemm_class(K_GEMM_HEAD_SILU, dt, T, W, F), 2.0 * T * (double)W * F,
          es * ((double)T * F + (double)W * F + (double)T * W),
-         launch_gemm_plain(dt, sinus, w->w_t1, fp(w->b_t1), T, W, F, h1, dt, true, stream));
+         launch_gemm_plain(dt, sinus, w->w_t1, fp(w->b_t1), T, W, F, h1, dt, true, W, stream));
   LAUNCH(gemm_class(K_GEMM_HEAD, dt, T, W, W), 2.0 * T * (double)W * W,
          es * ((double)T * W + (double)W * W) + 4.0 * T * W,
-         launch_gemm_plain(dt, h1, w->w_t2, fp(w->b_t2), T, W, W, temb, DType::F32, false, stream));
+         launch_gemm_plain(dt, h1, w->w_t2, fp(w->b_t2), T, W, W, temb, DType::F32, false, W,
+                           stream));
 
   // cosine schedule (double precision on the host)
   std::vector<double> betas(T), abar(T);
@@ -912,47 +918,122 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
       abar[i] = prod;
     }
   }
-  const float *x_init = noise + (size_t)T * M * C;
-  for (int i = T - 1; i >= 0; --i) {
-    const float *xc = i == T - 1 ? x_init : xs;
+  // Launch order.  Step i's modulations (chunk c < nb: shift, scale and gate
+  // of block c; chunk nb: the final layer's shift and scale) depend on the
+  // condition and the timestep only, so they need not wait for step i + 1.
+  // With side products (`beside`: bf16, at least two blocks, and they fit) the
+  // one modulation buffer is refilled as it is used up:
+  //   chunk c < nb - 1 of step i  beside block c + 1 of step i + 1 (its last
+  //                               reader is block c's second product there),
+  //   chunk nb - 1                beside block 0 of step i,
+  //   chunk nb                    beside blocks 1 .. nb - 1 of step i;
+  // otherwise chunks 0 .. nb - 1 of step i are a product of their own before
+  // step i + 1's row kernel (which applies chunk 0) and chunk nb one after it.
+  // So SiLU(condition + time embedding) is held for two steps; the second
+  // buffer takes the place of the block outputs, which the gated residual in
+  // the second product's epilogue never stores.
+  void *scs[2] = {sc, tbuf};
+  const int tw = W / 128;                     // 128-column tiles of a width
+  const int side_fit = head_side_tiles(dt, M, W);
+  const int final_share = nb > 1 ? (2 * tw + 2 * nb - 3) / (2 * nb - 2) : 0;
+  const bool beside = nb > 1 && side_fit >= (3 * tw + 1) / 2 + final_share;
+  auto mod_cols = [&](void *from, int c0, int n) {  // columns [c0, c0 + n) from SiLU rows
+    return HeadSide{from, static_cast<const char *>(w->w_ada) + (size_t)c0 * W * es,
+                    fp(w->b_ada) + c0, static_cast<char *>(mod) + (size_t)c0 * es, n};
+  };
+  auto mod_gemm = [&](void *from, int c0, int n) -> marche_status_t {
+    const HeadSide m = mod_cols(from, c0, n);
+    LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, n, W), 2.0 * M * (double)n * W,
+           es * ((double)M * W + (double)n * W + (double)M * n),
+           launch_gemm_plain(dt, m.a, m.w, m.bias, M, n, W, m.out, dt, false, ML, stream));
+    return MARCHE_OK;
+  };
+  auto silu_rows = [&](int i) -> marche_status_t {
     LAUNCH(K_HEAD_SILU_COND, 0, 4.0 * M * W + es * (double)M * W,
-           launch_silu_cond(dt, sc, cond, temb + (size_t)i * W, M, W, stream));
-    LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, ML, W), 2.0 * M * (double)ML * W,
-           es * ((double)M * W + (double)ML * W + (double)M * ML),
-           launch_gemm_plain(dt, sc, w->w_ada, fp(w->b_ada), M, ML, W, mod, dt, false, stream));
-    LAUNCH(K_HEAD_IN_MOD, 2.0 * M * (double)W * C,
-           4.0 * M * C + 4.0 * M * W + es * 3.0 * M * W,
-           launch_head_in_mod(dt, abuf, hbuf, xc, w_in_t, fp(w->b_in), mod, ML, M, W, C,
-                              hd->ln_eps, stream));
+           launch_silu_cond(dt, scs[i & 1], cond, temb + (size_t)i * W, M, W, stream));
+    return MARCHE_OK;
+  };
+  HeadRows hr{};
+  hr.h = hbuf;
+  hr.a = abuf;
+  hr.mod = mod;
+  hr.mod_ld = ML;
+  hr.shift_off = 3 * nb * W;
+  hr.scale_off = hr.shift_off + W;
+  hr.w_out = fp(w->w_out);
+  hr.b_out = fp(w->b_out);
+  hr.w_in_t = w_in_t;
+  hr.b_in = fp(w->b_in);
+  hr.x_next = xs;
+  hr.out_rows = out_rows;
+  hr.cond = cond;
+  hr.rows = M;
+  hr.c_tok = C;
+  hr.eps = hd->ln_eps;
+
+  st = silu_rows(T - 1);
+  if (st != MARCHE_OK) return st;
+  if (T > 1 && (st = silu_rows(T - 2)) != MARCHE_OK) return st;
+  if ((st = mod_gemm(scs[(T - 1) & 1], 0, 3 * (beside ? nb - 1 : nb) * W)) != MARCHE_OK) return st;
+  hr.in = true;
+  hr.x_cur = noise + (size_t)T * M * C;
+  LAUNCH(K_HEAD_STEP, 2.0 * M * (double)W * C, 4.0 * M * C + 4.0 * M * W + es * 3.0 * M * W,
+         launch_head_step(dt, hr, W, stream));
+  hr.out = true;
+  for (int i = T - 1; i >= 0; --i) {
+    void *sc_i = scs[i & 1], *sc_p = scs[(i & 1) ^ 1];  // of this step and of the next (i - 1)
+    if (!beside && (st = mod_gemm(sc_i, 3 * nb * W, 2 * W)) != MARCHE_OK) return st;
     for (int k = 0; k < nb; ++k) {
       const char *w1 = static_cast<const char *>(w->w_1) + (size_t)k * W * W * es;
       const char *w2 = static_cast<const char *>(w->w_2) + (size_t)k * W * W * es;
-      LAUNCH(gemm_class(K_GEMM_HEAD_SILU, dt, M, W, W), 2.0 * M * (double)W * W,
-             es * (2.0 * M * W + (double)W * W),
-             launch_gemm_plain(dt, abuf, w1, fp(w->b_1) + (size_t)k * W, M, W, W, ybuf, dt, true,
-                               stream));
-      LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, W, W), 2.0 * M * (double)W * W,
-             es * ((double)M * W + (double)W * W) + 4.0 * M * W,
-             launch_gemm_plain(dt, ybuf, w2, fp(w->b_2) + (size_t)k * W, M, W, W, tbuf,
-                               DType::F32, false, stream));
-      // the next modulated norm: block k + 1's, or the final layer's
-      const int nxt = 3 * (k + 1) * W;
-      LAUNCH(K_HEAD_GATE_MOD, 0, 4.0 * 3.0 * M * W + es * 4.0 * M * W,
-             launch_head_gate_mod(dt, abuf, hbuf, tbuf, mod, ML, 3 * k * W + 2 * W, nxt, nxt + W,
-                                  M, W, hd->ln_eps, stream));
+      HeadSides sides[2] = {};
+      double side_n[2] = {0, 0};
+      for (int g = 0; g < 2 && beside; ++g) {
+        sides[g].ld = ML;
+        // half of a chunk's 3 W columns to each of the block's products
+        const int lo = g ? (3 * tw + 1) / 2 : 0, hi = g ? 3 * tw : (3 * tw + 1) / 2;
+        if (k == 0)
+          sides[g].s[0] = mod_cols(sc_i, 3 * (nb - 1) * W + lo * 128, (hi - lo) * 128);
+        else if (i > 0)
+          sides[g].s[0] = mod_cols(sc_p, 3 * (k - 1) * W + lo * 128, (hi - lo) * 128);
+        if (k > 0) {
+          const int q = 2 * (k - 1) + g, nq = 2 * nb - 2;
+          const int f0 = 2 * tw * q / nq, f1 = 2 * tw * (q + 1) / nq;
+          sides[g].s[1] = mod_cols(sc_i, 3 * nb * W + f0 * 128, (f1 - f0) * 128);
+        }
+        side_n[g] = (double)sides[g].s[0].n + sides[g].s[1].n;
+      }
+      LAUNCH(gemm_class(K_GEMM_HEAD_SILU, dt, M, W, W), 2.0 * M * (W + side_n[0]) * W,
+             es * (2.0 * M * W + (double)W * W + side_n[0] * (W + M)),
+             launch_head_gemm_silu(dt, abuf, w1, fp(w->b_1) + (size_t)k * W, M, W, ybuf, sides[0],
+                                   stream));
+      LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, W, W), 2.0 * M * (W + side_n[1]) * W,
+             es * (2.0 * M * W + (double)W * W + side_n[1] * (W + M)) + 8.0 * M * W,
+             launch_head_gemm_gate(dt, ybuf, w2, fp(w->b_2) + (size_t)k * W, M, W, hbuf,
+                                   static_cast<const char *>(mod) + (size_t)(3 * k + 2) * W * es,
+                                   ML, sides[1], stream));
+      if (k + 1 < nb) {
+        const int nxt = 3 * (k + 1) * W;
+        LAUNCH(K_HEAD_MOD, 0, 4.0 * M * W + es * 3.0 * M * W,
+               launch_head_mod(dt, abuf, hbuf, mod, ML, nxt, nxt + W, M, W, hd->ln_eps, stream));
+      }
     }
+    if (!beside && i > 0 && (st = mod_gemm(sc_p, 0, 3 * nb * W)) != MARCHE_OK) return st;
     const double ab = abar[i], abp = i > 0 ? abar[i - 1] : 1.0, b = betas[i];
-    HeadStep hs;
-    hs.sra = (float)(1.0 / std::sqrt(ab));
-    hs.srm1 = (float)std::sqrt(1.0 / ab - 1.0);
-    hs.c1 = (float)(b * std::sqrt(abp) / (1.0 - ab));
-    hs.c2 = (float)((1.0 - abp) * std::sqrt(1.0 - b) / (1.0 - ab));
-    hs.sigma = i > 0 ? (float)(temperature * std::sqrt(b * (1.0 - abp) / (1.0 - ab))) : 0.0f;
-    LAUNCH(K_HEAD_OUT_STEP, 2.0 * M * (double)W * C,
-           es * (double)M * W + 4.0 * ((double)C * W + 3.0 * M * C),
-           launch_head_out_step(dt, xs, i == 0 ? tok_out : nullptr, abuf, fp(w->w_out),
-                                fp(w->b_out), xc, noise + (size_t)i * M * C, out_rows, M, W, C,
-                                hs, stream));
+    hr.st.sra = (float)(1.0 / std::sqrt(ab));
+    hr.st.srm1 = (float)std::sqrt(1.0 / ab - 1.0);
+    hr.st.c1 = (float)(b * std::sqrt(abp) / (1.0 - ab));
+    hr.st.c2 = (float)((1.0 - abp) * std::sqrt(1.0 - b) / (1.0 - ab));
+    hr.st.sigma = i > 0 ? (float)(temperature * std::sqrt(b * (1.0 - abp) / (1.0 - ab))) : 0.0f;
+    hr.in = i > 0;
+    hr.noise = noise + (size_t)i * M * C;
+    hr.tok_out = i == 0 ? tok_out : nullptr;
+    hr.sc = i > 1 ? sc_i : nullptr;  // of step i - 2, in the buffer step i is done with
+    hr.temb = i > 1 ? temb + (size_t)(i - 2) * W : nullptr;
+    LAUNCH(K_HEAD_STEP, (i > 0 ? 4.0 : 2.0) * M * (double)W * C,
+           (es * 5.0 + 12.0) * (double)M * W + 4.0 * (2.0 * C * W + 3.0 * M * C),
+           launch_head_step(dt, hr, W, stream));
+    hr.x_cur = xs;
   }
   return MARCHE_OK;
 }

@@ -77,24 +77,37 @@ hipError_t launch_silu_cond(DType dt, void *sc, const float *cond, const float *
 // w_t = w^T for a [rows][cols] float32 matrix.
 hipError_t launch_transpose_f32(float *w_t, const float *w, int32_t rows, int32_t cols,
                                 hipStream_t s);
-// h = w_in x + b_in (w_in given transposed, [C][W]); a = LN(h) (1 + scale) +
-// shift with block 0's modulation.
-hipError_t launch_head_in_mod(DType dt, void *a, float *h, const float *x, const float *w_in_t,
-                              const float *b_in, const void *mod, int32_t mod_ld, int32_t rows,
-                              int32_t width, int32_t c_tok, float eps, hipStream_t s);
-// h += gate t; a = LN(h) (1 + scale) + shift (slices of mod at the offsets).
-hipError_t launch_head_gate_mod(DType dt, void *a, float *h, const float *t, const void *mod,
-                                int32_t mod_ld, int32_t gate_off, int32_t shift_off,
-                                int32_t scale_off, int32_t rows, int32_t width, float eps,
-                                hipStream_t s);
-// Coefficients of one DDPM step (see head_out_step_kernel).
+// a = LN(h) (1 + scale) + shift (slices of mod at the offsets).
+hipError_t launch_head_mod(DType dt, void *a, const float *h, const void *mod, int32_t mod_ld,
+                           int32_t shift_off, int32_t scale_off, int32_t rows, int32_t width,
+                           float eps, hipStream_t s);
+// Coefficients of one DDPM step (see head_step_kernel).
 struct HeadStep {
   float sra, srm1, c1, c2, sigma;
 };
-hipError_t launch_head_out_step(DType dt, float *x_next, float *tok_out, const void *a,
-                                const float *w_out, const float *b_out, const float *x_cur,
-                                const float *noise, const int32_t *out_rows, int32_t rows,
-                                int32_t width, int32_t c_tok, const HeadStep &st, hipStream_t s);
+// Everything between two sampling steps' blocks, row by row (see
+// head_step_kernel).  `out`: this step's output projection and DDPM update
+// (final modulation at shift_off, scale_off); `in`: the next step's input
+// projection and first modulated norm (slices 0 and width of mod); sc != NULL:
+// SiLU(cond + temb) into it.
+struct HeadRows {
+  bool out, in;
+  float *h;
+  void *a;
+  const void *mod;
+  int32_t mod_ld, shift_off, scale_off;
+  const float *w_out, *b_out;    // [C][W], [C]
+  const float *w_in_t, *b_in;    // [C][W], [W]
+  const float *x_cur, *noise;    // [rows][C]
+  float *x_next, *tok_out;       // tok_out: last step only
+  const int32_t *out_rows;
+  HeadStep st;
+  void *sc;
+  const float *cond, *temb;      // [rows][W], [W]
+  int32_t rows, c_tok;
+  float eps;
+};
+hipError_t launch_head_step(DType dt, const HeadRows &p, int32_t width, hipStream_t s);
 
 // ---- GEMMs with fused epilogues (k_gemm.hip) ----
 // C[M][N] = A[M][K] . W[N][K]^T (+ bias) followed by one epilogue:
@@ -116,11 +129,35 @@ hipError_t launch_gemm_resid(DType dt, const void *a, const void *w, const float
                              hipStream_t s);
 hipError_t launch_gemm_gelu(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                             int32_t n, int32_t k, void *h, hipStream_t s);
-// Sampler GEMMs: out[r][c] = act(C + bias) as out_dt (row-major, ld = n), act
-// SiLU or the identity; a float32 GEMM writes float32 only.
+// Sampler GEMMs: out[r][c] = act(C + bias) as out_dt (row-major, row stride
+// ld), act SiLU or the identity; a float32 GEMM writes float32 only.
 hipError_t launch_gemm_plain(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                              int32_t n, int32_t k, void *out, DType out_dt, bool silu_act,
-                             hipStream_t s);
+                             int32_t ld, hipStream_t s);
+// The two products of a sampler block (width x width): y = SiLU(a w^T + bias),
+// and h += gate (a w^T + bias) with the gate a slice of the modulations.  Side
+// products out = a w^T + bias (bf16, same rows and reduction length as the
+// main one, n columns a multiple of 128, ld = HeadSides::ld) share the launch:
+// a block product of a few hundred rows leaves most compute units idle.
+struct HeadSide {
+  const void *a, *w;
+  const float *bias;
+  void *out;
+  int32_t n;
+};
+struct HeadSides {
+  HeadSide s[2];
+  int32_t ld;
+};
+// 128-column side tiles per launch that fit beside the main product in one
+// wave of workgroups (0: none, or no side products for this type).
+int head_side_tiles(DType dt, int32_t m, int32_t width);
+hipError_t launch_head_gemm_silu(DType dt, const void *a, const void *w, const float *bias,
+                                 int32_t m, int32_t width, void *y, const HeadSides &sides,
+                                 hipStream_t s);
+hipError_t launch_head_gemm_gate(DType dt, const void *a, const void *w, const float *bias,
+                                 int32_t m, int32_t width, float *h, const void *gate,
+                                 int32_t mod_ld, const HeadSides &sides, hipStream_t s);
 // Decoder embedding of the encoder rows scattered to their sequence positions
 // (n = d_model): x[b][j][c] = C + bias + pe[j][c], j the position encoder row
 // r = b * n_enc + i holds (i < n_buf: i; else n_buf + known[b][i - n_buf]).
@@ -136,6 +173,8 @@ enum GemmTile {
   GEMM_TILE_320 = 4
 };
 int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k);
+// Whether a sampler product of m rows runs the few-row kernel instead.
+bool gemm_few_rows(DType dt, int32_t m);
 // Compute units of the current device (queried once per device, then cached).
 int device_cu_count();
 

@@ -1,15 +1,20 @@
 """One block at the edges of the launch rules, against the fp64 oracle: fp32
 products of one row, of 16 / 32 / 64-row remainders and of enough rows for the
 64x64 tile; fp32 attention with one and with four rows per workgroup; bf16
-attention on ragged key tails at both head widths, with few (image, head)
-pairs (two key groups per workgroup) and with many, for one to four query
-blocks, with the score pass as a kernel of its own."""
+attention on ragged key tails at both head widths for one to four query
+blocks, with the score pass as a kernel of its own, and stand-alone with few
+(image, head) pairs (two key groups per workgroup) and with many; the sampler's block
+products and modulations at the row counts where their kernels change."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
+from oracle import mar
 from paper_2506_12035_amd import workload
-from tests.gpu_util import TOL, SingleLayer, f64, say
+from tests.gpu_util import TOL, SingleLayer, f64, rel_err, say
 from tests.test_gpu_layer import _check_layer, _oracle_layer
+from tests.test_gpu_mar import _oracle_head, _run_head
 
 pytestmark = pytest.mark.gpu
 
@@ -48,10 +53,8 @@ def test_f32_layer_shapes(case):
     _case(cfg, sizes, gens, seed=sum(sizes) + n)
 
 
-# Two images: at most 32 (image, head) pairs per query block; nine images: 144
-# and more.  Lists up to 32, 64, 128 and more rows; key tails of 1 and 37 (an
-# aligned length too: it takes the streaming kernel of its own with many
-# pairs).  More than 64 generating rows need the separate score pass at every
+# Lists up to 32, 64, 128 and more rows; key tails of 1 and 37, and aligned
+# lengths.  More than 64 generating rows need the separate score pass at every
 # length that the resident kernel does not take.
 BF16 = [
     (1024, 16, 64, 65, [32, 5], [32, 2]),
@@ -72,3 +75,82 @@ def test_bf16_attention_shapes(case):
     d, h, dh, n, sizes, gens = case
     cfg = workload.Config(61, "bf16-shape", 1, d, h, dh, 1024, n, 0, len(sizes), "bf16")
     _case(cfg, sizes, gens, seed=sum(sizes) + n)
+
+
+# (batch, heads, head_dim, queries, active keys, cached keys).  One and two key
+# groups; segments shorter than a tile, of one key, of whole tiles, and a
+# single segment; queries that are not the active keys.
+SEGMENTS = [
+    (2, 4, 64, 1, 1, 63), (2, 4, 80, 32, 64, 1), (3, 4, 80, 33, 1, 130), (2, 4, 64, 64, 0, 320),
+    (1, 4, 64, 200, 65, 128), (33, 8, 64, 17, 17, 47), (33, 8, 80, 40, 3, 190),
+    (22, 12, 64, 100, 64, 64), (22, 12, 80, 129, 100, 1),
+]
+
+
+@pytest.mark.parametrize("case", SEGMENTS, ids=lambda c: "b{}h{}d{}q{}-{}-{}".format(*c))
+def test_segment_shapes(case):
+    import torch
+    from oracle import block
+    from paper_2506_12035_amd import binding
+
+    B, H, dh, nq, na, nc = case
+    say(f"segment attention {case}")
+    rng = np.random.default_rng(nq + na + nc)
+    draw = lambda *s: workload.round_to(rng.standard_normal(s, dtype=np.float32), "bf16")
+    q, ka, va, kc, vc = (draw(B, nq, H * dh), draw(B, H, na, dh), draw(B, H, na, dh),
+                         draw(B, H, nc, dh), draw(B, H, nc, dh))
+    dev = [torch.from_numpy(t).to("cuda").bfloat16() if t.size else None for t in (q, ka, va, kc, vc)]
+    o = torch.full((B, nq, H * dh), float("nan"), device="cuda", dtype=torch.bfloat16)
+    binding.attention_segments(dev[0], o, nq, dev[1], dev[2], na, dev[3], dev[4], nc, B, H, dh,
+                               binding.MARCHE_BF16, binding.MARCHE_ATTN_TWO_SEGMENT)
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy().reshape(B, nq, H, dh)
+    for b in (0, B - 1):
+        for h in range(H):
+            ref = block.attention_two_segment(q[b, :, h * dh:(h + 1) * dh], ka[b, h], va[b, h],
+                                              kc[b, h], vc[b, h])
+            assert rel_err(got[b, :, h], ref) <= TOL["bf16"], (b, h)
+
+
+# (rows, width, blocks, sampling steps, channels, dtype): the few-row kernel with
+# 16, 32 and 64 rows, the 64x128 tile with a ragged last tile, row counts whose
+# modulations no longer fit beside the block products, one block (no
+# side products) and two, one to three sampling steps, other channel counts.
+SAMPLER = [
+    (1, 256, 2, 3, 16, "bf16"),
+    (16, 512, 3, 2, 16, "bf16"),
+    (17, 256, 1, 3, 5, "bf16"),
+    (33, 768, 2, 1, 16, "bf16"),
+    (64, 256, 5, 3, 33, "bf16"),
+    (65, 512, 2, 3, 16, "bf16"),
+    (200, 256, 1, 2, 16, "bf16"),
+    (1500, 1280, 3, 2, 16, "bf16"),
+    (5, 256, 2, 3, 16, "f32"),
+    (70, 512, 1, 2, 3, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", SAMPLER, ids=lambda c: "m{}w{}n{}t{}c{}-{}".format(*c))
+def test_sampler_shapes(case):
+    rows, width, blocks, steps, chans, dtype = case
+    tiny = workload.MAR_CONFIGS["tiny"]
+    B = rows // 100 + 2
+    mc = replace(tiny, dec=tiny.dec.with_(dtype=dtype, n_tokens=104, batch=B), head_width=width,
+                 head_blocks=blocks, sample_steps=steps, c_tok=chans, head_std=0.04)
+    cfg = mc.dec
+    say(f"sampler rows={rows} width={width} blocks={blocks} steps={steps} channels={chans} {dtype}")
+    hs = mar.HeadShape(width, blocks, chans, cfg.d_model, mc.t_freq, mc.head_eps)
+    head, emb = workload.head_weights(mc), workload.mar_embeddings(mc)
+    rng = np.random.default_rng(rows + width)
+    x_dec = rng.standard_normal((B, cfg.n_tokens, cfg.d_model)).astype(np.float32)
+    cells = rng.choice(B * cfg.n_img, size=rows, replace=False)
+    b_of, p_of = cells // cfg.n_img, cells % cfg.n_img
+    out_rows = (b_of * cfg.n_img + p_of).astype(np.int32)
+    src = (b_of * cfg.n_tokens + cfg.n_buf + p_of).astype(np.int32)
+    noise = workload.head_noise(mc, rows, rows)
+    got = _run_head(mc, head, emb, x_dec, src, out_rows, noise, 1.0)
+    ref = _oracle_head(mc, hs, head, emb, x_dec, b_of, p_of, noise, 1.0)
+    e = rel_err(got[out_rows], ref)
+    say(f"  max rel err {e:.2e}")
+    assert e <= TOL[dtype]
+    assert np.isnan(got[np.setdiff1d(np.arange(got.shape[0]), out_rows)]).all()
