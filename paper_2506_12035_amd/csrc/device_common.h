@@ -24,6 +24,23 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Sum over the wavefront, every lane (lane exchanges inside 16 lanes as DPP
+// modifiers: a shuffle through the LDS crossbar costs several times as long,
+// which counts where a kernel is a chain of such sums).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
+  v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  v = dpp_add<0x140>(v);  // row_mirror: every lane of 16 holds their sum
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  return v;
+}
+
 // Exact-erf GELU, z * Phi(z), written as max(z, 0) - |z| * Phi(-|z|) (the two
 // agree for either sign of z).  The normal tail is Phi(-a) = 2^P(min(a, 6)),
 // P(u) = c0 + c1 u + ... + c7 u^7 a polynomial fit to log2 Phi(-u) on [0, 6]

@@ -1460,10 +1460,70 @@ namespace rows16 {
 constexpr int kWaves = 8;
 constexpr int kBN = 16;
 
-// The 16 columns from n0 of the whole M <= MB * 16 rows.
-template <class Epi, int MB>
+// The activations of a block's first product are the modulated norm of h,
+// a = LN(h) (1 + scale) + shift.  With up to 16 rows every workgroup forms them
+// itself instead of a launch before it doing so: the rows' float32 values
+// are a few dozen KB that the L2 holds, and a launch costs as much as the
+// whole product.
+struct NormIn {
+  const float *h;  // [M][K]; NULL: the activations are given
+  const bf16 *shift, *scale;  // row stride mod_ld
+  int mod_ld;
+  float eps;
+};
+constexpr int kNormElems = 28 * 1024;  // M (K + 8) of them in LDS at most (56 KB)
+
+// Rows wave, wave + 8 of the activations into `lds` (row stride K + 8: the 16
+// rows of a fragment read start on distinct bank groups).
+__device__ __forceinline__ void norm_rows(const NormIn &in, int M, int K, bf16 *lds, int wave,
+                                          int lane) {
+  constexpr int NV = 16;  // K <= 4096: float4 chunks per lane
+  const int nv = K / 256;
+  for (int r = wave; r < M; r += kWaves) {
+    const f32x4 *hr = reinterpret_cast<const f32x4 *>(in.h + (size_t)r * K);
+    const bf16 *sh = in.shift + (size_t)r * in.mod_ld, *sc = in.scale + (size_t)r * in.mod_ld;
+    f32x4 v[NV];
+    bf16x4 a[NV], b[NV];
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (k < nv) {
+        v[k] = hr[lane + 64 * k];
+        a[k] = *reinterpret_cast<const bf16x4 *>(sc + 4 * (lane + 64 * k));
+        b[k] = *reinterpret_cast<const bf16x4 *>(sh + 4 * (lane + 64 * k));
+      }
+    big::pin();
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (k < nv) s += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
+    const float mean = wave_sum_dpp(s) / (float)K;
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (k < nv) {
+        v[k] -= mean;
+        ss += (v[k][0] * v[k][0] + v[k][1] * v[k][1]) + (v[k][2] * v[k][2] + v[k][3] * v[k][3]);
+      }
+    const float rstd = 1.0f / sqrtf(wave_sum_dpp(ss) / (float)K + in.eps);
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (k < nv) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o[e] = (bf16)(v[k][e] * rstd * (1.f + (float)a[k][e]) + (float)b[k][e]);
+        *reinterpret_cast<bf16x4 *>(lds + (size_t)r * (K + 8) + 4 * (lane + 64 * k)) = o;
+      }
+  }
+}
+
+// The 16 columns from n0 of the whole M <= MB * 16 rows.  NORM (MB = 1): the
+// activations come from `in` through `lds`.
+template <class Epi, int MB, bool NORM>
 __device__ __forceinline__ void tile(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M,
-                                     int K, const Epi epi, int n0, f32x4 (*part)[MB][64]) {
+                                     int K, const Epi epi, int n0, f32x4 (*part)[MB][64],
+                                     const NormIn &in, bf16 *lds) {
+  static_assert(!NORM || MB == 1, "one row block");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int steps = K / 32;  // of 32 k; wavefront w takes [w S / 8, (w + 1) S / 8)
@@ -1472,17 +1532,30 @@ __device__ __forceinline__ void tile(const bf16 *__restrict__ A, const bf16 *__r
   const bf16 *wp = W + (size_t)(n0 + (lane & 15)) * K + kl;
   const bf16 *xp[MB];
 #pragma unroll
-  for (int i = 0; i < MB; ++i) xp[i] = A + (size_t)min(i * 16 + (lane & 15), M - 1) * K + kl;
+  for (int i = 0; i < MB; ++i) {
+    const int row = min(i * 16 + (lane & 15), M - 1);
+    xp[i] = NORM ? lds + (size_t)row * (K + 8) + kl : A + (size_t)row * K + kl;
+  }
   f32x4 acc[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) acc[i] = f32x4{};
   constexpr int U = 5;  // steps whose loads are in flight together
   int s = s0;
+  bf16x8 w[U];
+  if constexpr (NORM) {
+    // the first weights are on their way while the activations are formed
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      w[u] = *reinterpret_cast<const bf16x8 *>(wp + min(s + u, steps - 1) * 32);
+    big::pin();
+    norm_rows(in, M, K, lds, wave, lane);
+    __syncthreads();
+  }
   for (; s + U <= s1; s += U) {
-    bf16x8 w[U], x[U][MB];
+    bf16x8 x[U][MB];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      w[u] = *reinterpret_cast<const bf16x8 *>(wp + (s + u) * 32);
+      if (!NORM || s > s0) w[u] = *reinterpret_cast<const bf16x8 *>(wp + (s + u) * 32);
 #pragma unroll
       for (int i = 0; i < MB; ++i)
         x[u][i] = *reinterpret_cast<const bf16x8 *>(xp[i] + (s + u) * 32);
@@ -1495,11 +1568,11 @@ __device__ __forceinline__ void tile(const bf16 *__restrict__ A, const bf16 *__r
         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u], x[u][i], acc[i], 0, 0, 0);
   }
   for (; s < s1; ++s) {
-    const bf16x8 w = *reinterpret_cast<const bf16x8 *>(wp + s * 32);
+    const bf16x8 w1 = *reinterpret_cast<const bf16x8 *>(wp + s * 32);
 #pragma unroll
     for (int i = 0; i < MB; ++i)
       acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-          w, *reinterpret_cast<const bf16x8 *>(xp[i] + s * 32), acc[i], 0, 0, 0);
+          w1, *reinterpret_cast<const bf16x8 *>(xp[i] + s * 32), acc[i], 0, 0, 0);
   }
 #pragma unroll
   for (int i = 0; i < MB; ++i) part[wave][i][lane] = acc[i];
@@ -1520,12 +1593,14 @@ __device__ __forceinline__ void tile(const bf16 *__restrict__ A, const bf16 *__r
 
 }  // namespace rows16
 
-template <class Epi, int MB, bool SIDES>
+template <class Epi, int MB, bool SIDES, bool NORM>
 __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, const bf16 *W, int M,
                                                              int N, int K, Epi epi,
-                                                             HeadSides sides) {
+                                                             HeadSides sides,
+                                                             rows16::NormIn in) {
   using namespace rows16;
   __shared__ f32x4 part[kWaves][MB][64];
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   int id = blockIdx.x;
   if constexpr (SIDES) {
     const int main_tiles = N / kBN;
@@ -1534,13 +1609,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
       const int first = sides.s[0].n / kBN;
       const HeadSide j = id < first ? sides.s[0] : sides.s[1];
       const EpiPlain<bf16, false> pe{{}, static_cast<bf16 *>(j.out), j.bias, sides.ld};
-      tile<EpiPlain<bf16, false>, MB>(static_cast<const bf16 *>(j.a),
-                                      static_cast<const bf16 *>(j.w), M, K, pe,
-                                      (id < first ? id : id - first) * kBN, part);
+      tile<EpiPlain<bf16, false>, MB, false>(
+          static_cast<const bf16 *>(j.a), static_cast<const bf16 *>(j.w), M, K, pe,
+          (id < first ? id : id - first) * kBN, part, in, nullptr);
       return;
     }
   }
-  tile<Epi, MB>(A, W, M, K, epi, id * kBN, part);
+  tile<Epi, MB, NORM>(A, W, M, K, epi, id * kBN, part, in, reinterpret_cast<bf16 *>(dyn));
 }
 
 // Tile choice.  A large tile (one workgroup per CU) when 256x256 tiles fill
@@ -1596,12 +1671,16 @@ template <class Epi, bool SIDES>
 static void run_rows(const bf16 *A, const bf16 *W, int m, int n, int k, const Epi &epi,
                      const HeadSides &sides, hipStream_t s) {
   const int grid = (n + (SIDES ? sides.s[0].n + sides.s[1].n : 0)) / rows16::kBN;
+  const rows16::NormIn none{};
   if (m <= 16)
-    launch_kernel(gemm_bf16_rows_kernel<Epi, 1, SIDES>, grid, 512, 0, s, A, W, m, n, k, epi, sides);
+    launch_kernel(gemm_bf16_rows_kernel<Epi, 1, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
+                  sides, none);
   else if (m <= 32)
-    launch_kernel(gemm_bf16_rows_kernel<Epi, 2, SIDES>, grid, 512, 0, s, A, W, m, n, k, epi, sides);
+    launch_kernel(gemm_bf16_rows_kernel<Epi, 2, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
+                  sides, none);
   else
-    launch_kernel(gemm_bf16_rows_kernel<Epi, 4, SIDES>, grid, 512, 0, s, A, W, m, n, k, epi, sides);
+    launch_kernel(gemm_bf16_rows_kernel<Epi, 4, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
+                  sides, none);
 }
 
 // N a multiple of 256 and K of 64 (the host limits d_model and d_mlp to
@@ -1935,6 +2014,26 @@ hipError_t launch_head_gemm_silu(DType dt, const void *a, const void *w, const f
                    EpiPlain<float, true>{{}, static_cast<float *>(y), bias, width}, s);
   return run_head(a, w, m, width, EpiPlain<bf16, true>{{}, static_cast<bf16 *>(y), bias, width},
                   sides, s);
+}
+
+bool head_norm_fits(DType dt, int32_t m, int32_t width) {
+  return dt == DType::BF16 && m >= 1 && m <= 16 && (int64_t)m * (width + 8) <= rows16::kNormElems;
+}
+
+hipError_t launch_head_gemm_norm_silu(const float *h, const void *mod, int32_t mod_ld,
+                                      int32_t shift_off, int32_t scale_off, float eps,
+                                      const void *w, const float *bias, int32_t m, int32_t width,
+                                      void *y, const HeadSides &sides, hipStream_t s) {
+  if (!head_norm_fits(DType::BF16, m, width) || width % 256 != 0 || width > 4096 ||
+      sides.s[0].n % 16 != 0 || sides.s[1].n % 16 != 0)
+    return hipErrorInvalidValue;
+  const bf16 *W = static_cast<const bf16 *>(w), *mo = static_cast<const bf16 *>(mod);
+  const EpiPlain<bf16, true> epi{{}, static_cast<bf16 *>(y), bias, width};
+  const rows16::NormIn in{h, mo + shift_off, mo + scale_off, mod_ld, eps};
+  launch_kernel(gemm_bf16_rows_kernel<EpiPlain<bf16, true>, 1, true, true>,
+                (width + sides.s[0].n + sides.s[1].n) / rows16::kBN, 512,
+                (uint32_t)(m * (width + 8) * 2), s, nullptr, W, m, width, width, epi, sides, in);
+  return hipGetLastError();
 }
 
 hipError_t launch_head_gemm_gate(DType dt, const void *a, const void *w, const float *bias,

@@ -245,23 +245,6 @@ __global__ __launch_bounds__(256) void head_mod_kernel(T *__restrict__ a_out,
   }
 }
 
-// Sum over the wavefront, every lane (lane exchanges inside 16 lanes as DPP
-// modifiers: a shuffle through the LDS crossbar costs several times as long,
-// and the row kernel below is a chain of such sums).
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float wave_sum_dpp(float v) {
-  v = dpp_add<0xB1>(v);   // quad_perm [1,0,3,2]
-  v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
-  v = dpp_add<0x141>(v);  // row_half_mirror
-  v = dpp_add<0x140>(v);  // row_mirror: every lane of 16 holds their sum
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
-  return v;
-}
-
 // Sum over a workgroup of 256 threads; `red` holds four floats.
 __device__ __forceinline__ float block_sum(float v, float *red) {
   v = wave_sum_dpp(v);
@@ -281,29 +264,82 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
 // Its time is its chain of dependent loads and sums; as four kernels of one
 // wavefront per row (norm, output + update, input + norm, SiLU) the same work
 // took 29 us per sampling step at 512 rows of width 1280.
+// The weights of both projections do not depend on the row: where they fit
+// the registers (PRE) their loads go out first, beside those of the row.
 template <typename T, int NV, int CM>
 __global__ __launch_bounds__(256) void head_step_kernel(HeadRows p) {
   constexpr int W = NV * 256;
   constexpr float inv_w = 1.0f / W;
+  constexpr int CW = (CM + 3) / 4;               // output channels per wavefront
+  constexpr bool PRE = NV * CM <= 96;
+  constexpr int PO = PRE ? CW * NV : 1, PI = PRE ? CM / 4 * NV : 1;
   __shared__ float red[4][4];
-  __shared__ float part[4][CM];
-  __shared__ float xv[CM];
-  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ __attribute__((aligned(16))) float as[W];
+  __shared__ float ev[CM];
+  __shared__ __attribute__((aligned(16))) float xv[CM];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int C = p.c_tok;
+  // w_in rows are whole, aligned float4s
+  const bool vec_in = C == CM && (reinterpret_cast<uintptr_t>(p.w_in) & 15) == 0;
+
+  // (the row's loads before the weights': they return in order)
+  const int r = blockIdx.x;
   float *hr = p.h + (size_t)r * W;
   const T *mr = static_cast<const T *>(p.mod) + (size_t)r * p.mod_ld;
-  if (tid < CM) {
-    const float x = tid < C ? p.x_cur[(size_t)r * C + tid] : 0.f;
-    if (!p.out || tid >= C) xv[tid] = x;
+  float v[NV], fsc[NV], fsh[NV], sc0[NV], sh0[NV];
+  float xc = 0.f, nz = 0.f;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int col = tid + 256 * k;
+    if (p.out) {
+      v[k] = hr[col];
+      fsc[k] = to_f32(mr[p.scale_off + col]);
+      fsh[k] = to_f32(mr[p.shift_off + col]);
+    }
+    if (p.in && p.a) {
+      sc0[k] = to_f32(mr[W + col]);
+      sh0[k] = to_f32(mr[col]);
+    }
   }
+  if (tid < C) {
+    const size_t idx = (size_t)r * C + tid;
+    xc = p.x_cur[idx];
+    if (p.out && p.st.sigma != 0.f) nz = p.noise[idx];
+  }
+  float4 wo[PO], wi[PI];
+  float bi[NV];
+  // channel wave * CW + i of the output projection; channels past C repeat the last
+  auto w_out4 = [&](int i, int k) {
+    const int c = min(wave * CW + i, C - 1);
+    return *reinterpret_cast<const float4 *>(p.w_out + (size_t)c * W + 4 * (lane + 64 * k));
+  };
+  auto w_in4 = [&](int k, int c4) {
+    return *reinterpret_cast<const float4 *>(p.w_in + (size_t)(tid + 256 * k) * CM + 4 * c4);
+  };
+  if constexpr (PRE) {
+    if (p.out) {
+#pragma unroll
+      for (int i = 0; i < CW; ++i)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) wo[i * NV + k] = w_out4(i, k);
+    }
+    if (p.in && vec_in) {
+#pragma unroll
+      for (int k = 0; k < NV; ++k)
+#pragma unroll
+        for (int c4 = 0; c4 < CM / 4; ++c4) wi[k * (CM / 4) + c4] = w_in4(k, c4);
+    }
+  }
+  if (p.in) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) bi[k] = p.b_in[tid + 256 * k];
+  }
+  const float bo = p.out && tid < C ? p.b_out[tid] : 0.f;
+  if (tid < CM) xv[tid] = xc;  // channels past C hold 0
   if (p.out) {
-    float v[NV];
     float s = 0.f;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      v[k] = hr[tid + 256 * k];
-      s += v[k];
-    }
+    for (int k = 0; k < NV; ++k) s += v[k];
     const float mean = block_sum(s, red[0]) * inv_w;
     float ss = 0.f;
 #pragma unroll
@@ -312,32 +348,35 @@ __global__ __launch_bounds__(256) void head_step_kernel(HeadRows p) {
       ss += v[k] * v[k];
     }
     const float rstd = 1.0f / sqrtf(block_sum(ss, red[1]) * inv_w + p.eps);
-    float acc[CM];
 #pragma unroll
-    for (int c = 0; c < CM; ++c) acc[c] = 0.f;
+    for (int k = 0; k < NV; ++k) as[tid + 256 * k] = v[k] * rstd * (1.f + fsc[k]) + fsh[k];
+    __syncthreads();
+    float acc[CW];
+#pragma unroll
+    for (int i = 0; i < CW; ++i) acc[i] = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      const int col = tid + 256 * k;
-      const float a =
-          v[k] * rstd * (1.f + to_f32(mr[p.scale_off + col])) + to_f32(mr[p.shift_off + col]);
+      const float4 a = *reinterpret_cast<const float4 *>(as + 4 * (lane + 64 * k));
 #pragma unroll
-      for (int c = 0; c < CM; ++c)  // rows past C repeat the last one
-        acc[c] = fmaf(a, p.w_out[(size_t)min(c, C - 1) * W + col], acc[c]);
+      for (int i = 0; i < CW; ++i) {
+        float4 w;
+        if constexpr (PRE) w = wo[i * NV + k];
+        else w = w_out4(i, k);
+        acc[i] = fmaf(a.x, w.x, fmaf(a.y, w.y, fmaf(a.z, w.z, fmaf(a.w, w.w, acc[i]))));
+      }
     }
 #pragma unroll
-    for (int c = 0; c < CM; ++c) {
-      const float t = wave_sum_dpp(acc[c]);
-      if (lane == 0) part[wave][c] = t;
+    for (int i = 0; i < CW; ++i) {
+      const float t = wave_sum_dpp(acc[i]);
+      if (lane == 0 && wave * CW + i < CM) ev[wave * CW + i] = t;
     }
     __syncthreads();
     if (tid < C) {
       const size_t idx = (size_t)r * C + tid;
-      const float xc = p.x_cur[idx];
-      const float eps_v =
-          (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]) + p.b_out[tid];
+      const float eps_v = ev[tid] + bo;
       const float x0 = p.st.sra * xc - p.st.srm1 * eps_v;
       float xn = p.st.c1 * x0 + p.st.c2 * xc;
-      if (p.st.sigma != 0.f) xn = fmaf(p.st.sigma, p.noise[idx], xn);
+      if (p.st.sigma != 0.f) xn = fmaf(p.st.sigma, nz, xn);
       p.x_next[idx] = xn;
       if (p.tok_out) p.tok_out[(size_t)p.out_rows[r] * C + tid] = xn;
       xv[tid] = xn;
@@ -345,32 +384,44 @@ __global__ __launch_bounds__(256) void head_step_kernel(HeadRows p) {
   }
   if (p.in) {
     __syncthreads();
-    float v[NV];
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int col = tid + 256 * k;
-      float h = p.b_in[col];
+      float h = bi[k];
+      if (vec_in) {
 #pragma unroll
-      for (int c = 0; c < CM; ++c)  // channels past C hold 0
-        h = fmaf(p.w_in_t[(size_t)min(c, C - 1) * W + col], xv[c], h);
+        for (int c4 = 0; c4 < CM / 4; ++c4) {
+          const float4 x = *reinterpret_cast<const float4 *>(xv + 4 * c4);
+          float4 w;
+          if constexpr (PRE) w = wi[k * (CM / 4) + c4];
+          else w = w_in4(k, c4);
+          h = fmaf(w.x, x.x, h);
+          h = fmaf(w.y, x.y, h);
+          h = fmaf(w.z, x.z, h);
+          h = fmaf(w.w, x.w, h);
+        }
+      } else {
+#pragma unroll 8
+        for (int c = 0; c < C; ++c) h = fmaf(p.w_in_t[(size_t)c * W + col], xv[c], h);
+      }
       hr[col] = h;
       v[k] = h;
       s += h;
     }
-    const float mean = block_sum(s, red[2]) * inv_w;
-    float ss = 0.f;
+    if (p.a) {
+      const float mean = block_sum(s, red[2]) * inv_w;
+      float ss = 0.f;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      v[k] -= mean;
-      ss += v[k] * v[k];
-    }
-    const float rstd = 1.0f / sqrtf(block_sum(ss, red[3]) * inv_w + p.eps);
-    T *ar = static_cast<T *>(p.a) + (size_t)r * W;
+      for (int k = 0; k < NV; ++k) {
+        v[k] -= mean;
+        ss += v[k] * v[k];
+      }
+      const float rstd = 1.0f / sqrtf(block_sum(ss, red[3]) * inv_w + p.eps);
+      T *ar = static_cast<T *>(p.a) + (size_t)r * W;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int col = tid + 256 * k;
-      ar[col] = from_f32<T>(v[k] * rstd * (1.f + to_f32(mr[W + col])) + to_f32(mr[col]));
+      for (int k = 0; k < NV; ++k)
+        ar[tid + 256 * k] = from_f32<T>(v[k] * rstd * (1.f + sc0[k]) + sh0[k]);
     }
   }
   if (p.sc) {

@@ -931,7 +931,8 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
   // step i + 1's row kernel (which applies chunk 0) and chunk nb one after it.
   // So SiLU(condition + time embedding) is held for two steps; the second
   // buffer takes the place of the block outputs, which the gated residual in
-  // the second product's epilogue never stores.
+  // the second product's epilogue never stores.  With few rows (norm_in) a
+  // block's first product forms its modulated norm itself.
   void *scs[2] = {sc, tbuf};
   const int tw = W / 128;                     // 128-column tiles of a width
   const int side_fit = head_side_tiles(dt, M, W);
@@ -955,13 +956,15 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
   };
   HeadRows hr{};
   hr.h = hbuf;
-  hr.a = abuf;
+  const bool norm_in = head_norm_fits(dt, M, W);
+  hr.a = norm_in ? nullptr : abuf;
   hr.mod = mod;
   hr.mod_ld = ML;
   hr.shift_off = 3 * nb * W;
   hr.scale_off = hr.shift_off + W;
   hr.w_out = fp(w->w_out);
   hr.b_out = fp(w->b_out);
+  hr.w_in = fp(w->w_in);
   hr.w_in_t = w_in_t;
   hr.b_in = fp(w->b_in);
   hr.x_next = xs;
@@ -1005,14 +1008,17 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
       }
       LAUNCH(gemm_class(K_GEMM_HEAD_SILU, dt, M, W, W), 2.0 * M * (W + side_n[0]) * W,
              es * (2.0 * M * W + (double)W * W + side_n[0] * (W + M)),
-             launch_head_gemm_silu(dt, abuf, w1, fp(w->b_1) + (size_t)k * W, M, W, ybuf, sides[0],
-                                   stream));
+             norm_in ? launch_head_gemm_norm_silu(hbuf, mod, ML, 3 * k * W, (3 * k + 1) * W,
+                                                  hd->ln_eps, w1, fp(w->b_1) + (size_t)k * W, M, W,
+                                                  ybuf, sides[0], stream)
+                     : launch_head_gemm_silu(dt, abuf, w1, fp(w->b_1) + (size_t)k * W, M, W, ybuf,
+                                             sides[0], stream));
       LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, W, W), 2.0 * M * (W + side_n[1]) * W,
              es * (2.0 * M * W + (double)W * W + side_n[1] * (W + M)) + 8.0 * M * W,
              launch_head_gemm_gate(dt, ybuf, w2, fp(w->b_2) + (size_t)k * W, M, W, hbuf,
                                    static_cast<const char *>(mod) + (size_t)(3 * k + 2) * W * es,
                                    ML, sides[1], stream));
-      if (k + 1 < nb) {
+      if (k + 1 < nb && !norm_in) {
         const int nxt = 3 * (k + 1) * W;
         LAUNCH(K_HEAD_MOD, 0, 4.0 * M * W + es * 3.0 * M * W,
                launch_head_mod(dt, abuf, hbuf, mod, ML, nxt, nxt + W, M, W, hd->ln_eps, stream));

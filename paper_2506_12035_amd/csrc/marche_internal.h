@@ -88,7 +88,8 @@ struct HeadStep {
 // Everything between two sampling steps' blocks, row by row (see
 // head_step_kernel).  `out`: this step's output projection and DDPM update
 // (final modulation at shift_off, scale_off); `in`: the next step's input
-// projection and first modulated norm (slices 0 and width of mod); sc != NULL:
+// projection and first modulated norm (slices 0 and width of mod; a == NULL:
+// without the norm, which the next launch forms itself); sc != NULL:
 // SiLU(cond + temb) into it.
 struct HeadRows {
   bool out, in;
@@ -97,7 +98,8 @@ struct HeadRows {
   const void *mod;
   int32_t mod_ld, shift_off, scale_off;
   const float *w_out, *b_out;    // [C][W], [C]
-  const float *w_in_t, *b_in;    // [C][W], [W]
+  const float *w_in, *w_in_t;    // [W][C] and its transpose
+  const float *b_in;             // [W]
   const float *x_cur, *noise;    // [rows][C]
   float *x_next, *tok_out;       // tok_out: last step only
   const int32_t *out_rows;
@@ -155,6 +157,13 @@ int head_side_tiles(DType dt, int32_t m, int32_t width);
 hipError_t launch_head_gemm_silu(DType dt, const void *a, const void *w, const float *bias,
                                  int32_t m, int32_t width, void *y, const HeadSides &sides,
                                  hipStream_t s);
+// The first with its activations a = LN(h) (1 + scale) + shift formed in the
+// same launch (bf16, where head_norm_fits: up to 16 rows).
+bool head_norm_fits(DType dt, int32_t m, int32_t width);
+hipError_t launch_head_gemm_norm_silu(const float *h, const void *mod, int32_t mod_ld,
+                                      int32_t shift_off, int32_t scale_off, float eps,
+                                      const void *w, const float *bias, int32_t m, int32_t width,
+                                      void *y, const HeadSides &sides, hipStream_t s);
 hipError_t launch_head_gemm_gate(DType dt, const void *a, const void *w, const float *bias,
                                  int32_t m, int32_t width, float *h, const void *gate,
                                  int32_t mod_ld, const HeadSides &sides, hipStream_t s);

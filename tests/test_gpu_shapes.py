@@ -113,12 +113,15 @@ def test_segment_shapes(case):
 
 
 # (rows, width, blocks, sampling steps, channels, dtype): the few-row kernel with
-# 16, 32 and 64 rows, the 64x128 tile with a ragged last tile, row counts whose
+# 16, 32 and 64 rows (up to 16, as far as they fit, norming their own
+# activations), the 64x128 tile with a ragged last tile, row counts whose
 # modulations no longer fit beside the block products, one block (no
 # side products) and two, one to three sampling steps, other channel counts.
 SAMPLER = [
     (1, 256, 2, 3, 16, "bf16"),
     (16, 512, 3, 2, 16, "bf16"),
+    (9, 1536, 1, 2, 8, "bf16"),
+    (16, 2048, 2, 2, 16, "bf16"),
     (17, 256, 1, 3, 5, "bf16"),
     (33, 768, 2, 1, 16, "bf16"),
     (64, 256, 5, 3, 33, "bf16"),
