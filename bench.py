@@ -105,11 +105,12 @@ def traffic_for(kernel: str, workload: str):
 def counter_class(name: str):
     """Timing class of a kernel symbol as rocprofv3 prints it (mangled or not),
     before the split into full and cache-aware layers."""
+    mid = re.search(r"gemm_bf16_mid_kernel.*?(?:, |ELi)(\d)(?:, |ELi)\d(?:>|EEEv)", name)
     tile = ("t256" if ("gemm_bf16_big_kernel" in name or "gemm_bf16_big8_kernel" in name) else
             "t320" if "gemm_bf16_t320_kernel" in name else
             "t64x128" if "gemm_bf16_small_kernel" in name else
             "rows" if "gemm_bf16_rows_kernel" in name else
-            "t128" if "gemm_bf16_mid_kernel" in name else "t128x256")
+            {"2": "t128", "3": "t192x128", "4": "t256x128"}[mid.group(1)] if mid else "")
     if "gemm_bf16" in name:
         for key, cls in (("EpiResidILi1E", "fc2"), ("EpiResid<1>", "fc2"), ("EpiResidILi0E", "o"),
                          ("EpiResid<0>", "o"), ("EpiGelu", "fc1"), ("EpiQkv", "qkv")):

@@ -9,13 +9,13 @@
 //   - adds into the float32 residual stream row     (output projection, fc2)
 //   - applies exact GELU and stores the hidden row  (fc1)
 //
-// bf16 path (v_mfma_f32_32x32x16_bf16, fp32 accumulators): a 256x256 tile
-// (one workgroup per CU; four wavefronts for K >= 2048, eight below) or a
-// 320x256 tile (whole 320-token images per tile row, eight wavefronts) for
-// shapes that fill the chip in whole waves, else a 128x256 tile of which two
-// workgroups share a CU, or 128x128 / 64x128 tiles for narrow products.  All
-// load operands straight from global memory into XOR-swizzled LDS stages and
-// write back through LDS in row-major order.
+// bf16 path (v_mfma_f32_32x32x16_bf16, fp32 accumulators), one workgroup per
+// CU: a 256x256 tile (four wavefronts for K >= 2048, eight below) or a 320x256
+// tile (whole 320-token images per tile row, eight wavefronts) for shapes that
+// fill the chip in whole waves, else 256, 192, 128 or 64 rows x 128 columns.
+// All load operands straight from global memory into XOR-swizzled LDS stages
+// and write back through LDS in row-major order.  The sampler's products on up
+// to 64 rows have a kernel of their own.
 //
 // fp32 path: fp32 matrix instructions, a 64x64 tile or, for few rows, a
 // workgroup per 16 columns whose wavefronts split K.
@@ -920,357 +920,194 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_t320_kernel(const bf16 *A, c
                              reinterpret_cast<const typename Epi::Row *>(side + 1024) + wm * 160, b);
 }
 
-// ------------------------------------------------------------------ 128x256 tile, two per CU
+// ------------------------------------------------------------------ 64 TM x 128 tiles
 //
-// A 128x256x32 workgroup tile on four wavefronts of 64x128 (8 accumulators,
-// 128 registers), budgeted so that two workgroups share a CU: while one
-// writes its tile back (bias, GELU, residual read-modify-write, KV-cache
-// scatter) the other keeps the matrix cores busy.  Three 24 KB stages of
-// 64-byte rows (16-byte chunks permuted by an XOR with bits 2..3 of the row,
-// so the 16 rows one fragment read touches per chunk hit 16 distinct bank
-// groups), loaded straight from global memory; the loads of k-tile t+3 go out
-// as soon as every wavefront is done with k-tile t, two k-tiles ahead of use.
-namespace pair {
-
-constexpr int kBM = 128, kBN = 256, kBK = 32;
-constexpr int kWOff = kBM * kBK * 2;             // weight rows start 8 KB into a stage
-constexpr int kStage = (kBM + kBN) * kBK * 2;    // 24 KB
-constexpr int kLoads = kStage / 1024 / 4;        // load instructions per wavefront per k-tile
-static_assert(kLoads == 6, "load schedule assumes six loads per wavefront");
-
-__device__ __forceinline__ int swz(int r, int c) { return c ^ ((r >> 2) & 3); }
-
-struct Frag {
-  bf16x8 x[2];  // activation rows (MFMA B operand)
-  bf16x8 w[4];  // weight rows (MFMA A operand)
-};
-
-// Load instruction q (0..23 per k-tile) moves 1 KB: q < 8 carries activation
-// rows 16q..16q+15, q >= 8 weight rows 16(q-8)..; lane l writes LDS bytes
-// [16 l, 16 l + 16) of the block: row 16 q' + l / 4 at physical chunk l % 4.
-__device__ __forceinline__ void load_lds(unsigned stage, int q, const bf16 *A, const bf16 *W,
-                                         int M, int K, int m0, int n0, int k0, int lane) {
-  const int rr = lane >> 2, pc = lane & 3;
-  const bf16 *g;
-  if (q < 8) {
-    const int r = q * 16 + rr;
-    g = A + (size_t)min(m0 + r, M - 1) * K + k0 + swz(r, pc) * 8;
-  } else {
-    const int r = (q - 8) * 16 + rr;
-    g = W + (size_t)(n0 + r) * K + k0 + swz(r, pc) * 8;
-  }
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(g), "s"(__builtin_amdgcn_readfirstlane(stage + q * 1024))
-               : "memory", "m0");
-}
-
-// Fragment r of k16 step s (0 or 1), in the order the MFMAs need them: x0 w0 x1 w1 w2 w3.
-__device__ __forceinline__ void read_frag(Frag &f, int r, const unsigned char *stage, int s, int wm,
-                                          int wn, int lane) {
-  const int c = 2 * s + (lane >> 5);
-  if (r == 0 || r == 2) {
-    const int row = wm * 64 + (r >> 1) * 32 + (lane & 31);
-    f.x[r >> 1] = *reinterpret_cast<const bf16x8 *>(stage + row * 64 + swz(row, c) * 16);
-  } else {
-    const int j = r == 1 ? 0 : r - 2;
-    const int row = wn * 128 + j * 32 + (lane & 31);
-    f.w[j] = *reinterpret_cast<const bf16x8 *>(stage + kWOff + row * 64 + swz(row, c) * 16);
-  }
-}
-
-__device__ __forceinline__ void mfma(f32x16 (&acc)[4][2], const Frag &f, int q) {
-  const int j = q >> 1, i = q & 1;
-  acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[j], f.x[i], acc[j][i], 0, 0, 0);
-}
-
-// Wait until at most VM of this wavefront's loads are in flight and its LDS
-// reads are done, then the workgroup barrier.
-template <int VM>
-__device__ __forceinline__ void barrier_vm() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
-}
-
-// The same with the loads of n whole k-tiles (six per wavefront each) still
-// in flight, n in [0, NS - 2].
-template <int NS>
-__device__ __forceinline__ void barrier_tiles(int n) {
-  static_assert(NS >= 3 && NS <= 7, "stage count");
-  if (NS > 6 && n >= 5) barrier_vm<30>();
-  else if (NS > 5 && n >= 4) barrier_vm<24>();
-  else if (NS > 4 && n >= 3) barrier_vm<18>();
-  else if (NS > 3 && n >= 2) barrier_vm<12>();
-  else if (n >= 1) barrier_vm<6>();
-  else barrier_vm<0>();
-}
-
-}  // namespace pair
-
-// NS stages of 24 KB: three when two workgroups share a CU; six for long
-// reductions (K >= 2048) whose workgroups each have a CU to themselves, so
-// that operands streamed from HBM (a cache-aware fc2's hidden rows, a
-// layer's weights not touched since the previous step) have five k-tiles to
-// land instead of two (measured: 82 -> 78 us for a cache-aware MAR-L fc2 with
-// operands not in any cache; short reductions gain nothing).  The loads of
-// k-tile t+NS go into the stage k-tile t leaves, issued once every wavefront
-// is done with k-tile t.
-template <class Epi, int NS>
-__global__ __launch_bounds__(256, NS <= 3 ? 2 : 1) void gemm_bf16_pair_kernel(
-    const bf16 *A, const bf16 *W, int M, int N, int K, Epi epi) {
-  using namespace pair;
-  using big::pin;
-  using Row = typename Epi::Row;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * kStage];
-  __shared__ __attribute__((aligned(16))) Row rows_lds[kBM];
-  static_assert(4 * 32 * big::kWbStride * 4 <= NS * kStage, "staged write-back fits the stages");
-  const int tiles_m = (M + kBM - 1) / kBM, tiles_n = N / kBN;
-  int tm, tn;
-  tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * kBM, n0 = tn * kBN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int q0 = wave * kLoads;
-  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
-  f32x16 acc[4][2];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) acc[j][i] = f32x16{};
-  const int nk = K / kBK;
-  auto stage = [&](int kt) { return lds0 + (unsigned)(kt % NS) * kStage; };
-
-  // The write-back's row record (threads < 128) and bias (each lane's four
-  // columns), loaded before the tile loads and kept in registers: they reach
-  // LDS only after the main loop, so no wait on them holds up the pipeline.
-  Row rec{};
-  if (tid < kBM) rec = epi.row(min(m0 + tid, M - 1));
-  const f32x4 bias = epi.bias4(n0 + wn * 128 + (lane & 31) * 4);
-
-  // k-tiles 0 .. NS-2 and the first half of k-tile NS-1, then wait for k-tile 0
-#pragma unroll
-  for (int kt = 0; kt + 1 < NS; ++kt) {
-    if (kt < nk) {
-#pragma unroll
-      for (int p = 0; p < kLoads; ++p)
-        load_lds(lds0 + kt * kStage, q0 + p, A, W, M, K, m0, n0, kt * kBK, lane);
-    }
-  }
-  if (nk >= NS) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      load_lds(lds0 + (NS - 1) * kStage, q0 + p, A, W, M, K, m0, n0, (NS - 1) * kBK, lane);
-    barrier_vm<6 * (NS - 2) + 3>();
-  } else {
-    barrier_tiles<NS>(nk - 1);
-  }
-  Frag fa, fb;
-  const unsigned char *smem_u = smem;
-#pragma unroll
-  for (int r = 0; r < 6; ++r) read_frag(fa, r, smem_u, 0, wm, wn, lane);
-
-  for (int t = 0; t + 1 < nk; ++t) {
-    // k-tile t+NS-1: its first half is in flight, the rest goes out now;
-    // k-tile t+NS: into k-tile t's stage once every wavefront is done with it
-    const int kl = t + NS - 1, kn = t + NS;
-    const bool has_l = kl < nk, has_n = kn < nk;
-    const unsigned sl = stage(kl), s_t = stage(t);
-    const unsigned char *sc = smem_u + (s_t - lds0), *sn = smem_u + (stage(t + 1) - lds0);
-    // k16 step 0: step-1 fragments; loads 3 and 4 of k-tile t+NS-1
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      mfma(acc, fa, q);
-      if (q < 6) read_frag(fb, q, sc, 1, wm, wn, lane);
-      else if (has_l) load_lds(sl, q0 + 3 + (q - 6), A, W, M, K, m0, n0, kl * kBK, lane);
-      pin();
-    }
-    // k16 step 1: load 5 of k-tile t+NS-1; barrier (k-tile t+1 complete,
-    // k-tile t read by all); step-0 fragments of k-tile t+1; first half of
-    // k-tile t+NS into the stage k-tile t leaves
-    mfma(acc, fb, 0);
-    if (has_l) load_lds(sl, q0 + 5, A, W, M, K, m0, n0, kl * kBK, lane);
-    pin();
-    mfma(acc, fb, 1);
-    pin();
-    barrier_tiles<NS>(min(NS - 2, nk - t - 2));
-    pin();
-#pragma unroll
-    for (int q = 2; q < 8; ++q) {
-      mfma(acc, fb, q);
-      read_frag(fa, q - 2, sn, 0, wm, wn, lane);
-      if (q >= 5 && has_n) load_lds(s_t, q0 + (q - 5), A, W, M, K, m0, n0, kn * kBK, lane);
-      pin();
-    }
-  }
-  {  // last k-tile
-    const unsigned char *sc = smem_u + (stage(nk - 1) - lds0);
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      mfma(acc, fa, q);
-      if (q < 6) read_frag(fb, q, sc, 1, wm, wn, lane);
-      pin();
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      mfma(acc, fb, q);
-      pin();
-    }
-  }
-  if (tid < kBM) rows_lds[tid] = rec;
-  // every wavefront is done with the stages before they hold the write-back's
-  // staging rows, and the row records are in LDS
-  barrier_vm<0>();
-  write_back_staged<4, 2, 8>(acc, epi, m0 + wm * 64, n0 + wn * 128, M, lane,
-                          reinterpret_cast<float *>(smem) + wave * 32 * big::kWbStride,
-                          rows_lds + wm * 64, bias);
-}
-
-// ------------------------------------------------------------------ 128x128 tile
-//
-// For the narrow products of cache-aware layers (N = d_model: the output
-// projection and fc2 on a few thousand active rows), where 256x256 tiles
-// would occupy a few dozen compute units and the 64x128 tile moves more
-// operand bytes per k-tile than its MFMAs take cycles (so it waits on the
-// L2).  A 128x128x64 tile on four wavefronts of 64x64 (4 accumulator blocks)
-// keeps one 64-row MFMA block per operand fragment and about as many load
-// cycles per k-tile as MFMA cycles.  Operand stages use the 256x256 tile's
-// 128-byte rows, XOR swizzle and direct-to-LDS loads (big::load_lds): NS
-// stages of 32 KB, the loads of k-tile t + NS - 1 issued once every
-// wavefront is done with k-tile t - 1, so NS - 1 k-tiles are in flight.
+// For products that leave 256x256 tiles a partial wave (the narrow products of
+// cache-aware layers, N = d_model on a few thousand active rows; every product
+// of a small batch): tiles of 64 TM x 128 x 64 on four wavefronts of 32 TM x 64
+// (2 TM accumulator blocks), one workgroup per CU.  Operand stages use the
+// 256x256 tile's 128-byte rows, XOR swizzle and direct-to-LDS loads with a
+// scalar base.  Alone, the loads of a 128x128 tile take 0.65 and its fragment
+// reads and MFMAs 0.7 of the time that a loop issuing them in bursts took, so
+// the loop spreads all three: beside each MFMA at most one or two memory
+// operations, fragments read two k16 steps before use (four register sets),
+// a k-tile's loads over the whole of the k-tile before, and one barrier per
+// k-tile that waits for the next k-tile's loads only (the stage it frees was
+// read a k-tile earlier).
 // No split of K: every output is one accumulation over all of K in
 // ascending k16 steps, as in every other tile, so the result does not depend
 // on which tile a shape gets.
 namespace mid {
 
-constexpr int kBM = 128, kBN = 128, kBK = 64;
-constexpr int kStage = (kBM + kBN) * kBK * 2;  // 32 KB: activation rows, then weight rows
-constexpr int kWOff = kBM * kBK * 2;           // weight rows 16 KB into a stage
+constexpr int kBN = 128, kBK = 64;
 
-struct Frag {
-  bf16x8 x[2];  // activation rows (MFMA B operand)
-  bf16x8 w[2];  // weight rows (MFMA A operand)
+template <int TM>
+struct Shape {
+  static constexpr int kBM = 64 * TM;
+  static constexpr int kWOff = kBM * kBK * 2;              // weight rows after the activation rows
+  static constexpr int kStage = (kBM + kBN) * kBK * 2;
+  static constexpr int kALoads = 2 * TM, kLoads = kALoads + 4;  // 1 KB each, per wavefront
 };
 
-// Fragments of k16 step s (0..3) of a stage for wavefront (wm, wn).
-__device__ __forceinline__ void read_frags(Frag &f, const unsigned char *stage, int s, int wm,
-                                           int wn, int lane) {
+template <int TM>
+struct Frag {
+  bf16x8 x[TM];  // activation rows (MFMA B operand)
+  bf16x8 w[2];   // weight rows (MFMA A operand)
+};
+
+// Fragment r of k16 step s of a stage, in the order the MFMAs need them: w0,
+// x0 .. x(TM-1), w1.
+template <int TM>
+__device__ __forceinline__ void read_frag(Frag<TM> &f, int r, const unsigned char *stage, int s,
+                                          int wm, int wn, int lane) {
   const int kc = s * 2 + (lane >> 5);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = wm * 64 + i * 32 + (lane & 31);
-    f.x[i] = *reinterpret_cast<const bf16x8 *>(stage + row * 128 + big::swz(row, kc) * 16);
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  if (r == 0 || r == TM + 1) {
+    const int j = r == 0 ? 0 : 1;
     const int row = wn * 64 + j * 32 + (lane & 31);
-    f.w[j] = *reinterpret_cast<const bf16x8 *>(stage + kWOff + row * 128 + big::swz(row, kc) * 16);
+    f.w[j] = *reinterpret_cast<const bf16x8 *>(stage + Shape<TM>::kWOff + row * 128 +
+                                               big::swz(row, kc) * 16);
+  } else {
+    const int row = wm * 32 * TM + (r - 1) * 32 + (lane & 31);
+    f.x[r - 1] = *reinterpret_cast<const bf16x8 *>(stage + row * 128 + big::swz(row, kc) * 16);
   }
 }
 
-__device__ __forceinline__ void mfma(f32x16 (&acc)[2][2], const Frag &f) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.w[j], f.x[i], acc[j][i], 0, 0, 0);
+// At most n (<= NMAX) of this wavefront's k-tiles of L loads in flight, then
+// the workgroup barrier.
+template <int L, int NMAX>
+__device__ __forceinline__ void barrier_tiles(int n) {
+  if constexpr (NMAX > 0) {
+    if (n < NMAX) {
+      barrier_tiles<L, NMAX - 1>(n);
+      return;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(L * NMAX) : "memory");
 }
 
 }  // namespace mid
 
-// Wait until at most n whole k-tiles (8 loads per wavefront each) of this
-// wavefront's loads are in flight and its LDS reads are done, then the
-// workgroup barrier; n in [0, 3].
-__device__ __forceinline__ void mid_barrier(int n) {
-  if (n >= 3) pair::barrier_vm<24>();
-  else if (n == 2) pair::barrier_vm<16>();
-  else if (n == 1) pair::barrier_vm<8>();
-  else pair::barrier_vm<0>();
-}
-
-template <class Epi, int NS>
+template <class Epi, int TM, int NS>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_mid_kernel(const bf16 *A, const bf16 *W, int M,
                                                                int N, int K, Epi epi) {
   using namespace mid;
   using big::pin;
   using Row = typename Epi::Row;
-  static_assert(NS >= 3 && NS <= 5, "stage count (the staged write-back needs 3 stages)");
-  // NS stages of 32 KB; after the main loop the write-back stages its rows in
-  // [0, 66 KB) and the tile's row records sit at 96 KB (in the fourth stage,
-  // or the third's second half)
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * kStage];
-  constexpr int kRowsOff = 96 * 1024 - (NS == 3 ? 16 * 1024 : 0);
-  static_assert(4 * 32 * big::kWbStride * 4 <= kRowsOff, "staged write-back below the row records");
-  static_assert(kRowsOff + kBM * sizeof(Row) <= NS * kStage, "row records fit the stages");
-  const int tiles_m = (M + kBM - 1) / kBM, tiles_n = N / kBN;
+  using S = Shape<TM>;
+  static_assert(NS >= 3 && S::kLoads * (NS - 1) <= 63, "stages; vmcnt holds 63");
+  // after the main loop the write-back stages 4 x 32 rows of 68 floats and
+  // keeps the tile's row records behind them
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * S::kStage];
+  constexpr int kRowsOff = 4 * 32 * 68 * 4;
+  static_assert(kRowsOff + S::kBM * sizeof(Row) <= NS * S::kStage, "row records fit the stages");
+  const int tiles_m = (M + S::kBM - 1) / S::kBM, tiles_n = N / kBN;
   int tm, tn;
   tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * kBM, n0 = tn * kBN;
+  const int m0 = tm * S::kBM, n0 = tn * kBN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
   const unsigned char *smem_u = smem;
-  f32x16 acc[2][2];
+  f32x16 acc[2][TM];
 #pragma unroll
   for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) acc[j][i] = f32x16{};
+    for (int i = 0; i < TM; ++i) acc[j][i] = f32x16{};
   const int nk = K / kBK;
-  // k-tile t into stage st: 16 load instructions of 1 KB (8 rows) per operand,
-  // four of each per wavefront
-  auto load_tile = [&](int st, int t) {
-    const unsigned sb = lds0 + (unsigned)st * kStage;
+  // Load p of every k-tile: p < kALoads moves activation rows 8 q .. 8 q + 7
+  // (q = kALoads wave + p), the rest weight rows; lane l writes row 8 q + l / 8
+  // at physical chunk l % 8, which holds logical chunk swz(row, l % 8).
+  // Activation rows past M repeat row M - 1 (their results are never stored).
+  uint32_t off[S::kLoads];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      big::load_lds(sb, wave * 4 + p, A, M, K, m0, t * kBK, lane);
-      big::load_lds(sb + kWOff, wave * 4 + p, W, N, K, n0, t * kBK, lane);
-    }
+  for (int p = 0; p < S::kLoads; ++p) {
+    const bool is_a = p < S::kALoads;
+    const int q = is_a ? wave * S::kALoads + p : wave * 4 + (p - S::kALoads);
+    const int r = q * 8 + (lane >> 3);
+    const int row = is_a ? min(m0 + r, M - 1) : n0 + r;
+    off[p] = ((uint32_t)row * (uint32_t)K + (uint32_t)(big::swz(r, lane & 7) * 8)) * 2u;
+  }
+  auto load = [&](int st, int t, int p) {
+    const unsigned sb = lds0 + (unsigned)st * S::kStage;
+    if (p < S::kALoads)
+      t320::load_lds(sb + (wave * S::kALoads + p) * 1024, A + t * kBK, off[p]);
+    else
+      t320::load_lds(sb + S::kWOff + (wave * 4 + p - S::kALoads) * 1024, W + t * kBK, off[p]);
   };
 
-  // the write-back's row record (threads < 128) and this lane's bias, kept in
-  // registers until after the main loop
-  Row rec{};
-  if (tid < kBM) rec = epi.row(min(m0 + tid, M - 1));
+  // the write-back's row record and this lane's bias, kept in registers until
+  // after the main loop
+  Row rec[(S::kBM + 255) / 256];
+#pragma unroll
+  for (int u = 0; u < (S::kBM + 255) / 256; ++u)
+    rec[u] = epi.row(min(m0 + min(tid + 256 * u, S::kBM - 1), M - 1));
   const f32x4 bias = epi.bias4(n0 + wn * 64 + (lane & 15) * 4);
 
   // k-tiles 0 .. NS-2 in flight, then wait for k-tile 0
-  const int issued = min(NS - 1, nk);
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t)
-    if (t < nk) load_tile(t, t);
-  mid_barrier(issued - 1);
-  Frag f[2];
-  read_frags(f[0], smem_u, 0, wm, wn, lane);
-
-  for (int t = 0; t < nk; ++t) {
-    const unsigned char *sc = smem_u + (t % NS) * kStage;
+    if (t < nk) {
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      read_frags(f[(s + 1) & 1], sc, s + 1, wm, wn, lane);
-      mfma(acc, f[s & 1]);
-      pin();
+      for (int p = 0; p < S::kLoads; ++p) load(t, t, p);
     }
-    if (t + 1 < nk) {
-      // k-tile t+1 landed and every wavefront is done with k-tile t-1's
-      // stage.  Issued so far: k-tiles up to t + NS - 2, so the ones after
-      // t + 1 that may stay in flight number min(NS - 3, nk - t - 2)
-      mid_barrier(min(NS - 3, nk - t - 2));
-      read_frags(f[0], smem_u + ((t + 1) % NS) * kStage, 0, wm, wn, lane);
-      // k-tile t+NS-1 into the stage k-tile t-1 used (free: the barrier above)
-      if (t + NS - 1 < nk) load_tile((t + NS - 1) % NS, t + NS - 1);
+  barrier_tiles<S::kLoads, NS - 2>(min(NS - 1, nk) - 1);
+  Frag<TM> f[4];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int r = 0; r < TM + 2; ++r) read_frag<TM>(f[s], r, smem_u, s, wm, wn, lane);
+
+  constexpr int MF = 2 * TM;  // MFMAs per k16 step
+  int cur = 0, nxt = NS > 1 ? 1 : 0, prv = NS - 1;  // stages of k-tiles t, t + 1, t - 1
+  for (int t = 0; t < nk; ++t) {
+    const unsigned char *sc = smem_u + cur * S::kStage, *sn = smem_u + nxt * S::kStage;
+    const bool more = t + 1 < nk, ld = t + NS - 1 < nk;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      // k-tile t+1 landed (issued so far: up to k-tile t + NS - 2, and the
+      // first half of t + NS - 1's loads) before its fragments are read
+      if (s == 2 && more) {
+        // loads outstanding after k-tile t+1: those of t + 2 .. t + NS - 2
+        barrier_tiles<S::kLoads, NS - 3>(min(NS - 3, nk - 2 - t));
+        pin();
+      }
+#pragma unroll
+      for (int q = 0; q < MF; ++q) {
+        const int j = q / TM, i = q % TM;
+        acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s].w[j], f[s].x[i], acc[j][i], 0, 0, 0);
+        // fragments of two steps on, TM + 2 over the step's MFMAs
+#pragma unroll
+        for (int r = q * (TM + 2) / MF; r < (q + 1) * (TM + 2) / MF; ++r) {
+          if (s < 2) read_frag<TM>(f[s + 2], r, sc, s + 2, wm, wn, lane);
+          else if (more) read_frag<TM>(f[s - 2], r, sn, s - 2, wm, wn, lane);
+        }
+        // k-tile t + NS - 1 into the stage of k-tile t - 1, which every
+        // wavefront has read before the barrier: steps 2 and 3
+        if (s >= 2 && ld) {
+          const int u = (s - 2) * MF + q;
+#pragma unroll
+          for (int p = u * S::kLoads / (2 * MF); p < (u + 1) * S::kLoads / (2 * MF); ++p)
+            load(prv, t + NS - 1, p);
+        }
+        pin();
+      }
     }
-    mfma(acc, f[1]);
-    pin();
+    prv = cur;
+    cur = nxt;
+    nxt = nxt + 1 == NS ? 0 : nxt + 1;
   }
   // every wavefront is done with the stages before the row records and the
   // staged rows overwrite them
-  pair::barrier_vm<0>();
+  big::barrier_vm<0>();
   Row *rows_lds = reinterpret_cast<Row *>(smem + kRowsOff);
-  if (tid < kBM) rows_lds[tid] = rec;
-  pair::barrier_vm<0>();
-  write_back_staged<2, 2, 8>(acc, epi, m0 + wm * 64, n0 + wn * 64, M, lane,
-                             reinterpret_cast<float *>(smem) + wave * 32 * big::kWbStride,
-                             rows_lds + wm * 64, bias);
+#pragma unroll
+  for (int u = 0; u < (S::kBM + 255) / 256; ++u)
+    if (tid + 256 * u < S::kBM) rows_lds[tid + 256 * u] = rec[u];
+  big::barrier_vm<0>();
+  write_back_staged<2, TM, 8>(acc, epi, m0 + wm * 32 * TM, n0 + wn * 64, M, lane,
+                              reinterpret_cast<float *>(smem) + wave * 32 * 68,
+                              rows_lds + wm * 32 * TM, bias);
 }
 
 // ------------------------------------------------------------------ 64x128 tile
@@ -1349,7 +1186,7 @@ __device__ __forceinline__ void small_tile(const bf16 *A, const bf16 *W, int M, 
                                            const Epi &epi, int id, unsigned char *smem,
                                            typename Epi::Row *rows_lds) {
   using namespace small;
-  using pair::barrier_vm;
+  using big::barrier_vm;
   using big::pin;
   using Row = typename Epi::Row;
   constexpr int kStr = 2 * 32 + 4;  // staged write-back row (floats)
@@ -1618,50 +1455,47 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
   tile<Epi, MB, NORM>(A, W, M, K, epi, id * kBN, part, in, reinterpret_cast<bf16 *>(dyn));
 }
 
-// Tile choice.  A large tile (one workgroup per CU) when 256x256 tiles fill
-// at least 45% of their last wave over the compute units: a partly filled
-// last wave runs at a higher clock under the chip's power limit, and beside
-// another image range's kernels when the step runs as ranges on streams
-// (which is why the bound is this low: with a single range, such a wave
-// leaves the rest of the chip idle).  Of the two large tiles, the 320x256
-// one when its waves cover no more rows than the 256x256 tile's.
-// Otherwise the 128x256 tile, two workgroups per CU, whose write-backs
-// overlap the other workgroup's main loop and whose finer steps fill the chip
-// better; the 128x128 tile for narrow products it would spread too thinly;
-// and when even 128x256 tiles would occupy fewer than half the compute units,
-// the 64x128 tile (K a multiple of 128).  At MAR-L sizes, per 64-image range:
-// every full-layer product takes the 320x256 tile (QKV 3, output projection
-// and fc2 1, fc1 4 whole waves); the cache-aware fc1 and QKV take the 256x256
-// tile when a range has more than 2304 active rows (10 tiles of rows), else
-// the 128x256 tile; the cache-aware output projection and fc2 the 128x128
-// tile; the sampler's per-block GEMMs (a few hundred rows) the 64x128 tile.
-// Under sustained load the 128x256 tile runs at a lower clock (more operand
-// traffic per flop), which is why it does not replace the large tiles.
+// Tile choice by estimated time.  Every tile runs one workgroup per CU, so a
+// product takes ceil(tiles / CUs) rounds of c0 + (K / 64) c1 us: c0 the launch,
+// first loads and write-back, c1 a 64-deep k-tile, both fitted to products of
+// 150 to 5120 rows at the model widths (N = D, 3D, 4D, K = D, 4D for D = 768,
+// 1024, 1280; within about 20% of every measured time except where the whole
+// chip is busy and its clock drops, which moves all tiles alike).  Half of the
+// time that the tiles would take spread evenly over the chip is added: a tile
+// that computes the same product with less of the chip leaves the rest to an
+// image range on another stream (weights 0, 0.5, 1 and 2 measured: 0.5 is
+// level with 0 for single calls and with 2 for two ranges).  Measured against
+// the best of the tiles used before (320, 256 and 128 rows x 256 columns, 128
+// x 128, 64 x 128), one box: 4352 x 1024 x 4096: 71 -> 51 us (192 x 128),
+// 1280 x 4096 x 1024: 24.5 -> 18.8, 3600 x 1280 x 5120: 90 -> 64, 2432 x 3072 x
+// 1024: 23.9 -> 21.4 (256 x 128).
 int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
-  if (dt != DType::BF16 || m <= 0) return GEMM_TILE_128x256;
-  const long cus = device_cu_count();
-  const long tiles = (long)((m + 255) / 256) * (n / 256);
-  const long waves = (tiles + cus - 1) / cus;
-  const double fill = (double)tiles / (double)(waves * cus);
-  if (fill >= 0.45) {
-    // the 320x256 tile where its whole waves take no more time than the
-    // 256x256 tile's, counting a wave as its tile area (whole 320-token
-    // images at N = 1024 / 3072 / 4096: 1 wave against 1.25, 3 against
-    // 3.75, 4 against 5 -- the tie, fc1, measured 176.8 against 180.8 us)
-    const long tiles320 = (long)((m + t320::kBM - 1) / t320::kBM) * (n / 256);
-    const long waves320 = (tiles320 + cus - 1) / cus;
-    if (waves320 * t320::kBM <= waves * 256) return GEMM_TILE_320;
-    return GEMM_TILE_256;
+  if (dt != DType::BF16 || m <= 0) return GEMM_TILE_128;
+  struct Tile {
+    int kind, rows, cols;
+    double c0, c1;
+  };
+  static constexpr Tile kTiles[] = {
+      {GEMM_TILE_320, 320, 256, 10.5, 1.20}, {GEMM_TILE_256, 256, 256, 9.5, 1.10},
+      {GEMM_TILE_256x128, 256, 128, 6.5, 0.80}, {GEMM_TILE_192x128, 192, 128, 5.5, 0.60},
+      {GEMM_TILE_128, 128, 128, 4.5, 0.45}, {GEMM_TILE_64x128, 64, 128, 3.6, 0.345},
+  };
+  const int cus = device_cu_count();
+  const bool small_off = (int64_t)n * k < (1LL << 31);  // 32-bit operand offsets
+  int best = -1;
+  double best_t = 0.0;
+  for (const Tile &t : kTiles) {
+    if (t.kind == GEMM_TILE_64x128 && k % small::kBK != 0) continue;
+    if (!small_off && t.kind != GEMM_TILE_256 && t.kind != GEMM_TILE_64x128) continue;
+    const int64_t tiles = (int64_t)((m + t.rows - 1) / t.rows) * (n / t.cols);
+    const double one = t.c0 + (k / 64) * t.c1;
+    const double time = (double)((tiles + cus - 1) / cus) * one + 0.5 * tiles * one / cus;
+    if (best < 0 || time < best_t) {
+      best = t.kind;
+      best_t = time;
+    }
   }
-  if (k % small::kBK == 0 && (long)((m + 127) / 128) * (n / 256) * 2 < cus) {
-    // narrow products that 128x128 tiles still spread over half the compute
-    // units or more take them (the cache-aware output projection and fc2 of
-    // a 64-image MAR-L range: 39 vs 52 us for fc2, 13.5 vs 19.8 us for the
-    // output projection, each alone); smaller ones the 64x128 tile
-    if ((long)((m + mid::kBM - 1) / mid::kBM) * (n / mid::kBN) * 2 >= cus) return GEMM_TILE_128;
-    return GEMM_TILE_64x128;
-  }
-  return GEMM_TILE_128x256;
+  return best;
 }
 
 bool gemm_few_rows(DType dt, int32_t m) { return dt == DType::BF16 && m <= 64; }
@@ -1681,6 +1515,14 @@ static void run_rows(const bf16 *A, const bf16 *W, int m, int n, int k, const Ep
   else
     launch_kernel(gemm_bf16_rows_kernel<Epi, 4, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
                   sides, none);
+}
+
+template <class Epi, int TM, int NS>
+static void run_mid(const bf16 *A, const bf16 *W, int m, int n, int k, const Epi &epi,
+                    hipStream_t s) {
+  constexpr int kBM = mid::Shape<TM>::kBM;
+  launch_kernel(gemm_bf16_mid_kernel<Epi, TM, NS>, ((m + kBM - 1) / kBM) * (n / mid::kBN), 256, 0,
+                s, A, W, m, n, k, epi);
 }
 
 // N a multiple of 256 and K of 64 (the host limits d_model and d_mlp to
@@ -1712,18 +1554,9 @@ static hipError_t run_bf16(const void *a, const void *w, int m, int n, int k, co
                     ((m + small::kBM - 1) / small::kBM) * (n / small::kBN), 256, 0, s, A, W, m, n,
                     k, epi, HeadSides{});
       break;
-    case GEMM_TILE_128:
-      launch_kernel(gemm_bf16_mid_kernel<Epi, 4>,
-                    ((m + mid::kBM - 1) / mid::kBM) * (n / mid::kBN), 256, 0, s, A, W, m, n, k,
-                    epi);
-      break;
-    default: {
-      const int tiles = ((m + pair::kBM - 1) / pair::kBM) * (n / pair::kBN);
-      if (tiles <= device_cu_count() && k >= 2048)
-        launch_kernel(gemm_bf16_pair_kernel<Epi, 6>, tiles, 256, 0, s, A, W, m, n, k, epi);
-      else
-        launch_kernel(gemm_bf16_pair_kernel<Epi, 3>, tiles, 256, 0, s, A, W, m, n, k, epi);
-    }
+    case GEMM_TILE_192x128: run_mid<Epi, 3, 4>(A, W, m, n, k, epi, s); break;
+    case GEMM_TILE_256x128: run_mid<Epi, 4, 3>(A, W, m, n, k, epi, s); break;
+    default: run_mid<Epi, 2, 4>(A, W, m, n, k, epi, s); break;
   }
   return hipGetLastError();
 }
@@ -1868,9 +1701,9 @@ __global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const float *A, cons
     // k-tile t landed (issued so far: up to t + NS - 2, four loads each) and
     // every wavefront done with k-tile t - 1, whose stage takes t + NS - 1
     const int ahead = min(NS - 2, nk - 1 - t);
-    if (ahead >= 2) pair::barrier_vm<8>();
-    else if (ahead == 1) pair::barrier_vm<4>();
-    else pair::barrier_vm<0>();
+    if (ahead >= 2) big::barrier_vm<8>();
+    else if (ahead == 1) big::barrier_vm<4>();
+    else big::barrier_vm<0>();
     if (t + NS - 1 < nk) load_tile(t + NS - 1);
     const unsigned char *sc = smem + (t % NS) * kStage;
 #pragma unroll
@@ -1885,7 +1718,7 @@ __global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const float *A, cons
     }
   }
   if (tid < T) rows_lds[tid] = rec;
-  pair::barrier_vm<0>();
+  big::barrier_vm<0>();
   write_back_staged<1, 1, 4>(acc, epi, m0 + wm * 32, n0 + wn * 32, M, lane,
                              reinterpret_cast<float *>(smem) + wave * 32 * kStr, rows_lds + wm * 32,
                              bias);

@@ -105,41 +105,30 @@ marche_status_t check_model(const marche_model_t *m) {
 // One class per kernel symbol.  The attention kernel is instantiated per
 // query-chunk width (1, 2, 4 or 8 wavefronts of 32 queries), chosen from the
 // largest active set and the number of (image, head) pairs of the call (fp32
-// attention is timed under the first); each bf16 GEMM has a 128x256, a 256x256
-// (class + 1), a 64x128 (_S), a 128x128 (_M), a 320x256 (_I) and, for the
-// sampler, a few-row (_R) instantiation, chosen from its shape (fp32 GEMMs are timed under the
-// first).
+// attention is timed under the first); each bf16 GEMM per tile, chosen from
+// its shape (fp32 GEMMs are timed under the 128x128 tile), the sampler's also
+// as a few-row kernel.
 enum KClass {
-  K_ROW_MAP, K_GATHER_LN, K_GEMM_QKV, K_GEMM_QKV_L, K_ATTN_W1, K_ATTN_W2, K_ATTN_W4,
-  K_ATTN_SCORES, K_GEMM_O, K_GEMM_O_L, K_GEMM_FC1, K_GEMM_FC1_L, K_GEMM_FC2, K_GEMM_FC2_L,
-  K_SELECT, K_DECODER_INPUT, K_FILL, K_ATTN2_W1, K_ATTN2_W2, K_ATTN2_W4, K_CONCAT, K_ATTN_RES,
-  K_ENC_INPUT, K_MASK_FILL, K_LN_ROWS, K_GEMM_EMBED, K_GEMM_EMBED_L, K_TIME_SINUS, K_GEMM_HEAD,
-  K_GEMM_HEAD_L, K_GEMM_HEAD_SILU, K_GEMM_HEAD_SILU_L, K_HEAD_SILU_COND, K_HEAD_MOD, K_HEAD_STEP,
-  K_GEMM_QKV_S, K_GEMM_O_S, K_GEMM_FC1_S, K_GEMM_FC2_S,
-  K_GEMM_EMBED_S, K_GEMM_HEAD_S, K_GEMM_HEAD_SILU_S, K_TRANSPOSE, K_GEMM_QKV_M, K_GEMM_O_M,
-  K_GEMM_FC1_M, K_GEMM_FC2_M, K_GEMM_EMBED_M, K_GEMM_HEAD_M, K_GEMM_HEAD_SILU_M,
-  K_ATTN_RES_SC, K_ATTN_W8, K_ATTN_SC, K_GEMM_QKV_I, K_GEMM_O_I, K_GEMM_FC1_I, K_GEMM_FC2_I,
-  K_GEMM_EMBED_I, K_GEMM_HEAD_I, K_GEMM_HEAD_SILU_I, K_GEMM_HEAD_R, K_GEMM_HEAD_SILU_R,
-  K_NCLASS
+  K_ROW_MAP, K_GATHER_LN, K_ATTN_W1, K_ATTN_W2, K_ATTN_W4, K_ATTN_SCORES, K_SELECT, K_DECODER_INPUT,
+  K_FILL, K_ATTN2_W1, K_ATTN2_W2, K_ATTN2_W4, K_CONCAT, K_ATTN_RES, K_ENC_INPUT, K_MASK_FILL,
+  K_LN_ROWS, K_TIME_SINUS, K_HEAD_SILU_COND, K_HEAD_MOD, K_HEAD_STEP, K_TRANSPOSE, K_ATTN_RES_SC,
+  K_ATTN_W8, K_ATTN_SC,
+  K_GEMM_FIRST  // then, per projection, one class per tile and the few-row kernel
 };
-const char *const kClassNames[K_NCLASS] = {
-    "row_map",           "gather_ln",      "gemm_qkv_t128x256", "gemm_qkv_t256",
-    "attention_q32",     "attention_q64",  "attention_q128",    "attn_scores",
-    "gemm_o_t128x256",   "gemm_o_t256",    "gemm_fc1_t128x256", "gemm_fc1_t256",
-    "gemm_fc2_t128x256", "gemm_fc2_t256",  "select_topk",       "decoder_input",
-    "fill_zero",         "attention2_q32", "attention2_q64",    "attention2_q128",
-    "concat_kv",         "attention_res",  "encoder_input",     "mask_fill",
-    "ln_rows",           "gemm_embed_t128x256", "gemm_embed_t256", "time_sinus",
-    "gemm_head_t128x256", "gemm_head_t256", "gemm_head_silu_t128x256", "gemm_head_silu_t256",
-    "head_silu_cond",    "head_mod",       "head_step",
-    "gemm_qkv_t64x128",  "gemm_o_t64x128", "gemm_fc1_t64x128",  "gemm_fc2_t64x128",
-    "gemm_embed_t64x128", "gemm_head_t64x128", "gemm_head_silu_t64x128", "transpose",
-    "gemm_qkv_t128",     "gemm_o_t128",    "gemm_fc1_t128",     "gemm_fc2_t128",
-    "gemm_embed_t128",   "gemm_head_t128", "gemm_head_silu_t128", "attention_res_scores", "attention_q256",
-    "attention_scores",  "gemm_qkv_t320",  "gemm_o_t320",      "gemm_fc1_t320",
-    "gemm_fc2_t320",     "gemm_embed_t320", "gemm_head_t320",  "gemm_head_silu_t320",
-    "gemm_head_rows",    "gemm_head_silu_rows"};
-static_assert(sizeof(kClassNames) / sizeof(kClassNames[0]) == K_NCLASS, "one name per class");
+const char *const kClassNames[K_GEMM_FIRST] = {
+    "row_map",        "gather_ln",      "attention_q32",  "attention_q64",       "attention_q128",
+    "attn_scores",    "select_topk",    "decoder_input",  "fill_zero",           "attention2_q32",
+    "attention2_q64", "attention2_q128", "concat_kv",     "attention_res",       "encoder_input",
+    "mask_fill",      "ln_rows",        "time_sinus",     "head_silu_cond",      "head_mod",
+    "head_step",      "transpose",      "attention_res_scores", "attention_q256", "attention_scores"};
+static_assert(sizeof(kClassNames) / sizeof(kClassNames[0]) == K_GEMM_FIRST, "one name per class");
+
+enum GemmProj { P_QKV, P_O, P_FC1, P_FC2, P_EMBED, P_HEAD, P_HEAD_SILU, P_COUNT };
+const char *const kProjNames[P_COUNT] = {"qkv", "o", "fc1", "fc2", "embed", "head", "head_silu"};
+constexpr int kGemmKinds = GEMM_TILE_COUNT + 1;
+const char *const kTileNames[kGemmKinds] = {"t256", "t320", "t64x128", "t128", "t192x128", "t256x128",
+                                            "rows"};
+constexpr int K_NCLASS = K_GEMM_FIRST + P_COUNT * kGemmKinds;
 
 // Launches inside marche_step in layers where not every token of every image
 // is active (cache-aware layers) are timed under a class of their own: the
@@ -151,54 +140,20 @@ constexpr int K_NTIMED = 2 * K_NCLASS;
 const char *class_name(int i) {
   static const std::vector<std::string> names = [] {
     std::vector<std::string> v;
-    for (int j = 0; j < K_NCLASS; ++j) v.emplace_back(kClassNames[j]);
-    for (int j = 0; j < K_NCLASS; ++j) v.emplace_back(std::string(kClassNames[j]) + "_ca");
+    for (int j = 0; j < K_GEMM_FIRST; ++j) v.emplace_back(kClassNames[j]);
+    for (const char *proj : kProjNames)
+      for (const char *tile : kTileNames)
+        v.emplace_back(std::string("gemm_") + proj + "_" + tile);
+    for (int j = 0; j < K_NCLASS; ++j) v.emplace_back(v[j] + "_ca");
     return v;
   }();
   return names[i].c_str();
 }
 
-// Timing class of a GEMM launch: base is the projection's 128x256 class, the
-// 256x256 class follows it; the 64x128 classes are listed separately.
-int gemm_class(int base, DType dt, int32_t m, int32_t n, int32_t k) {
-  if (gemm_few_rows(dt, m)) {
-    if (base == K_GEMM_HEAD) return K_GEMM_HEAD_R;
-    if (base == K_GEMM_HEAD_SILU) return K_GEMM_HEAD_SILU_R;
-  }
-  const int kind = gemm_tile_kind(dt, m, n, k);
-  if (kind == GEMM_TILE_256) return base + 1;
-  if (kind == GEMM_TILE_320) {
-    switch (base) {
-      case K_GEMM_QKV: return K_GEMM_QKV_I;
-      case K_GEMM_O: return K_GEMM_O_I;
-      case K_GEMM_FC1: return K_GEMM_FC1_I;
-      case K_GEMM_FC2: return K_GEMM_FC2_I;
-      case K_GEMM_EMBED: return K_GEMM_EMBED_I;
-      case K_GEMM_HEAD: return K_GEMM_HEAD_I;
-      default: return K_GEMM_HEAD_SILU_I;
-    }
-  }
-  if (kind == GEMM_TILE_128) {
-    switch (base) {
-      case K_GEMM_QKV: return K_GEMM_QKV_M;
-      case K_GEMM_O: return K_GEMM_O_M;
-      case K_GEMM_FC1: return K_GEMM_FC1_M;
-      case K_GEMM_FC2: return K_GEMM_FC2_M;
-      case K_GEMM_EMBED: return K_GEMM_EMBED_M;
-      case K_GEMM_HEAD: return K_GEMM_HEAD_M;
-      default: return K_GEMM_HEAD_SILU_M;
-    }
-  }
-  if (kind != GEMM_TILE_64x128) return base;
-  switch (base) {
-    case K_GEMM_QKV: return K_GEMM_QKV_S;
-    case K_GEMM_O: return K_GEMM_O_S;
-    case K_GEMM_FC1: return K_GEMM_FC1_S;
-    case K_GEMM_FC2: return K_GEMM_FC2_S;
-    case K_GEMM_EMBED: return K_GEMM_EMBED_S;
-    case K_GEMM_HEAD: return K_GEMM_HEAD_S;
-    default: return K_GEMM_HEAD_SILU_S;
-  }
+// Timing class of a GEMM launch.
+int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k) {
+  const bool few = (proj == P_HEAD || proj == P_HEAD_SILU) && gemm_few_rows(dt, m);
+  return K_GEMM_FIRST + proj * kGemmKinds + (few ? GEMM_TILE_COUNT : gemm_tile_kind(dt, m, n, k));
 }
 
 int attn_class(DType dt, const AttnArgs &a) {
@@ -473,7 +428,7 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
            launch_gather_ln(dt, buf0, x, map, static_cast<const float *>(L.ln1_g),
                             static_cast<const float *>(L.ln1_b), M, D, m->ln_eps, stream));
     QkvOut qo{buf1, kc, vc, D, dh, H, N};
-    LAUNCH(gemm_class(K_GEMM_QKV, dt, M, 3 * D, D) + ko, 2.0 * M * 3 * D * D,
+    LAUNCH(gemm_class(P_QKV, dt, M, 3 * D, D) + ko, 2.0 * M * 3 * D * D,
            gemm_bytes_act * ((double)M * D + 3.0 * D * D + 3.0 * M * D),
            launch_gemm_qkv(dt, buf0, L.w_qkv, static_cast<const float *>(L.b_qkv), M, 3 * D, D,
                            map, qo, stream));
@@ -503,17 +458,17 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
              es * (double)batch * N * D + 4.0 * batch * H * N,
              launch_attn_scores(dt, aa, n_gen, gen_max, scores, stream));
     }
-    LAUNCH(gemm_class(K_GEMM_O, dt, M, D, D) + ko, 2.0 * M * D * D, gemm_bytes_act * ((double)M * D + (double)D * D) + 8.0 * M * D,
+    LAUNCH(gemm_class(P_O, dt, M, D, D) + ko, 2.0 * M * D * D, gemm_bytes_act * ((double)M * D + (double)D * D) + 8.0 * M * D,
            launch_gemm_resid(dt, buf0, L.w_o, static_cast<const float *>(L.b_o), M, D, D, map, x,
                              0, stream));
     LAUNCH(K_GATHER_LN + ko, 0, (double)M * D * (4 + es),
            launch_gather_ln(dt, buf1, x, map, static_cast<const float *>(L.ln2_g),
                             static_cast<const float *>(L.ln2_b), M, D, m->ln_eps, stream));
-    LAUNCH(gemm_class(K_GEMM_FC1, dt, M, F, D) + ko, 2.0 * M * F * D,
+    LAUNCH(gemm_class(P_FC1, dt, M, F, D) + ko, 2.0 * M * F * D,
            gemm_bytes_act * ((double)M * D + (double)F * D + (double)M * F),
            launch_gemm_gelu(dt, buf1, L.w_1, static_cast<const float *>(L.b_1), M, F, D, hid,
                             stream));
-    LAUNCH(gemm_class(K_GEMM_FC2, dt, M, D, F) + ko, 2.0 * M * D * F,
+    LAUNCH(gemm_class(P_FC2, dt, M, D, F) + ko, 2.0 * M * D * F,
            gemm_bytes_act * ((double)M * F + (double)D * F) + 8.0 * M * D,
            launch_gemm_resid(dt, hid, L.w_2, static_cast<const float *>(L.b_2), M, D, F, map, x,
                              1, stream));
@@ -758,7 +713,7 @@ marche_status_t marche_encoder_to_decoder(float *x_dec, const float *x_enc, cons
     LAUNCH(K_LN_ROWS, 0, (double)M * D * (4 + es),
            launch_ln_rows(dt, workspace, x_enc, nullptr, ln_g, ln_b, nullptr, M, 1, 0, D, ln_eps,
                           stream));
-    LAUNCH(gemm_class(K_GEMM_EMBED, dt, M, D, D), 2.0 * M * (double)D * D,
+    LAUNCH(gemm_class(P_EMBED, dt, M, D, D), 2.0 * M * (double)D * D,
            es * ((double)M * D + (double)D * D) + 4.0 * (double)M * D + 4.0 * (double)n_tokens * D,
            launch_gemm_embed(dt, workspace, w_de, b_de, M, D, D, x_dec, pe_dec, known, n_enc, n_buf,
                              n_known, n_tokens, stream));
@@ -892,14 +847,14 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
   LAUNCH(K_LN_ROWS, 0, (double)M * D * (4 + es) + 4.0 * M * D,
          launch_ln_rows(dt, z, x_dec, rows, dec_ln_g, dec_ln_b, pe_diff, M, n_tokens, n_buf, D,
                         dec_ln_eps, stream));
-  LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, W, D), 2.0 * M * (double)W * D,
+  LAUNCH(gemm_class(P_HEAD, dt, M, W, D), 2.0 * M * (double)W * D,
          es * ((double)M * D + (double)W * D) + 4.0 * M * W,
          launch_gemm_plain(dt, z, w->w_c, fp(w->b_c), M, W, D, cond, DType::F32, false, W, stream));
   LAUNCH(K_TIME_SINUS, 0, es * (double)T * F, launch_time_sinus(dt, sinus, T, F, stream));
-  LAUNCH(gemm_class(K_GEMM_HEAD_SILU, dt, T, W, F), 2.0 * T * (double)W * F,
+  LAUNCH(gemm_class(P_HEAD_SILU, dt, T, W, F), 2.0 * T * (double)W * F,
          es * ((double)T * F + (double)W * F + (double)T * W),
          launch_gemm_plain(dt, sinus, w->w_t1, fp(w->b_t1), T, W, F, h1, dt, true, W, stream));
-  LAUNCH(gemm_class(K_GEMM_HEAD, dt, T, W, W), 2.0 * T * (double)W * W,
+  LAUNCH(gemm_class(P_HEAD, dt, T, W, W), 2.0 * T * (double)W * W,
          es * ((double)T * W + (double)W * W) + 4.0 * T * W,
          launch_gemm_plain(dt, h1, w->w_t2, fp(w->b_t2), T, W, W, temb, DType::F32, false, W,
                            stream));
@@ -944,7 +899,7 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
   };
   auto mod_gemm = [&](void *from, int c0, int n) -> marche_status_t {
     const HeadSide m = mod_cols(from, c0, n);
-    LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, n, W), 2.0 * M * (double)n * W,
+    LAUNCH(gemm_class(P_HEAD, dt, M, n, W), 2.0 * M * (double)n * W,
            es * ((double)M * W + (double)n * W + (double)M * n),
            launch_gemm_plain(dt, m.a, m.w, m.bias, M, n, W, m.out, dt, false, ML, stream));
     return MARCHE_OK;
@@ -1006,14 +961,14 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
         }
         side_n[g] = (double)sides[g].s[0].n + sides[g].s[1].n;
       }
-      LAUNCH(gemm_class(K_GEMM_HEAD_SILU, dt, M, W, W), 2.0 * M * (W + side_n[0]) * W,
+      LAUNCH(gemm_class(P_HEAD_SILU, dt, M, W, W), 2.0 * M * (W + side_n[0]) * W,
              es * (2.0 * M * W + (double)W * W + side_n[0] * (W + M)),
              norm_in ? launch_head_gemm_norm_silu(hbuf, mod, ML, 3 * k * W, (3 * k + 1) * W,
                                                   hd->ln_eps, w1, fp(w->b_1) + (size_t)k * W, M, W,
                                                   ybuf, sides[0], stream)
                      : launch_head_gemm_silu(dt, abuf, w1, fp(w->b_1) + (size_t)k * W, M, W, ybuf,
                                              sides[0], stream));
-      LAUNCH(gemm_class(K_GEMM_HEAD, dt, M, W, W), 2.0 * M * (W + side_n[1]) * W,
+      LAUNCH(gemm_class(P_HEAD, dt, M, W, W), 2.0 * M * (W + side_n[1]) * W,
              es * (2.0 * M * W + (double)W * W + side_n[1] * (W + M)) + 8.0 * M * W,
              launch_head_gemm_gate(dt, ybuf, w2, fp(w->b_2) + (size_t)k * W, M, W, hbuf,
                                    static_cast<const char *>(mod) + (size_t)(3 * k + 2) * W * es,

@@ -3,7 +3,8 @@ products of one row, of 16 / 32 / 64-row remainders and of enough rows for the
 64x64 tile; fp32 attention with one and with four rows per workgroup; bf16
 attention on ragged key tails at both head widths for one to four query
 blocks, with the score pass as a kernel of its own, and stand-alone with few
-(image, head) pairs (two key groups per workgroup) and with many; the sampler's block
+(image, head) pairs (two key groups per workgroup) and with many; the 192- and
+256-row tiles with ragged last tiles; the sampler's block
 products and modulations at the row counts where their kernels change."""
 from dataclasses import replace
 
@@ -75,6 +76,32 @@ def test_bf16_attention_shapes(case):
     d, h, dh, n, sizes, gens = case
     cfg = workload.Config(61, "bf16-shape", 1, d, h, dh, 1024, n, 0, len(sizes), "bf16")
     _case(cfg, sizes, gens, seed=sum(sizes) + n)
+
+
+# Active rows per image at D = 1024, MLP 4096, and a tile each product count
+# takes: 192 rows x 128 columns with 135 rows in the last tile, 256 x 128 with
+# one, 192 x 128 over several rounds of N = 1024.
+TILES = [
+    ([320] * 4 + [7], {"gemm_fc1_t192x128_ca"}),
+    ([320] * 7 + [65], {"gemm_qkv_t256x128_ca"}),
+    ([320] * 12 + [320, 1], {"gemm_o_t192x128_ca", "gemm_fc2_t192x128_ca"}),
+]
+
+
+@pytest.mark.parametrize("sizes,classes", TILES, ids=lambda v: str(sum(v)) if isinstance(v, list) else "")
+def test_gemm_tile_edges(sizes, classes):
+    from paper_2506_12035_amd import binding
+
+    cfg = workload.Config(62, "tile-edge", 1, 1024, 16, 64, 4096, 320, 0, len(sizes), "bf16")
+    binding.profile_reset()
+    binding.profile_enable(True)
+    try:
+        _case(cfg, sizes, [1] * len(sizes), seed=sum(sizes))
+        prof = binding.profile_collect()
+    finally:
+        binding.profile_enable(False)
+        binding.profile_reset()
+    assert classes <= set(prof), sorted(prof)
 
 
 # (batch, heads, head_dim, queries, active keys, cached keys).  One and two key
