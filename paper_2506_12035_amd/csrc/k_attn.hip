@@ -944,12 +944,29 @@ constexpr int RES_NTL = 5;    // keys resident: 320
 constexpr int RES_QMAX = 320; // queries per workgroup
 constexpr int RES_QMIN = 128; // queries below which the streaming kernels are used
 
-// Host choice of the resident kernel: more than 128 active queries in some
-// image (below that one streaming workgroup of four wavefronts covers an
-// (image, head), reads each K/V element once as well and skips wavefronts
-// without queries: 64 images x 16 heads with 9..71 queries of width 64
-// measured 25.5 against 30.7 us), all of them and all keys within one
+// Whether the resident kernel can take these sizes: more than 128 active
+// queries in some image (below that one streaming workgroup of four
+// wavefronts covers an (image, head), reads each K/V element once as well and
+// skips wavefronts without queries: 64 images x 16 heads with 9..71 queries of
+// width 64 measured 25.5 against 30.7 us), all of them and all keys within one
 // workgroup's reach, one key segment.
+static bool resident_fits(int32_t a_max, int32_t n_tokens, bool two_segments) {
+  return !two_segments && a_max > RES_QMIN && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
+}
+
+// Host choice of the resident kernel.  With fewer (image, head) pairs than two
+// workgroups per compute unit the streaming kernel spreads a pair's queries
+// over several workgroups instead (4 images x 12 heads x 320 tokens: 17.1
+// against about 8 us); from there on the two are level, and the resident one
+// is ahead when another image range runs beside it (two 64-image ranges of 16
+// heads: 12.94 against 13.09 ms for a full and a cache-aware step of 8
+// layers).  Both sum in the same order.  The score pass of these sizes is the
+// resident kernel's.
+bool attn_resident(const AttnArgs &a) {
+  return resident_fits(a.a_max, a.n_tokens, a.k2 != nullptr) &&
+         (a.scores || (int64_t)a.batch * a.n_heads >= 2 * device_cu_count());
+}
+
 // Query blocks per workgroup of the streaming kernel for a_max rows.
 static int reg_qb(int32_t a_max) {
   return a_max <= 32 ? 1 : a_max <= 64 ? 2 : a_max <= 128 ? 4 : 8;
@@ -960,7 +977,7 @@ bool attn_resident(int32_t a_max, int32_t n_tokens, bool two_segments) {
 }
 
 bool attn_fuses_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_t gen_max) {
-  if (attn_resident(a_max, n_tokens, false)) return true;
+  if (resident_fits(a_max, n_tokens, false)) return true;
   // streaming kernel: the generating rows within query chunk 0, and one
   // (key block, generating block) pair per wavefront
   return attn_streams(head_dim, n_tokens, false) && 2 * ((gen_max + 31) / 32) <= reg_qb(a_max);
@@ -1018,8 +1035,15 @@ static AttnShape attn_shape(const AttnArgs &a) {
                                          ((a.a_max + 32 * q - 1) / (32 * q)) <=
                                      device_cu_count();
   if (split) return {q, 2, false};
-  if (attn_streams(a.head_dim, a.n_tokens, a.k2 != nullptr) && !a.stats)
-    return {reg_qb(a.a_max), 1, true};
+  if (attn_streams(a.head_dim, a.n_tokens, a.k2 != nullptr) && !a.stats) {
+    // eight blocks (fewer passes over K/V) only where that leaves four
+    // workgroups per compute unit: 4 images x 16 heads x 1088 queries measured
+    // 50 us per call with eight and 44 with four
+    const int qb = reg_qb(a.a_max);
+    const int64_t wgs8 = (int64_t)a.batch * a.n_heads * ((a.a_max + 255) / 256);
+    if (qb == 8 && !a.scores && wgs8 < 4 * device_cu_count() && a.a_max > 256) return {4, 1, true};
+    return {qb, 1, true};
+  }
   return {std::min(reg_qb(a.a_max), 4), 1, false};
 }
 
@@ -1048,7 +1072,7 @@ static hipError_t attn_bf16_nw(const AttnArgs &a, hipStream_t s) {
 template <int DH>
 static hipError_t attn_bf16_dispatch(const AttnArgs &a, hipStream_t s) {
   if (a.k2) return attn_bf16_nw<DH, true>(a, s);
-  if (attn_resident(a.a_max, a.n_tokens, a.k2 != nullptr)) {
+  if (attn_resident(a)) {
     const int grid = a.batch * a.n_heads;
     if constexpr (DH == 64) {  // 80 KB of swizzled tiles: two workgroups per CU
       if (a.scores)

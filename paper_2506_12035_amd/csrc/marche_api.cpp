@@ -159,7 +159,7 @@ int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k) {
 int attn_class(DType dt, const AttnArgs &a) {
   const bool seg2 = a.k2 != nullptr;
   if (dt != DType::BF16) return K_ATTN_W1;
-  if (attn_resident(a.a_max, a.n_tokens, seg2)) return K_ATTN_RES;
+  if (attn_resident(a)) return K_ATTN_RES;
   switch (attn_query_blocks(a)) {
     case 1: return seg2 ? K_ATTN2_W1 : K_ATTN_W1;
     case 2: return seg2 ? K_ATTN2_W2 : K_ATTN_W2;

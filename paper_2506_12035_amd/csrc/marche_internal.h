@@ -210,9 +210,9 @@ struct AttnArgs {
   float *stats = nullptr;
 };
 hipError_t launch_attention(DType dt, const AttnArgs &a, hipStream_t s);
-// Whether bf16 attention with these sizes runs the resident-K/V kernel (one
-// workgroup per (image, head)).
-bool attn_resident(int32_t a_max, int32_t n_tokens, bool two_segments);
+// Whether these bf16 arguments run the resident-K/V kernel (one workgroup per
+// (image, head)).
+bool attn_resident(const AttnArgs &a);
 // Whether bf16 attention with these sizes runs the register-staged streaming
 // kernel (head width 64, one key segment of whole tiles).
 bool attn_streams(int32_t head_dim, int32_t n_tokens, bool two_segments);
