@@ -948,16 +948,17 @@ constexpr int RES_QMIN = 128; // queries below which the streaming kernels are u
 // queries in some image (below that one streaming workgroup of four
 // wavefronts covers an (image, head), reads each K/V element once as well and
 // skips wavefronts without queries: 64 images x 16 heads with 9..71 queries of
-// width 64 measured 25.5 against 30.7 us), all of them and all keys within one
-// workgroup's reach, one key segment.
+// width 64 took 30.7 us on the resident kernel, and the 4-layer call 652 us on
+// it against 631), all of them and all keys within one workgroup's reach, one
+// key segment.
 static bool resident_fits(int32_t a_max, int32_t n_tokens, bool two_segments) {
   return !two_segments && a_max > RES_QMIN && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
 }
 
 // Host choice of the resident kernel.  With fewer (image, head) pairs than two
 // workgroups per compute unit the streaming kernel spreads a pair's queries
-// over several workgroups instead (4 images x 12 heads x 320 tokens: 17.1
-// against about 8 us); from there on the two are level, and the resident one
+// over several workgroups instead (4 images x 12 heads x 320 tokens, 12 layers
+// of a full and a cache-aware step: 1761 us with it, 1655 without); from there on the two are level, and the resident one
 // is ahead when another image range runs beside it (two 64-image ranges of 16
 // heads: 12.94 against 13.09 ms for a full and a cache-aware step of 8
 // layers).  Both sum in the same order.  The score pass of these sizes is the
@@ -1037,8 +1038,8 @@ static AttnShape attn_shape(const AttnArgs &a) {
   if (split) return {q, 2, false};
   if (attn_streams(a.head_dim, a.n_tokens, a.k2 != nullptr) && !a.stats) {
     // eight blocks (fewer passes over K/V) only where that leaves four
-    // workgroups per compute unit: 4 images x 16 heads x 1088 queries measured
-    // 50 us per call with eight and 44 with four
+    // workgroups per compute unit: a step of 8 layers with 2 x 4 images x 16
+    // heads x 1088 queries measured 2602 us with eight and 2546 with four
     const int qb = reg_qb(a.a_max);
     const int64_t wgs8 = (int64_t)a.batch * a.n_heads * ((a.a_max + 255) / 256);
     if (qb == 8 && !a.scores && wgs8 < 4 * device_cu_count() && a.a_max > 256) return {4, 1, true};

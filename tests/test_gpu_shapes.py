@@ -5,7 +5,8 @@ attention on ragged key tails at both head widths for one to four query
 blocks, with the score pass as a kernel of its own, and stand-alone with few
 (image, head) pairs (two key groups per workgroup) and with many; the 192- and
 256-row tiles with ragged last tiles; the sampler's block
-products and modulations at the row counts where their kernels change."""
+products and modulations at the row counts where their kernels change; the
+encoder input at its channel widths, with one row per wavefront and several."""
 from dataclasses import replace
 
 import numpy as np
@@ -184,3 +185,46 @@ def test_sampler_shapes(case):
     say(f"  max rel err {e:.2e}")
     assert e <= TOL[dtype]
     assert np.isnan(got[np.setdiff1d(np.arange(got.shape[0]), out_rows)]).all()
+
+
+# (images, n_buf, n_img, n_known, d_model, channels).  64 images of 157 rows
+# give a wavefront five to ten rows of 512 columns (the last group ragged,
+# buffer and image rows within one group), two images one row; the channels sit
+# on both sides of each compile-time width.
+ENC_IN = [
+    (64, 7, 200, 150, 512, 16),
+    (64, 7, 200, 150, 512, 64),
+    (64, 7, 200, 150, 256, 33),
+    (2, 3, 20, 11, 1280, 17),
+    (2, 0, 20, 20, 256, 5),
+    (2, 3, 20, 11, 4096, 1),
+]
+
+
+@pytest.mark.parametrize("B,n_buf,n_img,n_known,D,C", ENC_IN)
+def test_encoder_input_rows(B, n_buf, n_img, n_known, D, C):
+    """Within 1e-6 of the largest output: a sum of at most 64 products in fp32
+    is off by 64 x 2^-24 of its terms' size, an order below that of a row's
+    largest output here.  The weights start at an odd word: they need 4-byte
+    alignment only."""
+    import torch
+
+    from paper_2506_12035_amd import binding
+
+    say(f"encoder input B={B} n_buf={n_buf} n_known={n_known} D={D} C={C}")
+    rng = np.random.default_rng(7)
+    cls, tok, b_z, pe, w_z = (rng.standard_normal(s).astype(np.float32) for s in (
+        (B, D), (B, n_img, C), (D,), (n_buf + n_img, D), (D, C)))
+    w_z *= 0.25
+    known = np.stack([np.sort(rng.permutation(n_img)[:n_known]) for _ in range(B)]).astype(np.int32)
+    dev = [torch.from_numpy(a).cuda() for a in (cls, tok, b_z, pe, known)]
+    w_dev = torch.empty(D * C + 1, device="cuda")[1:].view(D, C)
+    w_dev.copy_(torch.from_numpy(w_z))
+    x = torch.full((B, n_buf + n_known, D), float("nan"), device="cuda")
+    binding.encoder_input(x, dev[0], dev[1], w_dev, dev[2], dev[3], dev[4], B, n_buf, n_img, n_known, D, C)
+    torch.cuda.synchronize()
+    got = x.cpu().numpy()
+    for b in range(B):
+        ref = mar.encoder_input(cls[b], tok[b], w_z, b_z, pe, [n_buf + int(p) for p in known[b]], n_buf)
+        e = rel_err(got[b], ref)
+        assert e <= 1e-6, (b, e)
