@@ -106,7 +106,9 @@ def counter_class(name: str):
     """Timing class of a kernel symbol as rocprofv3 prints it (mangled or not),
     before the split into full and cache-aware layers."""
     mid = re.search(r"gemm_bf16_mid_kernel.*?(?:, |ELi)(\d)(?:, |ELi)\d(?:>|EEEv)", name)
-    tile = ("t256" if ("gemm_bf16_big_kernel" in name or "gemm_bf16_big8_kernel" in name) else
+    tiny = re.search(r"gemm_bf16_tiny_kernel.*?(?:, |ELi)(\d+)(?:, |ELi)(\d+)(?:, |ELi)\d(?:>|EEEv)", name)
+    tile = (f"t{tiny.group(1)}x{tiny.group(2)}" if tiny else
+            "t256" if ("gemm_bf16_big_kernel" in name or "gemm_bf16_big8_kernel" in name) else
             "t320" if "gemm_bf16_t320_kernel" in name else
             "t64x128" if "gemm_bf16_small_kernel" in name else
             "rows" if "gemm_bf16_rows_kernel" in name else

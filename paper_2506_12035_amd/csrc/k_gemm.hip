@@ -12,7 +12,8 @@
 // bf16 path (v_mfma_f32_32x32x16_bf16, fp32 accumulators), one workgroup per
 // CU: a 256x256 tile (four wavefronts for K >= 2048, eight below) or a 320x256
 // tile (whole 320-token images per tile row, eight wavefronts) for shapes that
-// fill the chip in whole waves, else 256, 192, 128 or 64 rows x 128 columns.
+// fill the chip in whole waves, else 256, 192, 128 or 64 rows x 128 columns, or
+// 64 x 64 to 32 x 32 for a few hundred rows.
 // All load operands straight from global memory into XOR-swizzled LDS stages
 // and write back through LDS in row-major order.  The sampler's products on up
 // to 64 rows have a kernel of their own.
@@ -95,7 +96,7 @@ struct EpiQkv : PlainPrior {
     return Row{(uint32_t)(r * d_model), (uint32_t)((m.b * n_heads * n_tokens + m.tok) * head_dim)};
   }
   // Which of q, K and V a column belongs to is decided once per wavefront:
-  // every tile gives a wavefront a span of 64 or 128 columns aligned to its
+  // every tile gives a wavefront a span of 32, 64 or 128 columns aligned to its
   // width, and d_model is a multiple of 256, so no span crosses from one of
   // the three into the next.  The choice is then uniform (scalar) and the
   // stores take no divergent branches.
@@ -1283,6 +1284,134 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16 *A, con
   small_tile(A, W, M, N, K, epi, id, smem, reinterpret_cast<typename Epi::Row *>(rows));
 }
 
+// ------------------------------------------------------------------ 32 and 64 rows x 32 and 64 columns
+//
+// For products of a few hundred rows, whose 64x128 tiles leave most of the
+// chip idle while each walks all of K alone, bound by what one CU loads
+// (about 60 to 85 GB/s where the weights come from the memory-side cache): a
+// tile of BM x BN x 128 keeps that walk in one workgroup -- every output is
+// still one accumulation over ascending k16 steps -- but loads (BM + BN) rows
+// instead of 192, on more CUs.  One 32x32 block per wavefront; tiles of fewer
+// than four blocks leave the other wavefronts to loading.  The loop is that of
+// the 64 TM x 128 tiles on the 256-byte rows of the 64x128 tile: fragments
+// read four k16 steps ahead, NS stages with NS - 1 k-tiles in flight, one
+// barrier per k-tile.
+template <class Epi, int BM, int BN, int NS>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, const bf16 *W, int M,
+                                                                int N, int K, Epi epi) {
+  using big::pin;
+  using small::kBK;
+  using small::kRow;
+  using Row = typename Epi::Row;
+  constexpr int kWOff = BM * kRow;
+  constexpr int kStage = (BM + BN) * kRow;
+  constexpr int kALoads = BM / 16, kLoads = (BM + BN) / 16;  // 1 KB each, per wavefront
+  constexpr int kBlocksN = BN / 32, kBlocks = BM / 32 * kBlocksN;
+  constexpr int kSteps = kBK / 16, PD = 4;  // k16 steps, fragments read PD of them ahead
+  constexpr int kStr = 32 + 4;              // staged write-back row (floats)
+  constexpr int kRowsOff = kBlocks * 32 * kStr * 4;
+  static_assert(NS >= 3 && kLoads * (NS - 1) <= 63, "stages; vmcnt holds 63");
+  static_assert(kRowsOff + BM * sizeof(Row) <= NS * kStage, "row records fit the stages");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * kStage];
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
+  int tm, tn;
+  tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool computes = wave < kBlocks;
+  const int wm = computes ? wave / kBlocksN : 0, wn = computes ? wave % kBlocksN : 0;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
+  f32x16 acc[1][1] = {{f32x16{}}};
+  const int nk = K / kBK;
+  // Load p of every k-tile: p < kALoads moves activation rows 4 q .. 4 q + 3
+  // (q = kALoads wave + p), the rest weight rows; lane l writes row 4 q + l / 16
+  // at physical chunk l % 16.  Activation rows past M repeat row M - 1.
+  uint32_t off[kLoads];
+#pragma unroll
+  for (int p = 0; p < kLoads; ++p) {
+    const bool is_a = p < kALoads;
+    const int q = is_a ? wave * kALoads + p : wave * (kLoads - kALoads) + (p - kALoads);
+    const int r = q * 4 + (lane >> 4);
+    const int row = is_a ? min(m0 + r, M - 1) : n0 + r;
+    off[p] = ((uint32_t)row * (uint32_t)K + (uint32_t)(small::swz(r, lane & 15) * 8)) * 2u;
+  }
+  auto load = [&](int st, int t, int p) {
+    const unsigned sb = lds0 + (unsigned)st * kStage;
+    if (p < kALoads)
+      t320::load_lds(sb + (wave * kALoads + p) * 1024, A + t * kBK, off[p]);
+    else
+      t320::load_lds(sb + kWOff + (wave * (kLoads - kALoads) + p - kALoads) * 1024, W + t * kBK,
+                     off[p]);
+  };
+  struct Frag {
+    bf16x8 x, w;
+  } f[kSteps];
+  const int xr = wm * 32 + (lane & 31), wr = wn * 32 + (lane & 31);
+  auto read = [&](int st, int s) {
+    const unsigned char *b = smem + st * kStage;
+    const int c = 2 * s + (lane >> 5);
+    f[s].x = *reinterpret_cast<const bf16x8 *>(b + xr * kRow + small::swz(xr, c) * 16);
+    f[s].w = *reinterpret_cast<const bf16x8 *>(b + kWOff + wr * kRow + small::swz(wr, c) * 16);
+  };
+
+  // the write-back's row record and this lane's bias, kept in registers until
+  // after the main loop
+  Row rec{};
+  if (tid < BM) rec = epi.row(min(m0 + tid, M - 1));
+  const f32x4 bias = epi.bias4(n0 + wn * 32 + (lane & 7) * 4);
+
+  // k-tiles 0 .. NS-2 in flight, then wait for k-tile 0
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < nk) {
+#pragma unroll
+      for (int p = 0; p < kLoads; ++p) load(t, t, p);
+    }
+  mid::barrier_tiles<kLoads, NS - 2>(min(NS - 1, nk) - 1);
+  if (computes) {
+#pragma unroll
+    for (int s = 0; s < PD; ++s) read(0, s);
+  }
+  int cur = 0, nxt = 1, prv = NS - 1;  // stages of k-tiles t, t + 1, t - 1
+  for (int t = 0; t < nk; ++t) {
+    const bool more = t + 1 < nk;
+    auto steps = [&](int s0, int s1, bool rd, int stage) {
+#pragma unroll
+      for (int s = s0; s < s1; ++s) {
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s].w, f[s].x, acc[0][0], 0, 0, 0);
+        if (rd) read(stage, (s + PD) % kSteps);
+        pin();
+      }
+    };
+    if (computes) steps(0, kSteps - PD, true, cur);
+    if (more) {
+      // k-tile t+1 landed; those of t + 2 .. t + NS - 2 may still be in flight
+      mid::barrier_tiles<kLoads, NS - 3>(min(NS - 3, nk - 2 - t));
+      pin();
+      // into the stage of k-tile t - 1, which every wavefront has read
+      if (t + NS - 1 < nk) {
+#pragma unroll
+        for (int p = 0; p < kLoads; ++p) load(prv, t + NS - 1, p);
+      }
+    }
+    if (computes) steps(kSteps - PD, kSteps, more, nxt);
+    prv = cur;
+    cur = nxt;
+    nxt = nxt + 1 == NS ? 0 : nxt + 1;
+  }
+  // every wavefront is done with the stages before the row records and the
+  // staged rows overwrite them
+  big::barrier_vm<0>();
+  Row *rows_lds = reinterpret_cast<Row *>(smem + kRowsOff);
+  if (tid < BM) rows_lds[tid] = rec;
+  big::barrier_vm<0>();
+  if (computes)
+    write_back_staged<1, 1, 4>(acc, epi, m0 + wm * 32, n0 + wn * 32, M, lane,
+                               reinterpret_cast<float *>(smem) + wave * 32 * kStr,
+                               rows_lds + wm * 32, bias);
+}
+
 // ------------------------------------------------------------------ few rows
 //
 // The sampler's products on up to 64 rows (a few images' generating tokens):
@@ -1458,7 +1587,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
 // Tile choice by estimated time.  Every tile runs one workgroup per CU, so a
 // product takes ceil(tiles / CUs) rounds of c0 + (K / 64) c1 us: c0 the launch,
 // first loads and write-back, c1 a 64-deep k-tile, both fitted to products of
-// 150 to 5120 rows at the model widths (N = D, 3D, 4D, K = D, 4D for D = 768,
+// 16 to 5120 rows at the model widths (N = D, 3D, 4D, K = D, 4D for D = 768,
 // 1024, 1280; within about 20% of every measured time except where the whole
 // chip is busy and its clock drops, which moves all tiles alike).  Half of the
 // time that the tiles would take spread evenly over the chip is added: a tile
@@ -1468,7 +1597,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
 // the best of the tiles used before (320, 256 and 128 rows x 256 columns, 128
 // x 128, 64 x 128), one box: 4352 x 1024 x 4096: 71 -> 51 us (192 x 128),
 // 1280 x 4096 x 1024: 24.5 -> 18.8, 3600 x 1280 x 5120: 90 -> 64, 2432 x 3072 x
-// 1024: 23.9 -> 21.4 (256 x 128).
+// 1024: 23.9 -> 21.4 (256 x 128).  The tiles of at most 64 x 64 against 64 x
+// 128: 150 x 768 x 3072: 19.5 -> 10.0 (32 x 32), 150 x 768 x 768: 7.9 -> 4.8,
+// 300 x 1024 x 4096: 24.6 -> 14.5 (32 x 64), 1280 x 768 x 3072: 20.5 -> 15.1
+// (64 x 64); 16 rows x 1280 x 5120: 29.0 -> 14.4 (32 x 32).
 int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
   if (dt != DType::BF16 || m <= 0) return GEMM_TILE_128;
   struct Tile {
@@ -1479,13 +1611,15 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
       {GEMM_TILE_320, 320, 256, 10.5, 1.20}, {GEMM_TILE_256, 256, 256, 9.5, 1.10},
       {GEMM_TILE_256x128, 256, 128, 6.5, 0.80}, {GEMM_TILE_192x128, 192, 128, 5.5, 0.60},
       {GEMM_TILE_128, 128, 128, 4.5, 0.45}, {GEMM_TILE_64x128, 64, 128, 3.6, 0.345},
+      {GEMM_TILE_64x64, 64, 64, 3.0, 0.217}, {GEMM_TILE_32x64, 32, 64, 2.95, 0.174},
+      {GEMM_TILE_32x32, 32, 32, 3.1, 0.1425},
   };
   const int cus = device_cu_count();
   const bool small_off = (int64_t)n * k < (1LL << 31);  // 32-bit operand offsets
   int best = -1;
   double best_t = 0.0;
   for (const Tile &t : kTiles) {
-    if (t.kind == GEMM_TILE_64x128 && k % small::kBK != 0) continue;
+    if (t.rows <= 64 && k % small::kBK != 0) continue;
     if (!small_off && t.kind != GEMM_TILE_256 && t.kind != GEMM_TILE_64x128) continue;
     const int64_t tiles = (int64_t)((m + t.rows - 1) / t.rows) * (n / t.cols);
     const double one = t.c0 + (k / 64) * t.c1;
@@ -1515,6 +1649,13 @@ static void run_rows(const bf16 *A, const bf16 *W, int m, int n, int k, const Ep
   else
     launch_kernel(gemm_bf16_rows_kernel<Epi, 4, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
                   sides, none);
+}
+
+template <class Epi, int BM, int BN, int NS>
+static void run_tiny(const bf16 *A, const bf16 *W, int m, int n, int k, const Epi &epi,
+                     hipStream_t s) {
+  launch_kernel(gemm_bf16_tiny_kernel<Epi, BM, BN, NS>, ((m + BM - 1) / BM) * (n / BN), 256, 0, s,
+                A, W, m, n, k, epi);
 }
 
 template <class Epi, int TM, int NS>
@@ -1554,6 +1695,9 @@ static hipError_t run_bf16(const void *a, const void *w, int m, int n, int k, co
                     ((m + small::kBM - 1) / small::kBM) * (n / small::kBN), 256, 0, s, A, W, m, n,
                     k, epi, HeadSides{});
       break;
+    case GEMM_TILE_64x64: run_tiny<Epi, 64, 64, 5>(A, W, m, n, k, epi, s); break;
+    case GEMM_TILE_32x64: run_tiny<Epi, 32, 64, 6>(A, W, m, n, k, epi, s); break;
+    case GEMM_TILE_32x32: run_tiny<Epi, 32, 32, 8>(A, W, m, n, k, epi, s); break;
     case GEMM_TILE_192x128: run_mid<Epi, 3, 4>(A, W, m, n, k, epi, s); break;
     case GEMM_TILE_256x128: run_mid<Epi, 4, 3>(A, W, m, n, k, epi, s); break;
     default: run_mid<Epi, 2, 4>(A, W, m, n, k, epi, s); break;

@@ -61,10 +61,10 @@ __device__ __forceinline__ float centre_rstd(float4 (&v)[NV], float eps) {
 // Bound by writing x.  Every lane keeps the CM weights of its V columns in
 // registers for `per_wave` rows; a wavefront that read them again for each row
 // (strided by a weight row from lane to lane) took 271 us for 64 images x 195
-// rows x 1024 columns x 16 channels, and 21 us now (30 and 4.9 for one image).  The weights come through LDS,
-// where the copy is coalesced and one padding word in 32 spreads the lanes'
-// strided reads over the banks.  Rows go four at a time with their loads up
-// front.  V x CM <= 128 registers of weights.
+// rows x 1024 columns x 16 channels, and 21 us now (30 and 4.9 for one image).
+// The weights come through LDS, where the copy is coalesced and one padding
+// word in 32 spreads the lanes' strided reads over the banks.  Rows go four at
+// a time with their loads up front.  V x CM <= 128 registers of weights.
 template <int CM>
 struct EncIn {
   static constexpr int V = CM >= 64 ? 2 : 4;  // columns per lane

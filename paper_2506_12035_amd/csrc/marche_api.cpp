@@ -127,7 +127,7 @@ enum GemmProj { P_QKV, P_O, P_FC1, P_FC2, P_EMBED, P_HEAD, P_HEAD_SILU, P_COUNT 
 const char *const kProjNames[P_COUNT] = {"qkv", "o", "fc1", "fc2", "embed", "head", "head_silu"};
 constexpr int kGemmKinds = GEMM_TILE_COUNT + 1;
 const char *const kTileNames[kGemmKinds] = {"t256", "t320", "t64x128", "t128", "t192x128", "t256x128",
-                                            "rows"};
+                                            "t64x64", "t32x64", "t32x32", "rows"};
 constexpr int K_NCLASS = K_GEMM_FIRST + P_COUNT * kGemmKinds;
 
 // Launches inside marche_step in layers where not every token of every image

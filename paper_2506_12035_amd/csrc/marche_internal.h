@@ -177,7 +177,7 @@ hipError_t launch_gemm_embed(DType dt, const void *a, const void *w, const float
 // bf16 GEMM workgroup tile of an M x N x K product (rows x columns).
 enum GemmTile {
   GEMM_TILE_256 = 0, GEMM_TILE_320, GEMM_TILE_64x128, GEMM_TILE_128, GEMM_TILE_192x128,
-  GEMM_TILE_256x128, GEMM_TILE_COUNT
+  GEMM_TILE_256x128, GEMM_TILE_64x64, GEMM_TILE_32x64, GEMM_TILE_32x32, GEMM_TILE_COUNT
 };
 int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k);
 // Whether a sampler product of m rows runs the few-row kernel instead.

@@ -3,8 +3,8 @@ products of one row, of 16 / 32 / 64-row remainders and of enough rows for the
 64x64 tile; fp32 attention with one and with four rows per workgroup; bf16
 attention on ragged key tails at both head widths for one to four query
 blocks, with the score pass as a kernel of its own, and stand-alone with few
-(image, head) pairs (two key groups per workgroup) and with many; the 192- and
-256-row tiles with ragged last tiles; the sampler's block
+(image, head) pairs (two key groups per workgroup) and with many; the tiles of
+32, 64, 192 and 256 rows with ragged last tiles; the sampler's block
 products and modulations at the row counts where their kernels change; the
 encoder input at its channel widths, with one row per wavefront and several."""
 from dataclasses import replace
@@ -81,8 +81,11 @@ def test_bf16_attention_shapes(case):
 
 # Active rows per image at D = 1024, MLP 4096, and a tile each product count
 # takes: 192 rows x 128 columns with 135 rows in the last tile, 256 x 128 with
-# one, 192 x 128 over several rounds of N = 1024.
+# one, 192 x 128 over several rounds of N = 1024; and the tiles of a few rows,
+# with one row in the last tile of 32 and 33 in the last of 64.
 TILES = [
+    ([96, 1], {"gemm_qkv_t64x64_ca", "gemm_o_t32x64_ca", "gemm_fc2_t32x32_ca"}),
+    ([1], {"gemm_qkv_t32x64_ca", "gemm_o_t32x32_ca"}),
     ([320] * 4 + [7], {"gemm_fc1_t192x128_ca"}),
     ([320] * 7 + [65], {"gemm_qkv_t256x128_ca"}),
     ([320] * 12 + [320, 1], {"gemm_o_t192x128_ca", "gemm_fc2_t192x128_ca"}),
