@@ -1296,9 +1296,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16 *A, con
 // the 64 TM x 128 tiles on the 256-byte rows of the 64x128 tile: fragments
 // read four k16 steps ahead, NS stages with NS - 1 k-tiles in flight, one
 // barrier per k-tile.
+// One tile of an M x N x K product; `smem` holds the NS stages.
 template <class Epi, int BM, int BN, int NS>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, const bf16 *W, int M,
-                                                                int N, int K, Epi epi) {
+__device__ __forceinline__ void tiny_tile(const bf16 *A, const bf16 *W, int M, int N, int K,
+                                          const Epi &epi, int id, unsigned char *smem) {
   using big::pin;
   using small::kBK;
   using small::kRow;
@@ -1312,10 +1313,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, c
   constexpr int kRowsOff = kBlocks * 32 * kStr * 4;
   static_assert(NS >= 3 && kLoads * (NS - 1) <= 63, "stages; vmcnt holds 63");
   static_assert(kRowsOff + BM * sizeof(Row) <= NS * kStage, "row records fit the stages");
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * kStage];
   const int tiles_m = (M + BM - 1) / BM, tiles_n = N / BN;
   int tm, tn;
-  tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, tm, tn);
+  tile_coords(id, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1410,6 +1410,30 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, c
     write_back_staged<1, 1, 4>(acc, epi, m0 + wm * 32, n0 + wn * 32, M, lane,
                                reinterpret_cast<float *>(smem) + wave * 32 * kStr,
                                rows_lds + wm * 32, bias);
+}
+
+// With side products (see HeadSides) the tiles of the main product come first.
+template <class Epi, bool SIDES, int BM, int BN, int NS>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, const bf16 *W, int M,
+                                                                int N, int K, Epi epi,
+                                                                HeadSides sides) {
+  using Plain = EpiPlain<bf16, false>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NS * (BM + BN) * small::kRow];
+  int id = xcd_remap(blockIdx.x, gridDim.x);
+  if constexpr (SIDES) {
+    const int tiles_m = (M + BM - 1) / BM;
+    const int main_tiles = tiles_m * (N / BN);
+    if (id >= main_tiles) {
+      id -= main_tiles;
+      const int first = tiles_m * (sides.s[0].n / BN);
+      const HeadSide j = id < first ? sides.s[0] : sides.s[1];
+      const Plain pe{{}, static_cast<bf16 *>(j.out), j.bias, sides.ld};
+      tiny_tile<Plain, BM, BN, NS>(static_cast<const bf16 *>(j.a), static_cast<const bf16 *>(j.w),
+                                   M, j.n, K, pe, id < first ? id : id - first, smem);
+      return;
+    }
+  }
+  tiny_tile<Epi, BM, BN, NS>(A, W, M, N, K, epi, id, smem);
 }
 
 // ------------------------------------------------------------------ few rows
@@ -1654,8 +1678,8 @@ static void run_rows(const bf16 *A, const bf16 *W, int m, int n, int k, const Ep
 template <class Epi, int BM, int BN, int NS>
 static void run_tiny(const bf16 *A, const bf16 *W, int m, int n, int k, const Epi &epi,
                      hipStream_t s) {
-  launch_kernel(gemm_bf16_tiny_kernel<Epi, BM, BN, NS>, ((m + BM - 1) / BM) * (n / BN), 256, 0, s,
-                A, W, m, n, k, epi);
+  launch_kernel(gemm_bf16_tiny_kernel<Epi, false, BM, BN, NS>, ((m + BM - 1) / BM) * (n / BN), 256,
+                0, s, A, W, m, n, k, epi, HeadSides{});
 }
 
 template <class Epi, int TM, int NS>
@@ -1966,6 +1990,27 @@ int head_side_tiles(DType dt, int32_t m, int32_t width) {
   return std::max(0, device_cu_count() / tiles_m - width / small::kBN);
 }
 
+// Tile of a sampler block's product of `width` columns with side products of
+// n_side columns on more rows than the few-row kernel takes: the smallest
+// whose tiles all run at once, one per CU, else 64 x 128 (50 steps of 8 blocks
+// of width 1280 with 64 x 128 always and by this rule: 96 rows 10.5 and 8.1 ms,
+// 128 rows 10.5 and 7.7, 256 rows 10.7 and 8.5).
+int head_tile_kind(int32_t m, int32_t width, int32_t n_side) {
+  if (n_side == 0) return gemm_tile_kind(DType::BF16, m, width, width);
+  const int cols = (width + n_side) / 64;
+  if ((m + 31) / 32 * cols <= device_cu_count()) return GEMM_TILE_32x64;
+  if ((m + 63) / 64 * cols <= device_cu_count()) return GEMM_TILE_64x64;
+  return GEMM_TILE_64x128;
+}
+
+template <class Epi, int BM, int BN, int NS>
+static void run_tiny_sides(const bf16 *A, const bf16 *W, int m, int width, const Epi &epi,
+                           const HeadSides &sides, int n_side, hipStream_t s) {
+  launch_kernel(gemm_bf16_tiny_kernel<Epi, true, BM, BN, NS>,
+                ((m + BM - 1) / BM) * ((width + n_side) / BN), 256, 0, s, A, W, m, width, width, epi,
+                sides);
+}
+
 template <class Epi>
 static hipError_t run_head(const void *a, const void *w, int m, int width, const Epi &epi,
                            const HeadSides &sides, hipStream_t s) {
@@ -1974,12 +2019,18 @@ static hipError_t run_head(const void *a, const void *w, int m, int width, const
   if (n_side == 0) return run_plain(a, w, m, width, width, epi, s);
   if (width % 256 != 0 || sides.s[0].n % small::kBN != 0 || sides.s[1].n % small::kBN != 0)
     return hipErrorInvalidValue;
-  if (gemm_few_rows(DType::BF16, m))
+  if (gemm_few_rows(DType::BF16, m)) {
     run_rows<Epi, true>(A, W, m, width, width, epi, sides, s);
-  else
-    launch_kernel(gemm_bf16_small_kernel<Epi, true>,
-                  ((m + small::kBM - 1) / small::kBM) * ((width + n_side) / small::kBN), 256, 0, s,
-                  A, W, m, width, width, epi, sides);
+    return hipGetLastError();
+  }
+  switch (head_tile_kind(m, width, n_side)) {
+    case GEMM_TILE_32x64: run_tiny_sides<Epi, 32, 64, 6>(A, W, m, width, epi, sides, n_side, s); break;
+    case GEMM_TILE_64x64: run_tiny_sides<Epi, 64, 64, 5>(A, W, m, width, epi, sides, n_side, s); break;
+    default:
+      launch_kernel(gemm_bf16_small_kernel<Epi, true>,
+                    ((m + small::kBM - 1) / small::kBM) * ((width + n_side) / small::kBN), 256, 0,
+                    s, A, W, m, width, width, epi, sides);
+  }
   return hipGetLastError();
 }
 

@@ -156,6 +156,12 @@ int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k) {
   return K_GEMM_FIRST + proj * kGemmKinds + (few ? GEMM_TILE_COUNT : gemm_tile_kind(dt, m, n, k));
 }
 
+// Timing class of a sampler block's product with n_side columns beside it.
+int head_class(GemmProj proj, DType dt, int32_t m, int32_t width, int32_t n_side) {
+  if (dt != DType::BF16 || gemm_few_rows(dt, m)) return gemm_class(proj, dt, m, width, width);
+  return K_GEMM_FIRST + proj * kGemmKinds + head_tile_kind(m, width, n_side);
+}
+
 int attn_class(DType dt, const AttnArgs &a) {
   const bool seg2 = a.k2 != nullptr;
   if (dt != DType::BF16) return K_ATTN_W1;
@@ -945,7 +951,7 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
       const char *w1 = static_cast<const char *>(w->w_1) + (size_t)k * W * W * es;
       const char *w2 = static_cast<const char *>(w->w_2) + (size_t)k * W * W * es;
       HeadSides sides[2] = {};
-      double side_n[2] = {0, 0};
+      int32_t side_n[2] = {0, 0};
       for (int g = 0; g < 2 && beside; ++g) {
         sides[g].ld = ML;
         // half of a chunk's 3 W columns to each of the block's products
@@ -959,17 +965,17 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
           const int f0 = 2 * tw * q / nq, f1 = 2 * tw * (q + 1) / nq;
           sides[g].s[1] = mod_cols(sc_i, 3 * nb * W + f0 * 128, (f1 - f0) * 128);
         }
-        side_n[g] = (double)sides[g].s[0].n + sides[g].s[1].n;
+        side_n[g] = sides[g].s[0].n + sides[g].s[1].n;
       }
-      LAUNCH(gemm_class(P_HEAD_SILU, dt, M, W, W), 2.0 * M * (W + side_n[0]) * W,
-             es * (2.0 * M * W + (double)W * W + side_n[0] * (W + M)),
+      LAUNCH(head_class(P_HEAD_SILU, dt, M, W, side_n[0]), 2.0 * M * (W + side_n[0]) * W,
+             es * (2.0 * M * W + (double)W * W + (double)side_n[0] * (W + M)),
              norm_in ? launch_head_gemm_norm_silu(hbuf, mod, ML, 3 * k * W, (3 * k + 1) * W,
                                                   hd->ln_eps, w1, fp(w->b_1) + (size_t)k * W, M, W,
                                                   ybuf, sides[0], stream)
                      : launch_head_gemm_silu(dt, abuf, w1, fp(w->b_1) + (size_t)k * W, M, W, ybuf,
                                              sides[0], stream));
-      LAUNCH(gemm_class(P_HEAD, dt, M, W, W), 2.0 * M * (W + side_n[1]) * W,
-             es * (2.0 * M * W + (double)W * W + side_n[1] * (W + M)) + 8.0 * M * W,
+      LAUNCH(head_class(P_HEAD, dt, M, W, side_n[1]), 2.0 * M * (W + side_n[1]) * W,
+             es * (2.0 * M * W + (double)W * W + (double)side_n[1] * (W + M)) + 8.0 * M * W,
              launch_head_gemm_gate(dt, ybuf, w2, fp(w->b_2) + (size_t)k * W, M, W, hbuf,
                                    static_cast<const char *>(mod) + (size_t)(3 * k + 2) * W * es,
                                    ML, sides[1], stream));

@@ -145,9 +145,10 @@ def test_segment_shapes(case):
 
 # (rows, width, blocks, sampling steps, channels, dtype): the few-row kernel with
 # 16, 32 and 64 rows (up to 16, as far as they fit, norming their own
-# activations), the 64x128 tile with a ragged last tile, row counts whose
-# modulations no longer fit beside the block products, one block (no
-# side products) and two, one to three sampling steps, other channel counts.
+# activations), the 32x64, 64x64 and 64x128 tiles with side products and a
+# ragged last tile, row counts whose modulations no longer fit beside the block
+# products, one block (no side products) and two, one to three sampling steps,
+# other channel counts.
 SAMPLER = [
     (1, 256, 2, 3, 16, "bf16"),
     (16, 512, 3, 2, 16, "bf16"),
@@ -157,6 +158,8 @@ SAMPLER = [
     (33, 768, 2, 1, 16, "bf16"),
     (64, 256, 5, 3, 33, "bf16"),
     (65, 512, 2, 3, 16, "bf16"),
+    (200, 1024, 2, 2, 16, "bf16"),
+    (300, 1024, 2, 2, 16, "bf16"),
     (200, 256, 1, 2, 16, "bf16"),
     (1500, 1280, 3, 2, 16, "bf16"),
     (5, 256, 2, 3, 16, "f32"),
