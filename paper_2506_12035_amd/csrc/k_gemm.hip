@@ -16,7 +16,7 @@
 // 64 x 64 to 32 x 32 for a few hundred rows.
 // All load operands straight from global memory into XOR-swizzled LDS stages
 // and write back through LDS in row-major order.  The sampler's products on up
-// to 64 rows have a kernel of their own.
+// to 40 rows have a kernel of their own.
 //
 // fp32 path: fp32 matrix instructions, a 64x64 tile or, for few rows, a
 // workgroup per 16 columns whose wavefronts split K.
@@ -1438,7 +1438,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, c
 
 // ------------------------------------------------------------------ few rows
 //
-// The sampler's products on up to 64 rows (a few images' generating tokens):
+// The sampler's products on up to 40 rows (a few images' generating tokens):
 // such a product is its weights streamed once, and its time the
 // latency of one workgroup's walk over K (the 64x128 tile gave 5 rows x 1280
 // x 1280 ten workgroups and 9.4 us).  A workgroup takes 16 columns; its eight
@@ -1656,7 +1656,10 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
   return best;
 }
 
-bool gemm_few_rows(DType dt, int32_t m) { return dt == DType::BF16 && m <= 64; }
+// Up to 40 rows: 50 steps of 8 blocks of width 1280 measured 7.0 ms against
+// 7.5 on the 32x64 tiles with 33 rows, 7.7 against 7.6 with 48 and 8.4 against
+// 7.6 with 64.
+bool gemm_few_rows(DType dt, int32_t m) { return dt == DType::BF16 && m <= 40; }
 
 // The few-row kernel with the side products' tiles after the main ones.
 template <class Epi, bool SIDES>
