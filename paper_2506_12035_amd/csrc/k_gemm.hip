@@ -1113,8 +1113,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_mid_kernel(const bf16 *A, co
 
 // ------------------------------------------------------------------ 64x128 tile
 //
-// For products too small to spread 128x256 tiles over the chip (the sampler's
-// MLP on a few hundred rows, a shard of a few images): a 64x128x128 tile on
+// For products of several hundred rows that larger tiles would not spread over
+// the chip (the sampler's block products on 512 rows): a 64x128x128 tile on
 // four wavefronts of 32x64 (2 accumulator blocks).  With so little work per
 // workgroup its time is the serial chain of k-tiles (barrier, LDS round trip,
 // dependent MFMAs), not bandwidth, so the k-tile is long: three 48 KB stages
