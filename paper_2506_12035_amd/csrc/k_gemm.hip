@@ -1752,11 +1752,16 @@ static hipError_t run_bf16(const void *a, const void *w, int m, int n, int k, co
 //    the MFMA registers (64-byte row segments, every load of a wavefront
 //    independent of the others) and sum their partial tiles through LDS in
 //    wavefront order.
-// The split depends on K alone, so a row's result does not depend on how many
-// rows share the call within either kernel.
+// Which of them runs depends on M, and an image's rows must not depend on the
+// images that share its call.  So both add up an output in one order, which
+// depends on K alone: 16 slices of K, each from zero and added to the sum of
+// those before it; inside a slice 16 k at a time, element e of the four
+// 16-byte chunks in turn for e = 0 .. 3.  (The matrix instructions add their
+// products one by one in ascending k, so 32x32x2 on chunk pairs (0, 1), (2, 3)
+// continues the sum as 16x16x4 on all four does.)
 namespace f32 {
 
-constexpr int kWaves = 16;  // K slices of the skinny kernel
+constexpr int kWaves = 16;  // K slices; the skinny kernel has a wavefront for each
 
 __device__ __forceinline__ f32x4 mfma4(const f32x4 &w, const f32x4 &x, f32x4 acc) {
 #pragma unroll
@@ -1831,9 +1836,9 @@ __global__ __launch_bounds__(1024) void gemm_f32_skinny_kernel(const float *__re
   epi.store(r, row, c, v);
 }
 
-// A 64x64x32 tile; `Frag`s are 16-byte chunks of 32 rows, as in the bf16 tiles.
+// A 64x64x32 tile (K a multiple of 256: whole steps in every slice).
 template <class Epi>
-__global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const float *A, const float *W, int M,
+__global__ __launch_bounds__(256, 2) void gemm_f32_tile_kernel(const float *A, const float *W, int M,
                                                             int N, int K, Epi epi) {
   using Row = typename Epi::Row;
   constexpr int T = 64, NS = 4;
@@ -1851,7 +1856,7 @@ __global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const float *A, cons
   const int wm = wave >> 1, wn = wave & 1;
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
   const int nk = K / 32;
-  // a k-tile of 32 floats is 64 16-bit elements to the loader
+  // a k-tile of 32 floats (two steps of 16) is 64 16-bit elements to the loader
   const bf16 *A2 = reinterpret_cast<const bf16 *>(A), *W2 = reinterpret_cast<const bf16 *>(W);
   auto load_tile = [&](int t) {
     const unsigned sb = lds0 + (unsigned)(t % NS) * kStage;
@@ -1864,33 +1869,72 @@ __global__ __launch_bounds__(256) void gemm_f32_tile_kernel(const float *A, cons
   Row rec{};
   if (tid < T) rec = epi.row(min(m0 + tid, M - 1));
   const f32x4 bias = epi.bias4(n0 + wn * 32 + (lane & 7) * 4);
-  f32x16 acc[1][1] = {{f32x16{}}};
+  const int rx = wm * 32 + (lane & 31), rw = wn * 32 + (lane & 31);
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t)
     if (t < nk) load_tile(t);
-  for (int t = 0; t < nk; ++t) {
-    // k-tile t landed (issued so far: up to t + NS - 2, four loads each) and
-    // every wavefront done with k-tile t - 1, whose stage takes t + NS - 1
-    const int ahead = min(NS - 2, nk - 1 - t);
-    if (ahead >= 2) big::barrier_vm<8>();
-    else if (ahead == 1) big::barrier_vm<4>();
-    else big::barrier_vm<0>();
-    if (t + NS - 1 < nk) load_tile(t + NS - 1);
-    const unsigned char *sc = smem + (t % NS) * kStage;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int kc = s * 2 + (lane >> 5);
-      const int rx = wm * 32 + (lane & 31), rw = wn * 32 + (lane & 31);
-      const f32x4 x = *reinterpret_cast<const f32x4 *>(sc + rx * 128 + big::swz(rx, kc) * 16);
-      const f32x4 w = *reinterpret_cast<const f32x4 *>(sc + kWOff + rw * 128 + big::swz(rw, kc) * 16);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[e], x[e], acc[0][0], 0, 0, 0);
+  // This half's chunks of the pairs (0, 1) and (2, 3) of a step, read one step
+  // ahead.
+  struct Frag {
+    f32x4 x[2], w[2];
+  };
+  const int steps = K / 16;
+  auto read = [&](int s) {
+    if ((s & 1) == 0) {
+      // k-tile t landed (issued so far: up to t + NS - 2, four loads each) and
+      // every wavefront done with k-tile t - 1, whose stage takes t + NS - 1
+      const int t = s >> 1, ahead = min(NS - 2, nk - 1 - t);
+      if (ahead >= 2) big::barrier_vm<8>();
+      else if (ahead == 1) big::barrier_vm<4>();
+      else big::barrier_vm<0>();
+      if (t + NS - 1 < nk) load_tile(t + NS - 1);
     }
+    const unsigned char *sc = smem + ((s >> 1) % NS) * kStage;
+    Frag f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int kc = (s & 1) * 4 + u * 2 + (lane >> 5);
+      f.x[u] = *reinterpret_cast<const f32x4 *>(sc + rx * 128 + big::swz(rx, kc) * 16);
+      f.w[u] = *reinterpret_cast<const f32x4 *>(sc + kWOff + rw * 128 + big::swz(rw, kc) * 16);
+    }
+    return f;
+  };
+  // One slice into `c`.  Two accumulators take the slices in turn, so that the
+  // one before, `done`, is added to the sum beside the MFMAs of this one: a
+  // layer of 2480 rows at D = 768 takes 476 us, with a single accumulator (read,
+  // added and cleared between two slices) 504, in one sum over all of K 447.
+  // Two wavefronts per SIMD as the launch bound keep the accumulators in VGPRs,
+  // which the additions can read.  The sum starts at -0, which leaves the first
+  // slice's bits alone.
+  f32x16 acc[2], sum[1][1];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) sum[0][0][e] = acc[1][e] = -0.0f;
+  int s = 0;
+  Frag f = read(0);
+  auto step = [&](f32x16 &c, const f32x16 &c0) {
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(f.w[0][0], f.x[0][0], c0, 0, 0, 0);
+    big::pin();
+    const Frag next = read(min(++s, steps - 1));  // (the last is odd: read again, no barrier)
+    big::pin();
+#pragma unroll
+    for (int i = 1; i < 8; ++i)
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(f.w[i & 1][i >> 1], f.x[i & 1][i >> 1], c, 0, 0, 0);
+    f = next;
+  };
+  auto slice = [&](f32x16 &c, const f32x16 &done) {
+    step(c, f32x16{});
+    sum[0][0] += done;
+    for (int j = 1; j < steps / f32::kWaves; ++j) step(c, c);
+  };
+#pragma unroll 1
+  for (int g = 0; g < f32::kWaves; g += 2) {
+    slice(acc[0], acc[1]);
+    slice(acc[1], acc[0]);
   }
+  sum[0][0] += acc[1];
   if (tid < T) rows_lds[tid] = rec;
   big::barrier_vm<0>();
-  write_back_staged<1, 1, 4>(acc, epi, m0 + wm * 32, n0 + wn * 32, M, lane,
+  write_back_staged<1, 1, 4>(sum, epi, m0 + wm * 32, n0 + wn * 32, M, lane,
                              reinterpret_cast<float *>(smem) + wave * 32 * kStr, rows_lds + wm * 32,
                              bias);
 }
@@ -1902,9 +1946,10 @@ static hipError_t run_f32(const void *a, const void *w, int m, int n, int k, con
   if (n % 64 != 0 || k % 32 != 0) return hipErrorInvalidValue;
   const float *A = static_cast<const float *>(a), *W = static_cast<const float *>(w);
   const long tiles = (long)((m + 63) / 64) * (n / 64);
-  // 64x64 tiles once every compute unit has one; below that the skinny kernel,
-  // with as few rows per workgroup as cover a small M
-  if (tiles >= device_cu_count())
+  // 64x64 tiles once every compute unit has one (and K is the model's: a time
+  // embedding's may be any multiple of 64); else the skinny kernel, with as
+  // few rows per workgroup as cover a small M
+  if (tiles >= device_cu_count() && k % 256 == 0)
     launch_kernel(gemm_f32_tile_kernel<Epi>, (unsigned)tiles, 256, 0, s, A, W, m, n, k, epi);
   else if (m <= 16)
     launch_kernel(gemm_f32_skinny_kernel<Epi, 1>, n / 16, 1024, 0, s, A, W, m, n, k, epi);

@@ -2,9 +2,10 @@
 its own HIP stream (marche_step_images), against the whole batch in one call.
 
 Images are independent and every kernel computes a row (or an image and head)
-the same way whatever else shares the launch, so the KV cache and the
-residual stream must match bit for bit over full and cache-aware steps, with
-the ranges overlapping on the GPU or run one after another."""
+the same way whatever else shares the launch -- where the number of rows picks
+another kernel, that one sums in the same order -- so the KV cache and the
+residual stream must match bit for bit over full and cache-aware steps, in bf16
+and fp32, with the ranges overlapping on the GPU or run one after another."""
 import pytest
 import torch
 
@@ -146,3 +147,48 @@ def test_step_images_touches_only_its_range():
     assert torch.equal(x_part[2:], x_all[2:])
     assert torch.equal(k_part[:, 2:], k_all[:, 2:]) and torch.equal(v_part[:, 2:], v_all[:, 2:])
     assert not torch.equal(x_part[2:], x0[2:])  # the range was really computed
+
+
+def _layer_ranges(cfg, sizes, cuts, want_scores=True):
+    """One block over images with ragged lists, in one call and as the ranges
+    that `cuts` makes of the images: the same bits of x and both caches (and
+    of the scores, where asked for)."""
+    import numpy as np
+    from tests.gpu_util import SingleLayer
+
+    say(f"layer ranges: {cfg.name} N={cfg.n_tokens} sizes={sizes[:6]}.. cuts={cuts}")
+    rng = np.random.default_rng(sum(sizes) + cfg.n_tokens)
+    B, N = len(sizes), cfg.n_tokens
+    x = rng.standard_normal((B, N, cfg.d_model), dtype=np.float32)
+    k, v = (workload.round_to(rng.standard_normal((B, cfg.n_heads, N, cfg.head_dim), dtype=np.float32),
+                              cfg.dtype) for _ in range(2))
+    act = [rng.permutation(N)[:s].astype(np.int32) for s in sizes]
+    gens = [min(5, s) for s in sizes]
+    p = workload.layer_weights(cfg, 0)
+    ref = SingleLayer(cfg, p, x, k, v).run(act, gens, want_scores)
+    for a, b in zip([0] + cuts, cuts + [B]):
+        got = SingleLayer(cfg, p, x[a:b], k[a:b], v[a:b]).run(act[a:b], gens[a:b], want_scores)
+        for name in ("x", "k", "v") + (("scores",) if want_scores else ()):
+            assert np.array_equal(got[name], ref[name][a:b]), f"{name} of images {a}..{b - 1}"
+    assert not np.array_equal(ref["x"], x)
+
+
+# (d_model, heads, head_dim, d_mlp, N, active rows per image, first images of the
+# ranges).  Whole batches of 2560 and 1335 rows take the 64x64 tile in every
+# product (K = 256, 768, 3072: slices of 16, 48 and 192), their ranges down to
+# one image the kernel that splits K over wavefronts.
+F32_RANGES = [
+    (768, 12, 64, 3072, 320, [320] * 8, [4]),
+    (768, 12, 64, 3072, 320, [320] * 8, [1]),
+    (256, 4, 64, 1024, 190, [190] * 24 + [5], [2, 24]),
+    (1280, 16, 80, 512, 203, [203] * 6 + [3, 41], [1, 6, 7]),
+]
+
+
+@pytest.mark.parametrize("case", F32_RANGES, ids=lambda c: f"d{c[0]}n{c[4]}b{len(c[5])}r{len(c[6]) + 1}")
+def test_f32_ranges_match_the_whole_batch(case):
+    """fp32 products take one of two kernels by their number of rows; an
+    image's rows are summed in the same order by both."""
+    d, h, dh, f, n, sizes, cuts = case
+    cfg = workload.Config(63, "f32-ranges", 1, d, h, dh, f, n, 0, len(sizes), "f32")
+    _layer_ranges(cfg, sizes, cuts)
