@@ -345,6 +345,7 @@ marche_status_t marche_encoder_to_decoder(float *x_dec, const float *x_enc, cons
  *   x0 = (x - sqrt(1 - ab_i) eps(x, i, z)) / sqrt(ab_i),
  *   x = posterior mean(x0, x) + temperature * sqrt(posterior variance) * noise[i]
  * (no noise at i = 0); the final x goes to tok_out[out_rows[i]] (c_tok floats).
+ * A row's result is bit for bit the same whichever rows share its call.
  * noise [n_steps + 1][n_rows][c_tok] float32 (caller-drawn, device);
  * rows, out_rows [n_rows] int32 (device).
  * Weights: w_t1 [W][t_freq], w_t2 [W][W], w_c [W][d_cond], w_ada [(3n+2)W][W],

@@ -41,6 +41,33 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return v;
 }
 
+// LayerNorm of a sampler row, a = LN(h) (1 + scale) + shift.  Three kernels form
+// it, with the row spread differently; so that a row's result does not depend
+// on which of them its call takes, all sum in one order -- column c first over
+// the 256-column groups into lane sums t = c mod 256, those pairwise (t with
+// t ^ 1, ^ 2, .. ^ 128) -- and share the operations below, which the compiler may not
+// contract differently from one kernel to the next.
+__device__ __forceinline__ float norm_mean(float sum, float inv_w) {
+#pragma clang fp contract(off)
+  return sum * inv_w;
+}
+__device__ __forceinline__ float norm_centre(float v, float mean) {
+#pragma clang fp contract(off)
+  return v - mean;
+}
+__device__ __forceinline__ float norm_rstd(float sum_sq, float inv_w, float eps) {
+#pragma clang fp contract(off)
+  return 1.0f / sqrtf(fmaf(sum_sq, inv_w, eps));
+}
+__device__ __forceinline__ float norm_mod(float centred, float rstd, float scale, float shift) {
+#pragma clang fp contract(off)
+  return fmaf(centred * rstd, 1.0f + scale, shift);
+}
+// The pairwise part where lane l of a wavefront holds t = 4 l .. 4 l + 3.
+__device__ __forceinline__ float norm_sum4(float a, float b, float c, float d) {
+  return wave_sum_dpp((a + b) + (c + d));
+}
+
 // Exact-erf GELU, z * Phi(z), written as max(z, 0) - |z| * Phi(-|z|) (the two
 // agree for either sign of z).  The normal tail is Phi(-a) = 2^P(min(a, 6)),
 // P(u) = c0 + c1 u + ... + c7 u^7 a polynomial fit to log2 Phi(-u) on [0, 6]

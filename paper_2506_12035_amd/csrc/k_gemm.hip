@@ -1441,14 +1441,28 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, c
 // The sampler's products on up to 40 rows (a few images' generating tokens):
 // such a product is its weights streamed once, and its time the
 // latency of one workgroup's walk over K (the 64x128 tile gave 5 rows x 1280
-// x 1280 ten workgroups and 9.4 us).  A workgroup takes 16 columns; its eight
-// wavefronts split K, load both operands straight into the MFMA registers
-// (64-byte row segments, all of a wavefront's loads independent) and add
-// their partial tiles through LDS in wavefront order.
+// x 1280 ten workgroups and 9.4 us).  A workgroup takes 16 columns.  Its eight
+// wavefronts bring both operands into LDS, a stage of 256 k at a time with all
+// NS stages in flight from the start (K = 1280 in one go), laid out as the
+// MFMAs read them; wavefront i then multiplies the 16 rows of block i, one
+// ascending sum over K, reading the next stage beside the MFMAs of the present
+// one.  That is the order of every tile (the matrix instructions add their
+// products one by one in ascending k, whatever their shape), so a row's result
+// does not depend on how many rows share its call.  With K split over the
+// wavefronts and their partial tiles added it did; 15 steps of 4 blocks of
+// width 1280 then took 735 us with 5 rows, 1003 with 24 and 1136 with 33, and
+// take 773, 972 and 1063.
 namespace rows16 {
 
 constexpr int kWaves = 8;
 constexpr int kBN = 16;
+constexpr int kSteps = 8;              // steps of 32 k per stage, one per wavefront
+constexpr int kPart = kSteps * 1024;   // bytes of a stage per 16 rows or columns
+
+// Stages in flight: five take K = 1280 whole; with three row blocks only four
+// fit the CU's LDS.  (Two and three blocks on three stages, which lets two
+// workgroups share a CU: 7% slower at width 1280, 3% faster to 25% slower above.)
+__host__ __device__ constexpr int stages(int mb) { return mb < 3 ? 5 : 4; }
 
 // The activations of a block's first product are the modulated norm of h,
 // a = LN(h) (1 + scale) + shift.  With up to 16 rows every workgroup forms them
@@ -1469,12 +1483,12 @@ __device__ __forceinline__ void norm_rows(const NormIn &in, int M, int K, bf16 *
                                           int lane) {
   constexpr int NV = 16;  // K <= 4096: float4 chunks per lane
   const int nv = K / 256;
+  const float inv_w = 1.0f / (float)K;
   for (int r = wave; r < M; r += kWaves) {
     const f32x4 *hr = reinterpret_cast<const f32x4 *>(in.h + (size_t)r * K);
     const bf16 *sh = in.shift + (size_t)r * in.mod_ld, *sc = in.scale + (size_t)r * in.mod_ld;
-    f32x4 v[NV];
+    f32x4 v[NV], t = f32x4{};
     bf16x4 a[NV], b[NV];
-    float s = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k)
       if (k < nv) {
@@ -1485,100 +1499,124 @@ __device__ __forceinline__ void norm_rows(const NormIn &in, int M, int K, bf16 *
     big::pin();
 #pragma unroll
     for (int k = 0; k < NV; ++k)
-      if (k < nv) s += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
-    const float mean = wave_sum_dpp(s) / (float)K;
-    float ss = 0.f;
+      if (k < nv) t += v[k];
+    const float mean = norm_mean(norm_sum4(t[0], t[1], t[2], t[3]), inv_w);
+    t = f32x4{};
 #pragma unroll
     for (int k = 0; k < NV; ++k)
       if (k < nv) {
-        v[k] -= mean;
-        ss += (v[k][0] * v[k][0] + v[k][1] * v[k][1]) + (v[k][2] * v[k][2] + v[k][3] * v[k][3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[k][e] = norm_centre(v[k][e], mean);
+          t[e] = fmaf(v[k][e], v[k][e], t[e]);
+        }
       }
-    const float rstd = 1.0f / sqrtf(wave_sum_dpp(ss) / (float)K + in.eps);
+    const float rstd = norm_rstd(norm_sum4(t[0], t[1], t[2], t[3]), inv_w, in.eps);
 #pragma unroll
     for (int k = 0; k < NV; ++k)
       if (k < nv) {
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          o[e] = (bf16)(v[k][e] * rstd * (1.f + (float)a[k][e]) + (float)b[k][e]);
+          o[e] = (bf16)norm_mod(v[k][e], rstd, (float)a[k][e], (float)b[k][e]);
         *reinterpret_cast<bf16x4 *>(lds + (size_t)r * (K + 8) + 4 * (lane + 64 * k)) = o;
       }
   }
 }
 
-// The 16 columns from n0 of the whole M <= MB * 16 rows.  NORM (MB = 1): the
-// activations come from `in` through `lds`.
+// Bytes of LDS: the stages in flight of the weights and MB row blocks, or
+// (NORM) of the weights, then the whole activations.
+inline uint32_t smem_bytes(int mb, bool norm, int m, int k) {
+  const int ns = std::min(stages(mb), k / (32 * kSteps));
+  const int plain = ns * (1 + mb) * kPart, with = ns * kPart + m * (k + 8) * 2;
+  return (uint32_t)(norm ? std::max(plain, with) : plain);  // (side products are plain)
+}
+
+// The 16 columns from n0 of the whole M <= MB * 16 rows, K a multiple of a
+// stage.  NORM (MB = 1): the
+// activations come from `in`.
 template <class Epi, int MB, bool NORM>
-__device__ __forceinline__ void tile(const bf16 *__restrict__ A, const bf16 *__restrict__ W, int M,
-                                     int K, const Epi epi, int n0, f32x4 (*part)[MB][64],
-                                     const NormIn &in, bf16 *lds) {
+__device__ __forceinline__ void tile(const bf16 *A, const bf16 *W, int M, int K, const Epi &epi,
+                                     int n0, unsigned char *smem, const NormIn &in) {
   static_assert(!NORM || MB == 1, "one row block");
+  constexpr int NS = stages(MB), L = NORM ? 1 : 1 + MB, kStage = L * kPart;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int steps = K / 32;  // of 32 k; wavefront w takes [w S / 8, (w + 1) S / 8)
-  const int s0 = wave * steps / kWaves, s1 = (wave + 1) * steps / kWaves;
-  const int kl = (lane >> 4) * 8;
-  const bf16 *wp = W + (size_t)(n0 + (lane & 15)) * K + kl;
-  const bf16 *xp[MB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) {
-    const int row = min(i * 16 + (lane & 15), M - 1);
-    xp[i] = NORM ? lds + (size_t)row * (K + 8) + kl : A + (size_t)row * K + kl;
-  }
-  f32x4 acc[MB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) acc[i] = f32x4{};
-  constexpr int U = 5;  // steps whose loads are in flight together
-  int s = s0;
-  bf16x8 w[U];
-  if constexpr (NORM) {
-    // the first weights are on their way while the activations are formed
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      w[u] = *reinterpret_cast<const bf16x8 *>(wp + min(s + u, steps - 1) * 32);
-    big::pin();
-    norm_rows(in, M, K, lds, wave, lane);
-    __syncthreads();
-  }
-  for (; s + U <= s1; s += U) {
-    bf16x8 x[U][MB];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (!NORM || s > s0) w[u] = *reinterpret_cast<const bf16x8 *>(wp + (s + u) * 32);
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-        x[u][i] = *reinterpret_cast<const bf16x8 *>(xp[i] + (s + u) * 32);
-    }
-    big::pin();  // every load before the first MFMA's wait
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[u], x[u][i], acc[i], 0, 0, 0);
-  }
-  for (; s < s1; ++s) {
-    const bf16x8 w1 = *reinterpret_cast<const bf16x8 *>(wp + s * 32);
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-          w1, *reinterpret_cast<const bf16x8 *>(xp[i] + s * 32), acc[i], 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < MB; ++i) part[wave][i][lane] = acc[i];
-  __syncthreads();
-  if (wave >= MB) return;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
+  const int nst = K / (32 * kSteps);
+  const int kl = (lane >> 4) * 8;  // MFMA operands: row or column lane % 16, k kl .. kl + 7
+
+  // what the results are combined with, on its way before the operands
   const int row = wave * 16 + (lane & 15), c0 = n0 + (lane >> 4) * 4;
-  const typename Epi::Col c = epi.col(c0);  // uniform parts: before the row guard
-  if (row >= M) return;
-  const typename Epi::Row r = epi.row(row);
-  f32x4 v = epi.bias4(c0);
-  typename Epi::Prior pr;
-  if constexpr (Epi::kPrior) pr = epi.prior(r, c);
-  f32x4 t = part[0][wave][lane];
+  typename Epi::Col col{};
+  typename Epi::Row rec{};
+  typename Epi::Prior pr{};
+  f32x4 bias{};
+  if (wave < MB) {
+    col = epi.col(c0);
+    rec = epi.row(min(row, M - 1));
+    bias = epi.bias4(c0);
+    if constexpr (Epi::kPrior) pr = epi.prior(rec, col);
+  }
+
+  // Step `wave` of stage t, in slot t % NS: lane l's 16 bytes of the weights,
+  // then of each row block, at 16 l.  Rows past M repeat row M - 1 (not stored).
+  uint32_t off[L];
 #pragma unroll
-  for (int g = 1; g < kWaves; ++g) t += part[g][wave][lane];
-  epi.store(r, row, c, epi.combine(t + v, pr));
+  for (int i = 0; i < L; ++i)
+    off[i] = (uint32_t)((i == 0 ? lane & 15 : min((i - 1) * 16 + (lane & 15), M - 1)) * K + kl) * 2u;
+  auto load = [&](int t) {
+    const unsigned at = lds0 + (unsigned)(t % NS) * kStage + wave * 1024;
+    const int k0 = (t * kSteps + wave) * 32;
+#pragma unroll
+    for (int i = 0; i < L; ++i)
+      t320::load_lds(at + i * kPart, (i == 0 ? W + (size_t)n0 * K : A) + k0, off[i]);
+  };
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    if (t < nst) load(t);
+  bf16 *acts = reinterpret_cast<bf16 *>(smem + min(NS, nst) * kStage);  // NORM
+  if constexpr (NORM) {
+    norm_rows(in, M, K, acts, wave, lane);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  }
+  bf16x8 w[kSteps], x[kSteps];
+  const bf16 *ap = acts + (size_t)min(lane & 15, M - 1) * (K + 8) + kl;
+  auto read = [&](int t, int s) {
+    const unsigned char *sp = smem + (t % NS) * kStage + s * 1024 + lane * 16;
+    w[s] = *reinterpret_cast<const bf16x8 *>(sp);
+    if constexpr (NORM) x[s] = *reinterpret_cast<const bf16x8 *>(ap + (t * kSteps + s) * 32);
+    else x[s] = *reinterpret_cast<const bf16x8 *>(sp + (1 + wave) * kPart);
+  };
+  f32x4 acc{};
+  // stage 0 landed; the others issued may still be on their way
+  mid::barrier_tiles<L, NS - 1>(min(nst, NS) - 1);
+  if (wave < MB) {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) read(0, s);
+  }
+  for (int t = 0; t + 1 < nst; ++t) {
+    // stage t + 1 landed.  Issued after it: min(nst, NS) - 2 stages at first,
+    // then up to NS - 3, as slots come free one at a time -- stage t - 1's now,
+    // which was read, and its MFMAs issued, before this barrier.
+    mid::barrier_tiles<L, NS - 2>(t == 0 ? min(nst, NS) - 2 : min(nst - 2 - t, NS - 3));
+    big::pin();
+    if (t > 0 && t - 1 + NS < nst) load(t - 1 + NS);
+    if (wave < MB) {
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s], x[s], acc, 0, 0, 0);
+        read(t + 1, s);
+        big::pin();
+      }
+    }
+  }
+  if (wave < MB) {
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s], x[s], acc, 0, 0, 0);
+  }
+  if (wave < MB && row < M) epi.store(rec, row, col, epi.combine(acc + bias, pr));
 }
 
 }  // namespace rows16
@@ -1589,8 +1627,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
                                                              HeadSides sides,
                                                              rows16::NormIn in) {
   using namespace rows16;
-  __shared__ f32x4 part[kWaves][MB][64];
-  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_rows[];
   int id = blockIdx.x;
   if constexpr (SIDES) {
     const int main_tiles = N / kBN;
@@ -1601,11 +1638,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
       const EpiPlain<bf16, false> pe{{}, static_cast<bf16 *>(j.out), j.bias, sides.ld};
       tile<EpiPlain<bf16, false>, MB, false>(
           static_cast<const bf16 *>(j.a), static_cast<const bf16 *>(j.w), M, K, pe,
-          (id < first ? id : id - first) * kBN, part, in, nullptr);
+          (id < first ? id : id - first) * kBN, smem_rows, in);
       return;
     }
   }
-  tile<Epi, MB, NORM>(A, W, M, K, epi, id * kBN, part, in, reinterpret_cast<bf16 *>(dyn));
+  tile<Epi, MB, NORM>(A, W, M, K, epi, id * kBN, smem_rows, in);
 }
 
 // Tile choice by estimated time.  Every tile runs one workgroup per CU, so a
@@ -1659,7 +1696,10 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
 // Up to 40 rows: 50 steps of 8 blocks of width 1280 measured 7.0 ms against
 // 7.5 on the 32x64 tiles with 33 rows, 7.7 against 7.6 with 48 and 8.4 against
 // 7.6 with 64.
-bool gemm_few_rows(DType dt, int32_t m) { return dt == DType::BF16 && m <= 40; }
+// A time embedding whose length is no whole number of stages takes a tile.
+bool gemm_few_rows(DType dt, int32_t m, int32_t k) {
+  return dt == DType::BF16 && m <= 40 && k % (32 * rows16::kSteps) == 0;
+}
 
 // The few-row kernel with the side products' tiles after the main ones.
 template <class Epi, bool SIDES>
@@ -1667,15 +1707,13 @@ static void run_rows(const bf16 *A, const bf16 *W, int m, int n, int k, const Ep
                      const HeadSides &sides, hipStream_t s) {
   const int grid = (n + (SIDES ? sides.s[0].n + sides.s[1].n : 0)) / rows16::kBN;
   const rows16::NormIn none{};
-  if (m <= 16)
-    launch_kernel(gemm_bf16_rows_kernel<Epi, 1, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
-                  sides, none);
-  else if (m <= 32)
-    launch_kernel(gemm_bf16_rows_kernel<Epi, 2, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
-                  sides, none);
-  else
-    launch_kernel(gemm_bf16_rows_kernel<Epi, 4, SIDES, false>, grid, 512, 0, s, A, W, m, n, k, epi,
-                  sides, none);
+#define R_(MB)                                                                             \
+  launch_kernel(gemm_bf16_rows_kernel<Epi, MB, SIDES, false>, grid, 512,                   \
+                rows16::smem_bytes(MB, false, m, k), s, A, W, m, n, k, epi, sides, none)
+  if (m <= 16) R_(1);
+  else if (m <= 32) R_(2);
+  else R_(3);
+#undef R_
 }
 
 template <class Epi, int BM, int BN, int NS>
@@ -2006,8 +2044,8 @@ namespace marche {
 template <class Epi>
 static hipError_t run_plain(const void *a, const void *w, int m, int n, int k, const Epi &epi,
                             hipStream_t s) {
-  if (m == 0 || !gemm_few_rows(DType::BF16, m)) return run_bf16(a, w, m, n, k, epi, s);
-  if (n % 256 != 0 || k % 64 != 0) return hipErrorInvalidValue;
+  if (m == 0 || !gemm_few_rows(DType::BF16, m, k)) return run_bf16(a, w, m, n, k, epi, s);
+  if (n % 256 != 0) return hipErrorInvalidValue;
   run_rows<Epi, false>(static_cast<const bf16 *>(a), static_cast<const bf16 *>(w), m, n, k, epi,
                        HeadSides{}, s);
   return hipGetLastError();
@@ -2033,7 +2071,7 @@ int head_side_tiles(DType dt, int32_t m, int32_t width) {
   if (dt != DType::BF16 || m <= 0) return 0;
   // few rows: the launches stream weights, so a side product of any size only
   // adds its own bytes
-  if (gemm_few_rows(dt, m)) return 1 << 20;
+  if (gemm_few_rows(dt, m, width)) return 1 << 20;
   const int tiles_m = (m + small::kBM - 1) / small::kBM;
   return std::max(0, device_cu_count() / tiles_m - width / small::kBN);
 }
@@ -2067,7 +2105,7 @@ static hipError_t run_head(const void *a, const void *w, int m, int width, const
   if (n_side == 0) return run_plain(a, w, m, width, width, epi, s);
   if (width % 256 != 0 || sides.s[0].n % small::kBN != 0 || sides.s[1].n % small::kBN != 0)
     return hipErrorInvalidValue;
-  if (gemm_few_rows(DType::BF16, m)) {
+  if (gemm_few_rows(DType::BF16, m, width)) {
     run_rows<Epi, true>(A, W, m, width, width, epi, sides, s);
     return hipGetLastError();
   }
@@ -2108,7 +2146,7 @@ hipError_t launch_head_gemm_norm_silu(const float *h, const void *mod, int32_t m
   const rows16::NormIn in{h, mo + shift_off, mo + scale_off, mod_ld, eps};
   launch_kernel(gemm_bf16_rows_kernel<EpiPlain<bf16, true>, 1, true, true>,
                 (width + sides.s[0].n + sides.s[1].n) / rows16::kBN, 512,
-                (uint32_t)(m * (width + 8) * 2), s, nullptr, W, m, width, width, epi, sides, in);
+                rows16::smem_bytes(1, true, m, width), s, nullptr, W, m, width, width, epi, sides, in);
   return hipGetLastError();
 }
 

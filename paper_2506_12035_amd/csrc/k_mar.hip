@@ -274,22 +274,36 @@ __global__ __launch_bounds__(256) void head_mod_kernel(T *__restrict__ a_out,
                                                        int shift_off, int scale_off, int rows,
                                                        float eps) {
   constexpr int W = NV * 256;
+  constexpr float inv_w = 1.0f / W;
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= rows) return;
   const T *mr = mod + (size_t)r * mod_ld;
   const float4 *hr = reinterpret_cast<const float4 *>(h + (size_t)r * W);
-  float4 v[NV];
+  float4 v[NV], t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int k = 0; k < NV; ++k) v[k] = hr[lane + 64 * k];
-  const float rstd = centre_rstd<NV>(v, eps);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    t.x += v[k].x; t.y += v[k].y; t.z += v[k].z; t.w += v[k].w;
+  }
+  const float mean = norm_mean(norm_sum4(t.x, t.y, t.z, t.w), inv_w);
+  t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    v[k] = make_float4(norm_centre(v[k].x, mean), norm_centre(v[k].y, mean),
+                       norm_centre(v[k].z, mean), norm_centre(v[k].w, mean));
+    t = make_float4(fmaf(v[k].x, v[k].x, t.x), fmaf(v[k].y, v[k].y, t.y),
+                    fmaf(v[k].z, v[k].z, t.z), fmaf(v[k].w, v[k].w, t.w));
+  }
+  const float rstd = norm_rstd(norm_sum4(t.x, t.y, t.z, t.w), inv_w, eps);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int c = 4 * (lane + 64 * k);
     const float4 sh = load_row4(mr + shift_off + c), sc = load_row4(mr + scale_off + c);
-    store_row4(a_out + (size_t)r * W + c, v[k].x * rstd * (1.f + sc.x) + sh.x,
-               v[k].y * rstd * (1.f + sc.y) + sh.y, v[k].z * rstd * (1.f + sc.z) + sh.z,
-               v[k].w * rstd * (1.f + sc.w) + sh.w);
+    store_row4(a_out + (size_t)r * W + c, norm_mod(v[k].x, rstd, sc.x, sh.x),
+               norm_mod(v[k].y, rstd, sc.y, sh.y), norm_mod(v[k].z, rstd, sc.z, sh.z),
+               norm_mod(v[k].w, rstd, sc.w, sh.w));
   }
 }
 
@@ -388,16 +402,16 @@ __global__ __launch_bounds__(256) void head_step_kernel(HeadRows p) {
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) s += v[k];
-    const float mean = block_sum(s, red[0]) * inv_w;
+    const float mean = norm_mean(block_sum(s, red[0]), inv_w);
     float ss = 0.f;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      v[k] -= mean;
-      ss += v[k] * v[k];
+      v[k] = norm_centre(v[k], mean);
+      ss = fmaf(v[k], v[k], ss);
     }
-    const float rstd = 1.0f / sqrtf(block_sum(ss, red[1]) * inv_w + p.eps);
+    const float rstd = norm_rstd(block_sum(ss, red[1]), inv_w, p.eps);
 #pragma unroll
-    for (int k = 0; k < NV; ++k) as[tid + 256 * k] = v[k] * rstd * (1.f + fsc[k]) + fsh[k];
+    for (int k = 0; k < NV; ++k) as[tid + 256 * k] = norm_mod(v[k], rstd, fsc[k], fsh[k]);
     __syncthreads();
     float acc[CW];
 #pragma unroll
@@ -458,18 +472,18 @@ __global__ __launch_bounds__(256) void head_step_kernel(HeadRows p) {
       s += h;
     }
     if (p.a) {
-      const float mean = block_sum(s, red[2]) * inv_w;
+      const float mean = norm_mean(block_sum(s, red[2]), inv_w);
       float ss = 0.f;
 #pragma unroll
       for (int k = 0; k < NV; ++k) {
-        v[k] -= mean;
-        ss += v[k] * v[k];
+        v[k] = norm_centre(v[k], mean);
+        ss = fmaf(v[k], v[k], ss);
       }
-      const float rstd = 1.0f / sqrtf(block_sum(ss, red[3]) * inv_w + p.eps);
+      const float rstd = norm_rstd(block_sum(ss, red[3]), inv_w, p.eps);
       T *ar = static_cast<T *>(p.a) + (size_t)r * W;
 #pragma unroll
       for (int k = 0; k < NV; ++k)
-        ar[tid + 256 * k] = from_f32<T>(v[k] * rstd * (1.f + sc0[k]) + sh0[k]);
+        ar[tid + 256 * k] = from_f32<T>(norm_mod(v[k], rstd, sc0[k], sh0[k]));
     }
   }
   if (p.sc) {

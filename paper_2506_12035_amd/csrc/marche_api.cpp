@@ -152,13 +152,13 @@ const char *class_name(int i) {
 
 // Timing class of a GEMM launch.
 int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k) {
-  const bool few = (proj == P_HEAD || proj == P_HEAD_SILU) && gemm_few_rows(dt, m);
+  const bool few = (proj == P_HEAD || proj == P_HEAD_SILU) && gemm_few_rows(dt, m, k);
   return K_GEMM_FIRST + proj * kGemmKinds + (few ? GEMM_TILE_COUNT : gemm_tile_kind(dt, m, n, k));
 }
 
 // Timing class of a sampler block's product with n_side columns beside it.
 int head_class(GemmProj proj, DType dt, int32_t m, int32_t width, int32_t n_side) {
-  if (dt != DType::BF16 || gemm_few_rows(dt, m)) return gemm_class(proj, dt, m, width, width);
+  if (dt != DType::BF16 || gemm_few_rows(dt, m, width)) return gemm_class(proj, dt, m, width, width);
   return K_GEMM_FIRST + proj * kGemmKinds + head_tile_kind(m, width, n_side);
 }
 

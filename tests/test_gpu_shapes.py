@@ -193,6 +193,45 @@ def test_sampler_shapes(case):
     assert np.isnan(got[np.setdiff1d(np.arange(got.shape[0]), out_rows)]).all()
 
 
+# (width, blocks, channels, dtype, rows of the whole call, rows of its parts): parts
+# on every kernel that a row count picks (norm inside the first product up to 16
+# rows as far as they fit, one to three row blocks of the few-row kernel, the
+# 32x64, 64x64 and 64x128 tiles, with and without side products), fp32 on both
+# sides of the 64x64 tile.
+SAMPLER_PARTS = [
+    (256, 3, 16, "bf16", 300, [1, 16, 17, 33, 41, 130]),
+    (1280, 2, 16, "bf16", 700, [1, 5, 15, 16, 17, 31, 40, 41, 64, 65, 129, 300]),
+    (2048, 2, 4, "bf16", 130, [2, 16, 32, 40]),
+    (1280, 1, 16, "bf16", 200, [3, 16, 20, 35, 60]),
+    (512, 2, 33, "f32", 1500, [1, 17, 40, 300]),
+]
+
+
+@pytest.mark.parametrize("case", SAMPLER_PARTS, ids=lambda c: "w{}n{}c{}-{}-m{}".format(*c))
+def test_sampler_rows_do_not_depend_on_the_call(case):
+    """The first rows of a call, sampled in a call of their own: bit for bit
+    the same values, whichever kernels the two row counts take."""
+    width, blocks, chans, dtype, rows, parts = case
+    tiny = workload.MAR_CONFIGS["tiny"]
+    B = rows // 100 + 2
+    mc = replace(tiny, dec=tiny.dec.with_(dtype=dtype, n_tokens=104, batch=B), head_width=width,
+                 head_blocks=blocks, sample_steps=3, c_tok=chans, head_std=0.04)
+    cfg = mc.dec
+    head, emb = workload.head_weights(mc), workload.mar_embeddings(mc)
+    rng = np.random.default_rng(rows + width)
+    x_dec = rng.standard_normal((B, cfg.n_tokens, cfg.d_model)).astype(np.float32)
+    cells = rng.choice(B * cfg.n_img, size=rows, replace=False)
+    out_rows = cells.astype(np.int32)
+    src = (cells // cfg.n_img * cfg.n_tokens + cfg.n_buf + cells % cfg.n_img).astype(np.int32)
+    noise = workload.head_noise(mc, rows, rows)
+    whole = _run_head(mc, head, emb, x_dec, src, out_rows, noise, 1.0)
+    for m in parts:
+        say(f"sampler width={width} {dtype}: {m} of {rows} rows")
+        got = _run_head(mc, head, emb, x_dec, src[:m], out_rows[:m],
+                        np.ascontiguousarray(noise[:, :m]), 1.0)
+        assert np.array_equal(got[out_rows[:m]], whole[out_rows[:m]]), m
+
+
 # (images, n_buf, n_img, n_known, d_model, channels).  64 images of 157 rows
 # give a wavefront five to ten rows of 512 columns (the last group ragged,
 # buffer and image rows within one group), two images one row; the channels sit
