@@ -1438,7 +1438,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_tiny_kernel(const bf16 *A, c
 
 // ------------------------------------------------------------------ few rows
 //
-// The sampler's products on up to 40 rows (a few images' generating tokens):
+// The sampler's products on up to 48 rows (a few images' generating tokens):
 // such a product is its weights streamed once, and its time the
 // latency of one workgroup's walk over K (the 64x128 tile gave 5 rows x 1280
 // x 1280 ten workgroups and 9.4 us).  A workgroup takes 16 columns.  Its eight
@@ -1693,12 +1693,19 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
   return best;
 }
 
-// Up to 40 rows: 50 steps of 8 blocks of width 1280 measured 7.0 ms against
-// 7.5 on the 32x64 tiles with 33 rows, 7.7 against 7.6 with 48 and 8.4 against
-// 7.6 with 64.
-// A time embedding whose length is no whole number of stages takes a tile.
-bool gemm_few_rows(DType dt, int32_t m, int32_t k) {
-  return dt == DType::BF16 && m <= 40 && k % (32 * rows16::kSteps) == 0;
+// Up to three blocks of 16 rows, as long as the launch's workgroups (16 of its
+// n columns each, side products among them) are resident at once: two per CU
+// with one row block (80 KB of LDS), one with two or three.  A sampling step in
+// us, this kernel / tiles: width 1280, 3 and 8 blocks: 5 rows 42 / 59 and 91 /
+// 142, 16 rows 49 / 61 and 114 / 147, 32 rows 53 / 62 and 127 / 151, 48 rows
+// 60 / 62 and 146 / 151; width 1536, 17 rows: 8 blocks (253 workgroups) 124 /
+// 162, 3 blocks (288) 66 / 67, 33 rows 81 / 67; width 2048, 3 blocks (384): 16
+// rows 82 / 82, 17 rows 92 / 82; width 4096 (768): 1 row 173 / 163, 16 rows
+// 206 / 166, 40 rows 314 / 183.  A time embedding whose length is no whole
+// number of stages takes a tile.  (Both give the same bits.)
+bool gemm_few_rows(DType dt, int32_t m, int32_t n, int32_t k) {
+  return dt == DType::BF16 && m <= 48 && k % (32 * rows16::kSteps) == 0 &&
+         n / rows16::kBN <= device_cu_count() * (m <= 16 ? 2 : 1);
 }
 
 // The few-row kernel with the side products' tiles after the main ones.
@@ -2044,7 +2051,7 @@ namespace marche {
 template <class Epi>
 static hipError_t run_plain(const void *a, const void *w, int m, int n, int k, const Epi &epi,
                             hipStream_t s) {
-  if (m == 0 || !gemm_few_rows(DType::BF16, m, k)) return run_bf16(a, w, m, n, k, epi, s);
+  if (m == 0 || !gemm_few_rows(DType::BF16, m, n, k)) return run_bf16(a, w, m, n, k, epi, s);
   if (n % 256 != 0) return hipErrorInvalidValue;
   run_rows<Epi, false>(static_cast<const bf16 *>(a), static_cast<const bf16 *>(w), m, n, k, epi,
                        HeadSides{}, s);
@@ -2069,9 +2076,6 @@ hipError_t launch_gemm_plain(DType dt, const void *a, const void *w, const float
 
 int head_side_tiles(DType dt, int32_t m, int32_t width) {
   if (dt != DType::BF16 || m <= 0) return 0;
-  // few rows: the launches stream weights, so a side product of any size only
-  // adds its own bytes
-  if (gemm_few_rows(dt, m, width)) return 1 << 20;
   const int tiles_m = (m + small::kBM - 1) / small::kBM;
   return std::max(0, device_cu_count() / tiles_m - width / small::kBN);
 }
@@ -2105,7 +2109,7 @@ static hipError_t run_head(const void *a, const void *w, int m, int width, const
   if (n_side == 0) return run_plain(a, w, m, width, width, epi, s);
   if (width % 256 != 0 || sides.s[0].n % small::kBN != 0 || sides.s[1].n % small::kBN != 0)
     return hipErrorInvalidValue;
-  if (gemm_few_rows(DType::BF16, m, width)) {
+  if (gemm_few_rows(DType::BF16, m, width + n_side, width)) {
     run_rows<Epi, true>(A, W, m, width, width, epi, sides, s);
     return hipGetLastError();
   }

@@ -152,13 +152,14 @@ const char *class_name(int i) {
 
 // Timing class of a GEMM launch.
 int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k) {
-  const bool few = (proj == P_HEAD || proj == P_HEAD_SILU) && gemm_few_rows(dt, m, k);
+  const bool few = (proj == P_HEAD || proj == P_HEAD_SILU) && gemm_few_rows(dt, m, n, k);
   return K_GEMM_FIRST + proj * kGemmKinds + (few ? GEMM_TILE_COUNT : gemm_tile_kind(dt, m, n, k));
 }
 
 // Timing class of a sampler block's product with n_side columns beside it.
 int head_class(GemmProj proj, DType dt, int32_t m, int32_t width, int32_t n_side) {
-  if (dt != DType::BF16 || gemm_few_rows(dt, m, width)) return gemm_class(proj, dt, m, width, width);
+  if (dt != DType::BF16 || gemm_few_rows(dt, m, width + n_side, width))
+    return gemm_class(proj, dt, m, width + n_side, width);
   return K_GEMM_FIRST + proj * kGemmKinds + head_tile_kind(m, width, n_side);
 }
 
@@ -896,9 +897,12 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
   // block's first product forms its modulated norm itself.
   void *scs[2] = {sc, tbuf};
   const int tw = W / 128;                     // 128-column tiles of a width
-  const int side_fit = head_side_tiles(dt, M, W);
   const int final_share = nb > 1 ? (2 * tw + 2 * nb - 3) / (2 * nb - 2) : 0;
-  const bool beside = nb > 1 && side_fit >= (3 * tw + 1) / 2 + final_share;
+  const int side_most = nb > 1 ? (3 * tw + 1) / 2 + final_share : 0;  // beside one product
+  // (launches of the few-row kernel stream weights: side products only add
+  // their own bytes)
+  const bool few = gemm_few_rows(dt, M, W + side_most * 128, W);
+  const bool beside = nb > 1 && (few || head_side_tiles(dt, M, W) >= side_most);
   auto mod_cols = [&](void *from, int c0, int n) {  // columns [c0, c0 + n) from SiLU rows
     return HeadSide{from, static_cast<const char *>(w->w_ada) + (size_t)c0 * W * es,
                     fp(w->b_ada) + c0, static_cast<char *>(mod) + (size_t)c0 * es, n};
@@ -917,7 +921,7 @@ marche_status_t marche_diffusion_sample(const marche_head_t *hd, const marche_he
   };
   HeadRows hr{};
   hr.h = hbuf;
-  const bool norm_in = head_norm_fits(dt, M, W);
+  const bool norm_in = few && head_norm_fits(dt, M, W);
   hr.a = norm_in ? nullptr : abuf;
   hr.mod = mod;
   hr.mod_ld = ML;

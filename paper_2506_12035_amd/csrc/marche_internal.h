@@ -183,8 +183,9 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k);
 // The tile of a sampler block's bf16 product (width x width) with side products
 // of n_side columns.
 int head_tile_kind(int32_t m, int32_t width, int32_t n_side);
-// Whether a sampler product of m rows over K = k runs the few-row kernel instead.
-bool gemm_few_rows(DType dt, int32_t m, int32_t k);
+// Whether a sampler launch of m rows and n columns (side products among them)
+// over K = k runs the few-row kernel instead.
+bool gemm_few_rows(DType dt, int32_t m, int32_t n, int32_t k);
 // Compute units of the current device (queried once per device, then cached).
 int device_cu_count();
 

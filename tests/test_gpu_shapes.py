@@ -143,33 +143,41 @@ def test_segment_shapes(case):
             assert rel_err(got[b, :, h], ref) <= TOL["bf16"], (b, h)
 
 
-# (rows, width, blocks, sampling steps, channels, dtype): the few-row kernel with
-# 16, 32 and 64 rows (up to 16, as far as they fit, norming their own
-# activations), the 32x64, 64x64 and 64x128 tiles with side products and a
-# ragged last tile, row counts whose modulations no longer fit beside the block
-# products, one block (no side products) and two, one to three sampling steps,
-# other channel counts.
+# (rows, width, blocks, sampling steps, channels, dtype, kernel of the block
+# products): the few-row kernel with one, two and three blocks of 16 rows (up to
+# 16 rows, as far as they fit, norming their own activations) up to the last row
+# count and the widest launches it takes, the next row or width on a tile; the
+# 32x64, 64x64 and 64x128 tiles with side products and a ragged last tile; row
+# counts whose modulations no longer fit beside the block products; one block
+# (no side products) and more, one to three sampling steps, other channel counts.
 SAMPLER = [
-    (1, 256, 2, 3, 16, "bf16"),
-    (16, 512, 3, 2, 16, "bf16"),
-    (9, 1536, 1, 2, 8, "bf16"),
-    (16, 2048, 2, 2, 16, "bf16"),
-    (17, 256, 1, 3, 5, "bf16"),
-    (33, 768, 2, 1, 16, "bf16"),
-    (64, 256, 5, 3, 33, "bf16"),
-    (65, 512, 2, 3, 16, "bf16"),
-    (200, 1024, 2, 2, 16, "bf16"),
-    (300, 1024, 2, 2, 16, "bf16"),
-    (200, 256, 1, 2, 16, "bf16"),
-    (1500, 1280, 3, 2, 16, "bf16"),
-    (5, 256, 2, 3, 16, "f32"),
-    (70, 512, 1, 2, 3, "f32"),
+    (1, 256, 2, 3, 16, "bf16", "rows"),
+    (16, 512, 3, 2, 16, "bf16", "rows"),
+    (9, 1536, 1, 2, 8, "bf16", "rows"),
+    (16, 1536, 3, 2, 16, "bf16", "rows"),
+    (17, 1536, 3, 2, 16, "bf16", "t32x64"),
+    (16, 2048, 2, 2, 16, "bf16", "rows"),
+    (5, 4096, 2, 1, 16, "bf16", "t32x64"),
+    (17, 256, 1, 3, 5, "bf16", "rows"),
+    (33, 768, 2, 1, 16, "bf16", "rows"),
+    (48, 1024, 3, 2, 16, "bf16", "rows"),
+    (49, 1024, 3, 2, 16, "bf16", "t32x64"),
+    (64, 256, 5, 3, 33, "bf16", "t32x64"),
+    (65, 512, 2, 3, 16, "bf16", "t32x64"),
+    (200, 1024, 2, 2, 16, "bf16", "t64x64"),
+    (300, 1024, 2, 2, 16, "bf16", "t64x128"),
+    (200, 256, 1, 2, 16, "bf16", "t32x64"),
+    (1500, 1280, 3, 2, 16, "bf16", "t64x128"),
+    (5, 256, 2, 3, 16, "f32", None),
+    (70, 512, 1, 2, 3, "f32", None),
 ]
 
 
 @pytest.mark.parametrize("case", SAMPLER, ids=lambda c: "m{}w{}n{}t{}c{}-{}".format(*c))
 def test_sampler_shapes(case):
-    rows, width, blocks, steps, chans, dtype = case
+    from paper_2506_12035_amd import binding
+
+    rows, width, blocks, steps, chans, dtype, kernel = case
     tiny = workload.MAR_CONFIGS["tiny"]
     B = rows // 100 + 2
     mc = replace(tiny, dec=tiny.dec.with_(dtype=dtype, n_tokens=104, batch=B), head_width=width,
@@ -185,7 +193,16 @@ def test_sampler_shapes(case):
     out_rows = (b_of * cfg.n_img + p_of).astype(np.int32)
     src = (b_of * cfg.n_tokens + cfg.n_buf + p_of).astype(np.int32)
     noise = workload.head_noise(mc, rows, rows)
-    got = _run_head(mc, head, emb, x_dec, src, out_rows, noise, 1.0)
+    binding.profile_reset()
+    binding.profile_enable(True)
+    try:
+        got = _run_head(mc, head, emb, x_dec, src, out_rows, noise, 1.0)
+        prof = binding.profile_collect()
+    finally:
+        binding.profile_enable(False)
+        binding.profile_reset()
+    if kernel:
+        assert {f"gemm_head_silu_{kernel}", f"gemm_head_{kernel}"} <= set(prof), sorted(prof)
     ref = _oracle_head(mc, hs, head, emb, x_dec, b_of, p_of, noise, 1.0)
     e = rel_err(got[out_rows], ref)
     say(f"  max rel err {e:.2e}")
@@ -199,9 +216,9 @@ def test_sampler_shapes(case):
 # 32x64, 64x64 and 64x128 tiles, with and without side products), fp32 on both
 # sides of the 64x64 tile.
 SAMPLER_PARTS = [
-    (256, 3, 16, "bf16", 300, [1, 16, 17, 33, 41, 130]),
-    (1280, 2, 16, "bf16", 700, [1, 5, 15, 16, 17, 31, 40, 41, 64, 65, 129, 300]),
-    (2048, 2, 4, "bf16", 130, [2, 16, 32, 40]),
+    (256, 3, 16, "bf16", 300, [1, 16, 17, 33, 48, 49, 130]),
+    (1024, 3, 16, "bf16", 700, [1, 5, 15, 16, 17, 31, 40, 48, 49, 65, 129, 300]),
+    (2048, 2, 4, "bf16", 130, [2, 16, 17, 40]),
     (1280, 1, 16, "bf16", 200, [3, 16, 20, 35, 60]),
     (512, 2, 33, "f32", 1500, [1, 17, 40, 300]),
 ]
