@@ -469,8 +469,10 @@ struct Lay {
 };
 
 // One tile of the online softmax (as strm::tile) of which the first `left`
-// keys exist (uniform).
-template <int DH, bool ALIGNED>
+// keys exist (uniform).  PART: the state covers a part of the keys only, whose
+// logits may all be -inf (infinite keys) while others' are not: a maximum of
+// -inf then scales nothing instead of making the state NaN.
+template <int DH, bool ALIGNED, bool PART>
 __device__ __forceinline__ void tile(const unsigned char *slot, const bf16x8 (&qf)[DH / 16],
                                      f32x16 (&acc)[Lay<DH>::ODB], float &m_run, float &l_run,
                                      float sl2, int left, int lane) {
@@ -504,13 +506,14 @@ __device__ __forceinline__ void tile(const unsigned char *slot, const bf16x8 (&q
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   const float m_new = fmaxf(m_run, mx * sl2);
-  const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+  const float m_ref = PART && m_new == -INFINITY ? 0.f : m_new;
+  const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
   float psum = 0.f;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], sl2, -m_new));
+      const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], sl2, -m_ref));
       s[kb][r] = p;
       psum += p;
     }
@@ -651,7 +654,7 @@ __global__ __launch_bounds__(QB *KS * 64) void attn_gen_kernel(AttnArgs a, int c
     if (live && t < nt) {
       const bf16 *kb, *vb;
       const int left = ALIGNED ? TK : tile_of(t, kb, vb);
-      gen::tile<DH, ALIGNED>(sp, qf, acc, m_run, l_run, sl2, left, lane);
+      gen::tile<DH, ALIGNED, (KS > 1)>(sp, qf, acc, m_run, l_run, sl2, left, lane);
     }
     __builtin_amdgcn_sched_barrier(0);
     sstore(slots + ((it + 1) & (SLOTS - 1)) * L::SLOT);
@@ -676,7 +679,6 @@ __global__ __launch_bounds__(QB *KS * 64) void attn_gen_kernel(AttnArgs a, int c
 #pragma unroll
     for (int g2 = 0; g2 < KS - 1; ++g2) {
       const float *o2 = reinterpret_cast<const float *>(smem) + (g2 * QB + qb) * REC + lane;
-      // group 0 always holds a key, so m_new is finite wherever the logits are
       const float m2 = o2[0], m_new = fmaxf(m_run, m2);
       const float a1 = __builtin_amdgcn_exp2f(m_run - m_new);
       const float a2 = __builtin_amdgcn_exp2f(m2 - m_new);

@@ -143,6 +143,35 @@ def test_segment_shapes(case):
             assert rel_err(got[b, :, h], ref) <= TOL["bf16"], (b, h)
 
 
+@pytest.mark.parametrize("dead", ["cached"])
+@pytest.mark.parametrize("B,dh,nq", [(1, 64, 20), (1, 80, 50), (20, 64, 50), (20, 80, 20), (6, 64, 140)])
+def test_infinite_keys_of_a_segment(B, dh, nq, dead):
+    """A segment whose keys all lie at -inf from every query has no weight: the
+    result is that of the other segment (both 64 keys, so that a segment is a
+    key tile, with few workgroups a key group's only one)."""
+    import torch
+    from oracle import block
+    from paper_2506_12035_amd import binding
+
+    H, n = 16, 64
+    say(f"infinite {dead} keys: B={B} dh={dh} nq={nq}")
+    rng = np.random.default_rng(nq)
+    draw = lambda *s: workload.round_to(rng.standard_normal(s, dtype=np.float32), "bf16")
+    q, ka, va, kc, vc = draw(B, nq, H * dh), *(draw(B, H, n, dh) for _ in range(4))
+    q[:, :, ::dh] = np.abs(q[:, :, ::dh]) + 0.25
+    (kc if dead == "cached" else ka)[..., 0] = -np.inf
+    dev = [torch.from_numpy(t).to("cuda").bfloat16() for t in (q, ka, va, kc, vc)]
+    o = torch.full((B, nq, H * dh), float("nan"), device="cuda", dtype=torch.bfloat16)
+    binding.attention_segments(dev[0], o, nq, dev[1], dev[2], n, dev[3], dev[4], n, B, H, dh,
+                               binding.MARCHE_BF16, binding.MARCHE_ATTN_TWO_SEGMENT)
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy().reshape(B, nq, H, dh)
+    k, v = (ka, va) if dead == "cached" else (kc, vc)
+    for h in range(H):
+        ref = block.attention(q[-1, :, h * dh:(h + 1) * dh], k[-1, h], v[-1, h])[0]
+        assert rel_err(got[-1, :, h], ref) <= TOL["bf16"], h
+
+
 # (rows, width, blocks, sampling steps, channels, dtype, kernel of the block
 # products): the few-row kernel with one, two and three blocks of 16 rows (up to
 # 16 rows, as far as they fit, norming their own activations) up to the last row
