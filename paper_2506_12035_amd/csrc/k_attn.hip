@@ -944,46 +944,61 @@ __global__ __launch_bounds__(NW * 64) void attn_resident_kernel(AttnArgs a) {
 
 constexpr int RES_NTL = 5;    // keys resident: 320
 constexpr int RES_QMAX = 320; // queries per workgroup
-constexpr int RES_QMIN = 128; // queries below which the streaming kernels are used
-
-// Whether the resident kernel can take these sizes: more than 128 active
-// queries in some image (below that one streaming workgroup of four
-// wavefronts covers an (image, head), reads each K/V element once as well and
-// skips wavefronts without queries: 64 images x 16 heads with 9..71 queries of
-// width 64 took 30.7 us on the resident kernel, and the 4-layer call 652 us on
-// it against 631), all of them and all keys within one workgroup's reach, one
-// key segment.
-static bool resident_fits(int32_t a_max, int32_t n_tokens, bool two_segments) {
-  return !two_segments && a_max > RES_QMIN && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
-}
-
-// Host choice of the resident kernel.  With fewer (image, head) pairs than two
-// workgroups per compute unit the streaming kernel spreads a pair's queries
-// over several workgroups instead (4 images x 12 heads x 320 tokens, 12 layers
-// of a full and a cache-aware step: 1761 us with it, 1655 without); from there on the two are level, and the resident one
-// is ahead when another image range runs beside it (two 64-image ranges of 16
-// heads: 12.94 against 13.09 ms for a full and a cache-aware step of 8
-// layers).  Both sum in the same order.  The score pass of these sizes is the
-// resident kernel's.
-bool attn_resident(const AttnArgs &a) {
-  return resident_fits(a.a_max, a.n_tokens, a.k2 != nullptr) &&
-         (a.scores || (int64_t)a.batch * a.n_heads >= 2 * device_cu_count());
-}
+constexpr int RES_QMIN = 128; // queries up to which the streaming kernels are used
+constexpr int RES_SCMIN = 64; // the same at a selection layer whose scores they cannot write
 
 // Query blocks per workgroup of the streaming kernel for a_max rows.
 static int reg_qb(int32_t a_max) {
   return a_max <= 32 ? 1 : a_max <= 64 ? 2 : a_max <= 128 ? 4 : 8;
 }
 
-bool attn_resident(int32_t a_max, int32_t n_tokens, bool two_segments) {
-  return !two_segments && a_max > RES_QMIN && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
+// The register-staged kernel of head width 64 for one key segment of whole
+// tiles (at least three).
+bool attn_streams(int32_t head_dim, int32_t n_tokens, bool two_segments) {
+  return head_dim == 64 && !two_segments && n_tokens % TK == 0 && n_tokens >= 3 * TK;
+}
+
+// Whether that kernel can write the score pass: the generating rows within
+// query chunk 0, and one (key block, generating block) pair per wavefront.
+static bool streams_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_t gen_max) {
+  return attn_streams(head_dim, n_tokens, false) && 2 * ((gen_max + 31) / 32) <= reg_qb(a_max);
+}
+
+// Whether the resident kernel writes the score pass: all queries and keys
+// within one workgroup's reach and more than 128 queries in some image, or more
+// than 64 where the streaming kernel cannot, because a separate score pass
+// costs more than the streaming attention saves there (one layer, scores and
+// selection, with it / on the resident kernel, 65 to 128 rows: 4 images, heads
+// of 80, 320 keys 88.2 / 82.7 us; 64 images 377 / 369; heads of 64, 229 keys
+// 72.9 / 67.8 and 253 / 235).
+static bool resident_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_t gen_max) {
+  const int q_min =
+      streams_scores(a_max, n_tokens, head_dim, gen_max) ? RES_QMIN : RES_SCMIN;
+  return a_max > q_min && a_max <= RES_QMAX && n_tokens <= RES_NTL * TK;
+}
+
+// Host choice of the resident kernel: more than 128 active queries in some
+// image (below that one streaming workgroup of four wavefronts covers an
+// (image, head), reads each K/V element once as well and skips wavefronts
+// without queries: 64 images x 16 heads with 9..71 queries of width 64 took
+// 30.7 us on the resident kernel, and the 4-layer call 652 us on it against
+// 631), all of them and all keys within one workgroup's reach, one key segment.
+// With fewer (image, head) pairs than two workgroups per compute unit the
+// streaming kernel spreads a pair's queries over several workgroups instead
+// (4 images x 12 heads x 320 tokens, 12 layers of a full and a cache-aware step:
+// 1761 us with it, 1655 without); from there on the two are level, and the
+// resident one is ahead when another image range runs beside it (two 64-image
+// ranges of 16 heads: 12.94 against 13.09 ms for a full and a cache-aware step
+// of 8 layers).  Both sum in the same order.
+bool attn_resident(const AttnArgs &a) {
+  if (a.scores) return resident_scores(a.a_max, a.n_tokens, a.head_dim, a.gen_max);
+  return !a.k2 && a.a_max > RES_QMIN && a.a_max <= RES_QMAX && a.n_tokens <= RES_NTL * TK &&
+         (int64_t)a.batch * a.n_heads >= 2 * device_cu_count();
 }
 
 bool attn_fuses_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_t gen_max) {
-  if (resident_fits(a_max, n_tokens, false)) return true;
-  // streaming kernel: the generating rows within query chunk 0, and one
-  // (key block, generating block) pair per wavefront
-  return attn_streams(head_dim, n_tokens, false) && 2 * ((gen_max + 31) / 32) <= reg_qb(a_max);
+  return resident_scores(a_max, n_tokens, head_dim, gen_max) ||
+         streams_scores(a_max, n_tokens, head_dim, gen_max);
 }
 
 template <int DH, int QB, int KS, bool SEG2>
@@ -995,12 +1010,6 @@ static hipError_t run_attn_gen(const AttnArgs &a, hipStream_t s) {
   else
     launch_kernel(attn_gen_kernel<DH, QB, KS, SEG2, false>, grid, QB * KS * 64, 0, s, a, chunks);
   return hipGetLastError();
-}
-
-// The register-staged kernel of head width 64 for one key segment of whole
-// tiles (at least three).
-bool attn_streams(int32_t head_dim, int32_t n_tokens, bool two_segments) {
-  return head_dim == 64 && !two_segments && n_tokens % TK == 0 && n_tokens >= 3 * TK;
 }
 
 template <int QB>

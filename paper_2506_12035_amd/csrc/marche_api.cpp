@@ -448,6 +448,7 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
     if (fused) {
       aa.n_gen = n_gen;
       aa.scores = scores;
+      aa.gen_max = gen_max;
     } else if (sel) {
       aa.stats = static_cast<float *>(hid);  // free until fc1; 8 H bytes per row of its >= 512
     }

@@ -208,6 +208,7 @@ struct AttnArgs {
   // attn_fuses_scores() holds (one key segment).
   const int32_t *n_gen = nullptr;
   float *scores = nullptr;
+  int32_t gen_max = 0;  // largest n_gen[b]
   // Optional row statistics [a_total][n_heads][2] (maximum logit, 1 / sum) for
   // launch_attn_scores, written by the kernels that run where
   // attn_fuses_scores() does not hold (and by every fp32 one).

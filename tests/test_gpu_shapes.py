@@ -79,6 +79,37 @@ def test_bf16_attention_shapes(case):
     _case(cfg, sizes, gens, seed=sum(sizes) + n)
 
 
+# 65 to 128 rows with scores: (d_model, heads, head_dim, N, rows, generating rows,
+# the attention kernel that writes the scores).  The resident one where the
+# streaming one cannot (heads of 80, a key tail, over 64 generating rows).
+SCORES = [
+    (1280, 16, 80, 320, [65, 3], [9, 3], "attention_res_scores_ca"),
+    (1280, 16, 80, 229, [128, 70], [66, 1], "attention_res_scores_ca"),
+    (1024, 16, 64, 289, [100, 1], [33, 1], "attention_res_scores_ca"),
+    (1024, 16, 64, 128, [66, 20], [5, 20], "attention_res_scores_ca"),
+    (1024, 16, 64, 320, [128, 9], [65, 9], "attention_res_scores_ca"),
+    (1024, 16, 64, 320, [128, 9], [64, 9], "attention_scores_ca"),
+    (1280, 16, 80, 320, [64, 3], [9, 3], "attn_scores_ca"),
+]
+
+
+@pytest.mark.parametrize("case", SCORES, ids=lambda c: f"h{c[2]}n{c[3]}a{max(c[4])}g{max(c[5])}")
+def test_score_layers_of_65_to_128_rows(case):
+    from paper_2506_12035_amd import binding
+
+    d, h, dh, n, sizes, gens, kernel = case
+    cfg = workload.Config(64, "score-rows", 1, d, h, dh, 1024, n, 0, len(sizes), "bf16")
+    binding.profile_reset()
+    binding.profile_enable(True)
+    try:
+        _case(cfg, sizes, gens, seed=sum(sizes) + n)
+        prof = binding.profile_collect()
+    finally:
+        binding.profile_enable(False)
+        binding.profile_reset()
+    assert kernel in prof, sorted(prof)
+
+
 # Active rows per image at D = 1024, MLP 4096, and a tile each product count
 # takes: 192 rows x 128 columns with 135 rows in the last tile, 256 x 128 with
 # one, 192 x 128 over several rounds of N = 1024; and the tiles of a few rows,
