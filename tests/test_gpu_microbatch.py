@@ -192,3 +192,34 @@ def test_f32_ranges_match_the_whole_batch(case):
     d, h, dh, f, n, sizes, cuts = case
     cfg = workload.Config(63, "f32-ranges", 1, d, h, dh, f, n, 0, len(sizes), "f32")
     _layer_ranges(cfg, sizes, cuts)
+
+
+# Whole batches of at least two (image, head) pairs per compute unit run the
+# attention with all keys in LDS, smaller ranges a streaming kernel over several
+# query chunks: head widths and key counts of each (N = 320 at width 64: the
+# register-staged one; a key tail, heads of 80: the general one).
+ATTENTION_RANGES = [
+    (1024, 16, 64, 320),
+    (1024, 16, 64, 289),
+    (1280, 16, 80, 320),
+    (1280, 16, 80, 229),
+]
+
+
+@pytest.mark.parametrize("case", ATTENTION_RANGES, ids=lambda c: f"h{c[2]}n{c[3]}")
+def test_attention_ranges_match_the_whole_batch(case):
+    from paper_2506_12035_amd import binding
+
+    d, h, dh, n = case
+    images = 2 * torch.cuda.get_device_properties(0).multi_processor_count // h + 1
+    sizes = ([n, 129, 33, 200, 1] * images)[:images]
+    cfg = workload.Config(65, "attn-ranges", 1, d, h, dh, 256, n, 0, images, "bf16")
+    binding.profile_reset()
+    binding.profile_enable(True)
+    try:
+        _layer_ranges(cfg, sizes, [2, 5, images // 2], want_scores=False)
+        prof = binding.profile_collect()
+    finally:
+        binding.profile_enable(False)
+        binding.profile_reset()
+    assert "attention_res_ca" in prof and {"attention_q128_ca", "attention_q256_ca"} & set(prof), sorted(prof)
