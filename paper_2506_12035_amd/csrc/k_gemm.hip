@@ -1465,9 +1465,9 @@ constexpr int kPart = kSteps * 1024;   // bytes of a stage per 16 rows or column
 __host__ __device__ constexpr int stages(int mb) { return mb < 3 ? 5 : 4; }
 
 // The activations of a block's first product are the modulated norm of h,
-// a = LN(h) (1 + scale) + shift.  With up to 16 rows every workgroup forms them
-// itself instead of a launch before it doing so: the rows' float32 values
-// are a few dozen KB that the L2 holds, and a launch costs as much as the
+// a = LN(h) (1 + scale) + shift.  With few rows (head_norm_fits) every workgroup
+// forms them itself instead of a launch before it doing so: the rows' float32
+// values are a few dozen KB that the L2 holds, and a launch costs as much as the
 // whole product.
 struct NormIn {
   const float *h;  // [M][K]; NULL: the activations are given
@@ -1695,7 +1695,8 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
 
 // Up to three blocks of 16 rows, as long as the launch's workgroups (16 of its
 // n columns each, side products among them) are resident at once: two per CU
-// with one row block (80 KB of LDS), one with two or three.  A sampling step in
+// with one row block (80 KB of LDS; up to 96 KB with the norm of more than 8
+// rows inside, at widths of 1536 and more), one with two or three.  A sampling step in
 // us, this kernel / tiles: width 1280, 3 and 8 blocks: 5 rows 42 / 59 and 91 /
 // 142, 16 rows 49 / 61 and 114 / 147, 32 rows 53 / 62 and 127 / 151, 48 rows
 // 60 / 62 and 146 / 151; width 1536, 17 rows: 8 blocks (253 workgroups) 124 /
@@ -2134,8 +2135,15 @@ hipError_t launch_head_gemm_silu(DType dt, const void *a, const void *w, const f
                   sides, s);
 }
 
+// One row per wavefront (8), or two at widths where the products are long enough
+// to hide the second, as far as they fit the LDS.  15 sampling steps of 8 blocks
+// in us, norm inside / a launch of its own: 8 rows: width 256 855 / 949, 1280
+// 1442 / 1520, 2048 2567 / 2804; 16 rows: width 256 1012 / 982, 1024 1559 / 1486,
+// 1280 1697 / 1612; 12 rows: width 1536 1739 / 1723 (3 blocks 820 / 855), 2048
+// 2730 / 2933.
 bool head_norm_fits(DType dt, int32_t m, int32_t width) {
-  return dt == DType::BF16 && m >= 1 && m <= 16 && (int64_t)m * (width + 8) <= rows16::kNormElems;
+  return dt == DType::BF16 && m >= 1 && m <= (width < 1536 ? 8 : 16) &&
+         (int64_t)m * (width + 8) <= rows16::kNormElems;
 }
 
 hipError_t launch_head_gemm_norm_silu(const float *h, const void *mod, int32_t mod_ld,

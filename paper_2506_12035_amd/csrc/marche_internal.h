@@ -158,7 +158,7 @@ hipError_t launch_head_gemm_silu(DType dt, const void *a, const void *w, const f
                                  int32_t m, int32_t width, void *y, const HeadSides &sides,
                                  hipStream_t s);
 // The first with its activations a = LN(h) (1 + scale) + shift formed in the
-// same launch (bf16, where head_norm_fits: up to 16 rows).
+// same launch (bf16, where head_norm_fits: up to 16 rows, by width).
 bool head_norm_fits(DType dt, int32_t m, int32_t width);
 hipError_t launch_head_gemm_norm_silu(const float *h, const void *mod, int32_t mod_ld,
                                       int32_t shift_off, int32_t scale_off, float eps,

@@ -204,17 +204,19 @@ def test_infinite_keys_of_a_segment(B, dh, nq, dead):
 
 
 # (rows, width, blocks, sampling steps, channels, dtype, kernel of the block
-# products): the few-row kernel with one, two and three blocks of 16 rows (up to
-# 16 rows, as far as they fit, norming their own activations) up to the last row
-# count and the widest launches it takes, the next row or width on a tile; the
+# products): the few-row kernel with one, two and three blocks of 16 rows ("norm":
+# forming the modulated norm itself, up to 8 rows, from width 1536 on up to 16 as
+# far as they fit) up to the last row count and the widest launches it takes, the next row or width on a tile; the
 # 32x64, 64x64 and 64x128 tiles with side products and a ragged last tile; row
 # counts whose modulations no longer fit beside the block products; one block
 # (no side products) and more, one to three sampling steps, other channel counts.
 SAMPLER = [
-    (1, 256, 2, 3, 16, "bf16", "rows"),
+    (1, 256, 2, 3, 16, "bf16", "norm"),
+    (8, 1280, 2, 2, 16, "bf16", "norm"),
+    (9, 1280, 2, 2, 16, "bf16", "rows"),
     (16, 512, 3, 2, 16, "bf16", "rows"),
     (9, 1536, 1, 2, 8, "bf16", "rows"),
-    (16, 1536, 3, 2, 16, "bf16", "rows"),
+    (16, 1536, 3, 2, 16, "bf16", "norm"),
     (17, 1536, 3, 2, 16, "bf16", "t32x64"),
     (16, 2048, 2, 2, 16, "bf16", "rows"),
     (5, 4096, 2, 1, 16, "bf16", "t32x64"),
@@ -261,7 +263,10 @@ def test_sampler_shapes(case):
     finally:
         binding.profile_enable(False)
         binding.profile_reset()
+    if kernel and blocks > 1:
+        assert ("head_mod" in prof) == (kernel != "norm"), sorted(prof)
     if kernel:
+        kernel = "rows" if kernel == "norm" else kernel
         assert {f"gemm_head_silu_{kernel}", f"gemm_head_{kernel}"} <= set(prof), sorted(prof)
     ref = _oracle_head(mc, hs, head, emb, x_dec, b_of, p_of, noise, 1.0)
     e = rel_err(got[out_rows], ref)
@@ -271,14 +276,14 @@ def test_sampler_shapes(case):
 
 
 # (width, blocks, channels, dtype, rows of the whole call, rows of its parts): parts
-# on every kernel that a row count picks (norm inside the first product up to 16
-# rows as far as they fit, one to three row blocks of the few-row kernel, the
-# 32x64, 64x64 and 64x128 tiles, with and without side products), fp32 on both
-# sides of the 64x64 tile.
+# on every kernel that a row count picks (norm inside the first product, one to
+# three row blocks of the few-row kernel, the 32x64, 64x64 and 64x128 tiles, with
+# and without side products), fp32 on both sides of the 64x64 tile.
 SAMPLER_PARTS = [
     (256, 3, 16, "bf16", 300, [1, 16, 17, 33, 48, 49, 130]),
     (1024, 3, 16, "bf16", 700, [1, 5, 15, 16, 17, 31, 40, 48, 49, 65, 129, 300]),
-    (2048, 2, 4, "bf16", 130, [2, 16, 17, 40]),
+    (2048, 2, 4, "bf16", 130, [2, 13, 14, 16, 17, 40]),
+    (1280, 2, 16, "bf16", 60, [8, 9]),
     (1280, 1, 16, "bf16", 200, [3, 16, 20, 35, 60]),
     (512, 2, 33, "f32", 1500, [1, 17, 40, 300]),
 ]
