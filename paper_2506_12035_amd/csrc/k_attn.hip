@@ -1399,9 +1399,8 @@ static hipError_t scores_dispatch(const AttnArgs &a, const int32_t *n_gen, float
   return hipGetLastError();
 }
 
-hipError_t launch_attn_scores(DType dt, const AttnArgs &a, const int32_t *n_gen, int32_t gen_max,
-                              float *scores, hipStream_t s) {
-  (void)gen_max;
+hipError_t launch_attn_scores(DType dt, const AttnArgs &a, const int32_t *n_gen, float *scores,
+                              hipStream_t s) {
   if (a.batch == 0) return hipSuccess;
   if (!a.stats) return hipErrorInvalidValue;
   if (dt == DType::BF16) {

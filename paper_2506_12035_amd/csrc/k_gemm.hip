@@ -96,7 +96,7 @@ struct EpiQkv : PlainPrior {
     return Row{(uint32_t)(r * d_model), (uint32_t)((m.b * n_heads * n_tokens + m.tok) * head_dim)};
   }
   // Which of q, K and V a column belongs to is decided once per wavefront:
-  // every tile gives a wavefront a span of 32, 64 or 128 columns aligned to its
+  // a wavefront has a span of 16 (fp32), 32, 64 or 128 columns aligned to its
   // width, and d_model is a multiple of 256, so no span crosses from one of
   // the three into the next.  The choice is then uniform (scalar) and the
   // stores take no divergent branches.
@@ -1060,16 +1060,15 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_mid_kernel(const bf16 *A, co
     for (int r = 0; r < TM + 2; ++r) read_frag<TM>(f[s], r, smem_u, s, wm, wn, lane);
 
   constexpr int MF = 2 * TM;  // MFMAs per k16 step
-  int cur = 0, nxt = NS > 1 ? 1 : 0, prv = NS - 1;  // stages of k-tiles t, t + 1, t - 1
+  int cur = 0, nxt = 1, prv = NS - 1;  // stages of k-tiles t, t + 1, t - 1
   for (int t = 0; t < nk; ++t) {
     const unsigned char *sc = smem_u + cur * S::kStage, *sn = smem_u + nxt * S::kStage;
     const bool more = t + 1 < nk, ld = t + NS - 1 < nk;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      // k-tile t+1 landed (issued so far: up to k-tile t + NS - 2, and the
-      // first half of t + NS - 1's loads) before its fragments are read
+      // k-tile t+1 landed before its fragments are read; of the k-tiles issued
+      // so far, t + 2 .. t + NS - 2 may still be on their way
       if (s == 2 && more) {
-        // loads outstanding after k-tile t+1: those of t + 2 .. t + NS - 2
         barrier_tiles<S::kLoads, NS - 3>(min(NS - 3, nk - 2 - t));
         pin();
       }

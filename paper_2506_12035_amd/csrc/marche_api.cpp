@@ -464,7 +464,7 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
     if (sel && !fused) {
       LAUNCH(K_ATTN_SCORES + ko, 2.0 * batch * gen_max * N * D,
              es * (double)batch * N * D + 4.0 * batch * H * N,
-             launch_attn_scores(dt, aa, n_gen, gen_max, scores, stream));
+             launch_attn_scores(dt, aa, n_gen, scores, stream));
     }
     LAUNCH(gemm_class(P_O, dt, M, D, D) + ko, 2.0 * M * D * D, gemm_bytes_act * ((double)M * D + (double)D * D) + 8.0 * M * D,
            launch_gemm_resid(dt, buf0, L.w_o, static_cast<const float *>(L.b_o), M, D, D, map, x,

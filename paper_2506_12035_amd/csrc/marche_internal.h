@@ -234,8 +234,8 @@ hipError_t launch_concat_kv(DType dt, void *k_dst, void *v_dst, const void *k_a,
                             const void *k_c, const void *v_c, int32_t bh, int32_t na, int32_t nc,
                             int32_t head_dim, hipStream_t s);
 // scores[b][h][j] = sum over the first n_gen[b] active rows i of P_h[i][j]
-hipError_t launch_attn_scores(DType dt, const AttnArgs &a, const int32_t *n_gen, int32_t gen_max,
-                              float *scores, hipStream_t s);
+hipError_t launch_attn_scores(DType dt, const AttnArgs &a, const int32_t *n_gen, float *scores,
+                              hipStream_t s);
 
 // ---- selection (k_select.hip) ----
 // lowest = false: highest scores first; true: lowest scores first.
