@@ -264,7 +264,11 @@ marche_status_t marche_decoder_input(float *x, const float *cls, const float *va
  * MARCHE_ATTN_CONCAT: the baseline Appendix B compares against: K_A and K_C
  *   (and V_A, V_C) are first concatenated into the workspace, then the same
  *   attention runs over one segment of n_a + n_c keys.
- * The two modes differ only in rounding (the key tiles fall differently).
+ * The two modes differ only in rounding (the key tiles fall differently), and so
+ * may one image's result in calls of different batch: where there are few
+ * (image, head) pairs, the keys are summed in two parts that are merged at the
+ * end.  (marche_step never does this: its images' results do not depend on the
+ * batch.)
  * head_dim in {64, 80}, 1 <= n_query <= 4096, n_a, n_c >= 0 with
  * 1 <= n_a + n_c <= 65536, batch * n_heads <= 65535; UNSUPPORTED for other dtypes or head widths;
  * WORKSPACE when CONCAT's workspace (marche_attention_workspace_bytes,
