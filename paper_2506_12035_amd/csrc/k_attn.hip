@@ -260,10 +260,13 @@ __global__ __launch_bounds__(QB * 64) void attn_reg_kernel(AttnArgs a, int chunk
   const int r0 = a.a_off ? a.a_off[b] : b * a.a_max;
   const int na = a.a_off ? a.a_off[b + 1] - r0 : a.a_max;
   const int q0 = chunk * QB * 32;
-  if (q0 >= na) return;  // uniform over the workgroup
-
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int N = a.n_tokens, D = a.d_model, nt = N / TK;
+  if (q0 >= na) {  // uniform over the workgroup
+    if (SCORES && chunk == 0)  // no active row: no key receives any mass
+      for (int j = tid; j < N; j += NT) a.scores[(size_t)bh * N + j] = 0.f;
+    return;
+  }
   const bf16 *kg = static_cast<const bf16 *>(a.k_cache) + (size_t)bh * N * 64;
   const bf16 *vg = static_cast<const bf16 *>(a.v_cache) + (size_t)bh * N * 64;
 

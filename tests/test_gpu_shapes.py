@@ -110,6 +110,40 @@ def test_score_layers_of_65_to_128_rows(case):
     assert kernel in prof, sorted(prof)
 
 
+# (dtype, d_model, heads, head_dim, N, active rows): the streaming kernels with one
+# to four query blocks and the resident one, with the scores inside, and a score
+# pass of its own.
+EMPTY = [
+    ("bf16", 1024, 16, 64, 320, [30, 0, 7]), ("bf16", 1024, 16, 64, 320, [0, 64]),
+    ("bf16", 1024, 16, 64, 384, [128, 0]), ("bf16", 1024, 16, 64, 384, [200, 0]),
+    ("bf16", 1024, 16, 64, 320, [0, 200, 0]), ("bf16", 1280, 16, 80, 229, [100, 0]),
+    ("bf16", 1280, 16, 80, 229, [40, 0]), ("f32", 256, 4, 64, 130, [0, 20]),
+]
+
+
+@pytest.mark.parametrize("case", EMPTY, ids=lambda c: "{}h{}n{}-{}".format(c[0], c[3], c[4], "-".join(map(str, c[5]))))
+def test_image_without_active_rows(case):
+    """Its scores are 0 (the buffer held NaN) and its rows stay; the others'
+    are those of a call without it."""
+    dtype, d, h, dh, n, sizes = case
+    cfg = workload.Config(66, "empty", 1, d, h, dh, 512, n, 0, len(sizes), dtype)
+    say(f"empty images: {dtype} dh={dh} N={n} sizes={sizes}")
+    rng = np.random.default_rng(n + sum(sizes))
+    B = len(sizes)
+    x = rng.standard_normal((B, n, d), dtype=np.float32)
+    k, v = (workload.round_to(rng.standard_normal((B, h, n, dh), dtype=np.float32), dtype) for _ in range(2))
+    act = [rng.permutation(n)[:s].astype(np.int32) for s in sizes]
+    gens = [min(3, s) for s in sizes]
+    p = workload.layer_weights(cfg, 0)
+    got = SingleLayer(cfg, p, x, k, v).run(act, gens)
+    live = [b for b in range(B) if sizes[b]]
+    ref = SingleLayer(cfg, p, x[live], k[live], v[live]).run([act[b] for b in live], [gens[b] for b in live])
+    for name in ("x", "k", "v", "scores"):
+        assert np.array_equal(got[name][live], ref[name]), name
+    for b in set(range(B)) - set(live):
+        assert np.array_equal(got["x"][b], x[b]) and not got["scores"][b].any(), b
+
+
 # Active rows per image at D = 1024, MLP 4096, and a tile each product count
 # takes: 192 rows x 128 columns with 135 rows in the last tile, 256 x 128 with
 # one, 192 x 128 over several rounds of N = 1024; and the tiles of a few rows,
