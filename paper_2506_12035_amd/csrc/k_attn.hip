@@ -972,8 +972,8 @@ static bool streams_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, in
 // than 64 where the streaming kernel cannot, because a separate score pass
 // costs more than the streaming attention saves there (one layer, scores and
 // selection, with it / on the resident kernel, 65 to 128 rows: 4 images, heads
-// of 80, 320 keys 88.2 / 82.7 us; 64 images 377 / 369; heads of 64, 229 keys
-// 72.9 / 67.8 and 253 / 235).
+// of 80, 320 keys 88.2 / 82.7 us; 64 images 379 / 372; heads of 64, 229 keys
+// 72.7 / 67.3 and 252 / 234).
 static bool resident_scores(int32_t a_max, int32_t n_tokens, int32_t head_dim, int32_t gen_max) {
   const int q_min =
       streams_scores(a_max, n_tokens, head_dim, gen_max) ? RES_QMIN : RES_SCMIN;

@@ -1650,18 +1650,21 @@ __global__ __launch_bounds__(512) void gemm_bf16_rows_kernel(const bf16 *A, cons
 // 16 to 5120 rows at the model widths (N = D, 3D, 4D, K = D, 4D for D = 768,
 // 1024, 1280; within about 20% of every measured time except where the whole
 // chip is busy and its clock drops, which moves all tiles alike).  Half of the
-// time that the tiles would take spread evenly over the chip is added: a tile
-// that computes the same product with less of the chip leaves the rest to an
-// image range on another stream (weights 0, 0.5, 1 and 2 measured: 0.5 is
-// level with 0 for single calls and with 2 for two ranges).  Measured against
-// the best of the tiles used before (320, 256 and 128 rows x 256 columns, 128
-// x 128, 64 x 128), one box: 4352 x 1024 x 4096: 71 -> 51 us (192 x 128),
-// 1280 x 4096 x 1024: 24.5 -> 18.8, 3600 x 1280 x 5120: 90 -> 64, 2432 x 3072 x
-// 1024: 23.9 -> 21.4 (256 x 128).  The tiles of at most 64 x 64 against 64 x
+// time that the tiles would take spread evenly over the chip is added, which
+// settles near ties for the tile that takes less of the chip.  A call that is one
+// of several image ranges shares the chip with them (`shared`): there the time of
+// two such products side by side is added instead (a full and a cache-aware step
+// as two ranges in us, by the single call's rule / this one: 64 images, D = 768,
+// 8 layers 4943 / 4681, 16 images 1821 / 1730; 32 images, D = 1280, 4 layers
+// 3234 / 3025; 64 images, D = 1024, 8 layers 7050 / 6770, 8 images 1682 / 1732).
+// Measured against the best of the tiles used before (320, 256 and 128 rows x
+// 256 columns, 128 x 128, 64 x 128), one box: 4352 x 1024 x 4096: 71 -> 51 us (192
+// x 128), 1280 x 4096 x 1024: 24.5 -> 18.8, 3600 x 1280 x 5120: 90 -> 64, 2432 x
+// 3072 x 1024: 23.9 -> 21.4 (256 x 128).  The tiles of at most 64 x 64 against 64 x
 // 128: 150 x 768 x 3072: 19.5 -> 10.0 (32 x 32), 150 x 768 x 768: 7.9 -> 4.8,
 // 300 x 1024 x 4096: 24.6 -> 14.5 (32 x 64), 1280 x 768 x 3072: 20.5 -> 15.1
 // (64 x 64); 16 rows x 1280 x 5120: 29.0 -> 14.4 (32 x 32).
-int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
+int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k, bool shared) {
   if (dt != DType::BF16 || m <= 0) return GEMM_TILE_128;
   struct Tile {
     int kind, rows, cols;
@@ -1683,7 +1686,9 @@ int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k) {
     if (!small_off && t.kind != GEMM_TILE_256 && t.kind != GEMM_TILE_64x128) continue;
     const int64_t tiles = (int64_t)((m + t.rows - 1) / t.rows) * (n / t.cols);
     const double one = t.c0 + (k / 64) * t.c1;
-    const double time = (double)((tiles + cus - 1) / cus) * one + 0.5 * tiles * one / cus;
+    const int64_t alone = (tiles + cus - 1) / cus, two = (2 * tiles + cus - 1) / cus;
+    const double time = shared ? (double)(alone + two) * one
+                               : (double)alone * one + 0.5 * tiles * one / cus;
     if (best < 0 || time < best_t) {
       best = t.kind;
       best_t = time;
@@ -1742,11 +1747,11 @@ static void run_mid(const bf16 *A, const bf16 *W, int m, int n, int k, const Epi
 // multiples of 256).
 template <class Epi>
 static hipError_t run_bf16(const void *a, const void *w, int m, int n, int k, const Epi &epi,
-                           hipStream_t s) {
+                           hipStream_t s, bool shared = false) {
   if (m == 0) return hipSuccess;
   if (n % 256 != 0 || k % 64 != 0) return hipErrorInvalidValue;
   const bf16 *A = static_cast<const bf16 *>(a), *W = static_cast<const bf16 *>(w);
-  switch (gemm_tile_kind(DType::BF16, m, n, k)) {
+  switch (gemm_tile_kind(DType::BF16, m, n, k, shared)) {
     case GEMM_TILE_256:
       // eight wavefronts where the write-back is a large share of a tile
       // (K < 2048: fc1, QKV, the output projection), four where the main
@@ -2009,7 +2014,8 @@ static hipError_t run_f32(const void *a, const void *w, int m, int n, int k, con
 // ------------------------------------------------------------------ launchers
 
 hipError_t launch_gemm_qkv(DType dt, const void *a, const void *w, const float *bias, int32_t m,
-                           int32_t n, int32_t k, const RowMap *map, QkvOut o, hipStream_t s) {
+                           int32_t n, int32_t k, const RowMap *map, QkvOut o, bool shared,
+                           hipStream_t s) {
   if (dt == DType::F32) {
     EpiQkv<float> e{{}, static_cast<float *>(o.q), static_cast<float *>(o.k_cache),
                     static_cast<float *>(o.v_cache), bias, map, o.d_model, o.head_dim,
@@ -2019,28 +2025,28 @@ hipError_t launch_gemm_qkv(DType dt, const void *a, const void *w, const float *
   EpiQkv<bf16> e{{}, static_cast<bf16 *>(o.q), static_cast<bf16 *>(o.k_cache),
                  static_cast<bf16 *>(o.v_cache), bias, map, o.d_model, o.head_dim, o.n_heads,
                  o.n_tokens};
-  return run_bf16(a, w, m, n, k, e, s);
+  return run_bf16(a, w, m, n, k, e, s, shared);
 }
 
 hipError_t launch_gemm_resid(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                              int32_t n, int32_t k, const RowMap *map, float *x, int32_t tag,
-                             hipStream_t s) {
+                             bool shared, hipStream_t s) {
   if (tag == 0) {
     EpiResid<0> e{{}, x, bias, map, n};
-    return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s);
+    return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s, shared);
   }
   EpiResid<1> e{{}, x, bias, map, n};
-  return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s);
+  return dt == DType::F32 ? run_f32(a, w, m, n, k, e, s) : run_bf16(a, w, m, n, k, e, s, shared);
 }
 
 hipError_t launch_gemm_gelu(DType dt, const void *a, const void *w, const float *bias, int32_t m,
-                            int32_t n, int32_t k, void *h, hipStream_t s) {
+                            int32_t n, int32_t k, void *h, bool shared, hipStream_t s) {
   if (dt == DType::F32) {
     EpiGelu<float> e{{}, static_cast<float *>(h), bias, n};
     return run_f32(a, w, m, n, k, e, s);
   }
   EpiGelu<bf16> e{{}, static_cast<bf16 *>(h), bias, n};
-  return run_bf16(a, w, m, n, k, e, s);
+  return run_bf16(a, w, m, n, k, e, s, shared);
 }
 
 }  // namespace marche

@@ -151,9 +151,10 @@ const char *class_name(int i) {
 }
 
 // Timing class of a GEMM launch.
-int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k) {
+int gemm_class(GemmProj proj, DType dt, int32_t m, int32_t n, int32_t k, bool shared = false) {
   const bool few = (proj == P_HEAD || proj == P_HEAD_SILU) && gemm_few_rows(dt, m, n, k);
-  return K_GEMM_FIRST + proj * kGemmKinds + (few ? GEMM_TILE_COUNT : gemm_tile_kind(dt, m, n, k));
+  return K_GEMM_FIRST + proj * kGemmKinds +
+         (few ? GEMM_TILE_COUNT : gemm_tile_kind(dt, m, n, k, shared));
 }
 
 // Timing class of a sampler block's product with n_side columns beside it.
@@ -406,6 +407,7 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
   const size_t es = elem_size(m->dtype);
   const int D = m->d_model, F = m->d_mlp, H = m->n_heads, dh = m->head_dim, N = m->n_tokens;
   const int M = a_total;
+  const bool shared = batch < cache->batch;  // an image range: others may run beside it
 
   char *ws = static_cast<char *>(workspace);
   RowMap *map = reinterpret_cast<RowMap *>(ws);
@@ -435,10 +437,10 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
            launch_gather_ln(dt, buf0, x, map, static_cast<const float *>(L.ln1_g),
                             static_cast<const float *>(L.ln1_b), M, D, m->ln_eps, stream));
     QkvOut qo{buf1, kc, vc, D, dh, H, N};
-    LAUNCH(gemm_class(P_QKV, dt, M, 3 * D, D) + ko, 2.0 * M * 3 * D * D,
+    LAUNCH(gemm_class(P_QKV, dt, M, 3 * D, D, shared) + ko, 2.0 * M * 3 * D * D,
            gemm_bytes_act * ((double)M * D + 3.0 * D * D + 3.0 * M * D),
            launch_gemm_qkv(dt, buf0, L.w_qkv, static_cast<const float *>(L.b_qkv), M, 3 * D, D,
-                           map, qo, stream));
+                           map, qo, shared, stream));
     AttnArgs aa{buf1, kc, vc, buf0, a_off, map, batch, H, N, dh, D, M, a_max};
     // At the selection layer the resident attention kernel also writes the
     // score pass (Section 4.2) from the K tiles it holds; other sizes run the
@@ -466,20 +468,20 @@ marche_status_t marche::step_impl(const marche_model_t *m, const marche_layer_t 
              es * (double)batch * N * D + 4.0 * batch * H * N,
              launch_attn_scores(dt, aa, n_gen, scores, stream));
     }
-    LAUNCH(gemm_class(P_O, dt, M, D, D) + ko, 2.0 * M * D * D, gemm_bytes_act * ((double)M * D + (double)D * D) + 8.0 * M * D,
+    LAUNCH(gemm_class(P_O, dt, M, D, D, shared) + ko, 2.0 * M * D * D, gemm_bytes_act * ((double)M * D + (double)D * D) + 8.0 * M * D,
            launch_gemm_resid(dt, buf0, L.w_o, static_cast<const float *>(L.b_o), M, D, D, map, x,
-                             0, stream));
+                             0, shared, stream));
     LAUNCH(K_GATHER_LN + ko, 0, (double)M * D * (4 + es),
            launch_gather_ln(dt, buf1, x, map, static_cast<const float *>(L.ln2_g),
                             static_cast<const float *>(L.ln2_b), M, D, m->ln_eps, stream));
-    LAUNCH(gemm_class(P_FC1, dt, M, F, D) + ko, 2.0 * M * F * D,
+    LAUNCH(gemm_class(P_FC1, dt, M, F, D, shared) + ko, 2.0 * M * F * D,
            gemm_bytes_act * ((double)M * D + (double)F * D + (double)M * F),
            launch_gemm_gelu(dt, buf1, L.w_1, static_cast<const float *>(L.b_1), M, F, D, hid,
-                            stream));
-    LAUNCH(gemm_class(P_FC2, dt, M, D, F) + ko, 2.0 * M * D * F,
+                            shared, stream));
+    LAUNCH(gemm_class(P_FC2, dt, M, D, F, shared) + ko, 2.0 * M * D * F,
            gemm_bytes_act * ((double)M * F + (double)D * F) + 8.0 * M * D,
            launch_gemm_resid(dt, hid, L.w_2, static_cast<const float *>(L.b_2), M, D, F, map, x,
-                             1, stream));
+                             1, shared, stream));
   }
   return MARCHE_OK;
 }

@@ -123,14 +123,17 @@ struct QkvOut {
   void *v_cache;  // layer base
   int32_t d_model, head_dim, n_heads, n_tokens;
 };
+// `shared`: the call computes a part of its cache's images, so that others may
+// run beside it (see gemm_tile_kind).
 hipError_t launch_gemm_qkv(DType dt, const void *a, const void *w, const float *bias, int32_t m,
-                           int32_t n, int32_t k, const RowMap *map, QkvOut out, hipStream_t s);
+                           int32_t n, int32_t k, const RowMap *map, QkvOut out, bool shared,
+                           hipStream_t s);
 // tag: 0 = output projection, 1 = fc2 (separate kernel symbols)
 hipError_t launch_gemm_resid(DType dt, const void *a, const void *w, const float *bias, int32_t m,
                              int32_t n, int32_t k, const RowMap *map, float *x, int32_t tag,
-                             hipStream_t s);
+                             bool shared, hipStream_t s);
 hipError_t launch_gemm_gelu(DType dt, const void *a, const void *w, const float *bias, int32_t m,
-                            int32_t n, int32_t k, void *h, hipStream_t s);
+                            int32_t n, int32_t k, void *h, bool shared, hipStream_t s);
 // Sampler GEMMs: out[r][c] = act(C + bias) as out_dt (row-major, row stride
 // ld), act SiLU or the identity; a float32 GEMM writes float32 only.
 hipError_t launch_gemm_plain(DType dt, const void *a, const void *w, const float *bias, int32_t m,
@@ -179,7 +182,7 @@ enum GemmTile {
   GEMM_TILE_256 = 0, GEMM_TILE_320, GEMM_TILE_64x128, GEMM_TILE_128, GEMM_TILE_192x128,
   GEMM_TILE_256x128, GEMM_TILE_64x64, GEMM_TILE_32x64, GEMM_TILE_32x32, GEMM_TILE_COUNT
 };
-int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k);
+int gemm_tile_kind(DType dt, int32_t m, int32_t n, int32_t k, bool shared = false);
 // The tile of a sampler block's bf16 product (width x width) with side products
 // of n_side columns.
 int head_tile_kind(int32_t m, int32_t width, int32_t n_side);

@@ -97,6 +97,29 @@ def test_uneven_range_sizes_match_the_whole_batch(whole):
         assert torch.equal(eng.v_layer(l), ref.v_layer(l)), f"V of layer {l}"
 
 
+def test_ranges_take_tiles_for_a_shared_chip():
+    """32 images in a call of their own and as one of two ranges: the ranges'
+    products take the tile that leaves the other range its share of the chip."""
+    from paper_2506_12035_amd import binding
+
+    cfg = workload.CONFIGS[2].with_(n_layers=3, batch=64)
+    say(f"tiles of ranges: {cfg.name} B={cfg.batch}, L=3")
+    ws = workload.all_weights(cfg)
+    tiles = {}
+    for batch, parts in ((32, 1), (64, 2)):
+        eng = driver.Engine(cfg.with_(batch=batch), weights=ws, micro_batches=parts)
+        binding.profile_reset()
+        binding.profile_enable(True)
+        try:
+            eng.step(0)
+            tiles[parts] = set(binding.profile_collect())
+        finally:
+            binding.profile_enable(False)
+            binding.profile_reset()
+    assert {"gemm_o_t256x128", "gemm_fc2_t256x128"} <= tiles[1], sorted(tiles[1])
+    assert {"gemm_o_t256", "gemm_fc2_t256"} <= tiles[2], sorted(tiles[2])
+
+
 def test_step_images_touches_only_its_range():
     """marche_step_images on images [2, 4) of a 4-image cache and residual
     stream: images 0 and 1 keep every bit of x and of both caches, and images
